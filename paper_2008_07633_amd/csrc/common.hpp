@@ -110,6 +110,19 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb) {
     return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
+// The same in chunks dealt round-robin: XCD x takes chunks x, x + 8, ... of
+// `chunk` consecutive logical blocks (0: one contiguous range per XCD).  Every
+// XCD then gets a sample of the whole index range, where contiguous ranges
+// would give one XCD most of the work (nodes numbered by degree).  Blocks past
+// the last whole round of chunks keep their own index.
+__device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb, uint32_t chunk) {
+    if (chunk == 0) return xcd_remap(b, nb);
+    const uint32_t round = kNumXcd * chunk;
+    if (b >= nb / round * round) return b;
+    const uint32_t x = b % kNumXcd, i = b / kNumXcd;
+    return ((i / chunk) * kNumXcd + x) * chunk + i % chunk;
+}
+
 template <typename T> struct DT;
 template <> struct DT<double> { static constexpr sfg_dtype id = SFG_F64; };
 template <> struct DT<float> { static constexpr sfg_dtype id = SFG_F32; };

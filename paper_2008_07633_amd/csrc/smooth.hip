@@ -23,7 +23,8 @@
 //     sweeps of one column part, then the next), so the working set of a part
 //     stays in the memory-side cache;
 //   - in reduced precision, rows longer than 256 entries (hubs of power-law
-//     graphs) are taken out and swept by a whole workgroup each.
+//     graphs) are taken out and swept by a whole workgroup each, in the same
+//     launch.
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
@@ -158,15 +159,110 @@ __device__ __forceinline__ void load_row(const TIN *p, const double *mo, TA (&ou
     }
 }
 
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER>
+// Rows longer than max_len (hubs of power-law graphs), reduced precision
+// only: one workgroup per row, workgroup `wg` of `nwg` (`part`: 256 VPL
+// values of LDS).  Its 256/lpr lane groups take interleaved entries of the
+// row, four in flight each (a single one left the group waiting for every
+// gather: the 44k-node, 57M-entry coarse level of the 4M-node Chung-Lu graph
+// swept in 499 us against 429), then their partial sums are combined in LDS
+// by a fixed-shape tree, so the result is deterministic (the order differs
+// from the sequential one, which FP64 keeps).
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
+__device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *part, int32_t lpr, int32_t ldx,
+                                                int32_t ldy, const int32_t *__restrict__ long_rows,
+                                                const int32_t *__restrict__ long_cnt,
+                                                const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                                const TW *__restrict__ val, const TW *__restrict__ deg,
+                                                const TIN *__restrict__ x, const double *__restrict__ mean,
+                                                TO *__restrict__ y, TA keep, TA omega) {
+    const int t = threadIdx.x;
+    const int ngroups = 256 / lpr;
+    const int g = t / lpr, l = t % lpr;
+    const int off = l * VPL;
+    const bool active = g < ngroups;
+    double mo[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) mo[i] = (CENTER && active) ? mean[off + i] : 0.0;
+    const int32_t cnt = *long_cnt;
+    for (int32_t r = wg; r < cnt; r += nwg) {
+        const int64_t row = long_rows[r];
+        const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+        TA acc[VPL];
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
+        if (active) {
+            // four of the group's entries in flight, added in their order
+            for (int32_t j = j0 + g; j < j1; j += 4 * ngroups) {
+                int32_t cj[4];
+                TA wj[4], xv[4][VPL];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int32_t jj = j + i * ngroups < j1 ? j + i * ngroups : j1 - 1;
+                    cj[i] = col[jj];
+                    wj[i] = cvt<TA>(val[jj]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (j + i * ngroups < j1) {
+#pragma unroll
+                        for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
+                    }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
+        __syncthreads();
+        for (int st = 1; st < ngroups; st <<= 1) {
+            if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
+#pragma unroll
+                for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
+            }
+            __syncthreads();
+        }
+        if (g == 0) {
+            TA self[VPL];
+            load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
+            const TA d = cvt<TA>(deg[row]);
+            Vec<TO, VPL> out;
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                const TA a = keep * self[i];
+                const TA q = part[l * VPL + i] / d;
+                const TA bo = omega * q;
+                out.v[i] = cvt<TO>(a + bo);
+            }
+            *reinterpret_cast<Vec<TO, VPL> *>(y + row * ldy + off) = out;
+        }
+        __syncthreads();
+    }
+}
+
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER, bool LONG>
 __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, int32_t lpr_log2, int32_t ldx,
-                                               int32_t ldy, int32_t max_len, const int32_t *__restrict__ rows,
+                                               int32_t ldy, int32_t max_len, uint32_t chunk, uint32_t nlong,
+                                               const int32_t *__restrict__ long_rows,
+                                               const int32_t *__restrict__ long_cnt,
+                                               const int32_t *__restrict__ rows,
                                                const int32_t *__restrict__ rowptr,
                                                const int32_t *__restrict__ col, const TW *__restrict__ val,
                                                const TW *__restrict__ deg, const TIN *__restrict__ x,
                                                const double *__restrict__ mean, TO *__restrict__ y, TA keep,
                                                TA omega) {
-    const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    // LONG (reduced precision): the first nlong workgroups (a multiple of 8,
+    // so that the others keep their XCD) take the rows over max_len
+    if constexpr (LONG) {
+        __shared__ TA part[256 * VPL];
+        if (blockIdx.x < nlong) {
+            sweep_long_rows<TIN, TX, TO, TW, TA, VPL, CENTER>((int32_t)blockIdx.x, (int32_t)nlong, part, lpr, ldx, ldy,
+                                                             long_rows, long_cnt, rowptr, col, val, deg, x, mean, y,
+                                                             keep, omega);
+            return;
+        }
+    }
+    const uint32_t b = xcd_remap_chunked(blockIdx.x - nlong, gridDim.x - nlong, chunk);
     const int64_t t = (int64_t)b * 256 + threadIdx.x;
     if (t >= nthreads) return;
     const int64_t ri = lpr_log2 >= 0 ? (t >> lpr_log2) : t / lpr;
@@ -177,7 +273,7 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
 #pragma unroll
     for (int i = 0; i < VPL; ++i) mo[i] = CENTER ? mean[off + i] : 0.0;
     const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-    if (j1 - j0 > max_len) return;      // a long row: k_sweep_long handles it
+    if (j1 - j0 > max_len) return;      // a long row: taken by the workgroups above (FP64: k_sweep_hub64)
     TA self[VPL];
     load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
     const TA d = cvt<TA>(deg[row]);
@@ -213,74 +309,6 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
         out.v[i] = cvt<TO>(a + bo);
     }
     *reinterpret_cast<Vec<TO, VPL> *>(y + row * ldy + off) = out;
-}
-
-// Rows longer than max_len (hubs of power-law graphs), reduced precision
-// only: one workgroup per row.  Its 256/lpr lane groups take interleaved
-// entries of the row, then their partial sums are combined in LDS by a
-// fixed-shape tree, so the result is deterministic (the order differs from
-// the sequential one, which FP64 keeps).
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
-__global__ __launch_bounds__(256) void k_sweep_long(int32_t lpr, int32_t ldx, int32_t ldy,
-                                                    const int32_t *__restrict__ long_rows,
-                                                    const int32_t *__restrict__ long_cnt,
-                                                    const int32_t *__restrict__ rowptr,
-                                                    const int32_t *__restrict__ col, const TW *__restrict__ val,
-                                                    const TW *__restrict__ deg, const TIN *__restrict__ x,
-                                                    const double *__restrict__ mean, TO *__restrict__ y, TA keep,
-                                                    TA omega) {
-    __shared__ TA part[256 * VPL];
-    const int t = threadIdx.x;
-    const int ngroups = 256 / lpr;
-    const int g = t / lpr, l = t % lpr;
-    const int off = l * VPL;
-    const bool active = g < ngroups;
-    double mo[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) mo[i] = (CENTER && active) ? mean[off + i] : 0.0;
-    const int32_t cnt = *long_cnt;
-    for (int32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
-        const int64_t row = long_rows[r];
-        const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-        TA acc[VPL];
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
-        if (active) {
-            for (int32_t j = j0 + g; j < j1; j += ngroups) {
-                const int64_t c = col[j];
-                const TA wv = cvt<TA>(val[j]);
-                TA xv[VPL];
-                load_row<TIN, TX, TA, VPL, CENTER>(x + c * ldx + off, mo, xv);
-#pragma unroll
-                for (int i = 0; i < VPL; ++i) acc[i] = madd(acc[i], wv, xv[i]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
-        __syncthreads();
-        for (int st = 1; st < ngroups; st <<= 1) {
-            if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
-#pragma unroll
-                for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
-            }
-            __syncthreads();
-        }
-        if (g == 0) {
-            TA self[VPL];
-            load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
-            const TA d = cvt<TA>(deg[row]);
-            Vec<TO, VPL> out;
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) {
-                const TA a = keep * self[i];
-                const TA q = part[l * VPL + i] / d;
-                const TA bo = omega * q;
-                out.v[i] = cvt<TO>(a + bo);
-            }
-            *reinterpret_cast<Vec<TO, VPL> *>(y + row * ldy + off) = out;
-        }
-        __syncthreads();
-    }
 }
 
 // Multicolour Gauss-Seidel reading of the smoother: the listed rows (one
@@ -339,7 +367,7 @@ __global__ __launch_bounds__(256) void k_sweep_color(int64_t nthreads, int32_t l
     *reinterpret_cast<Vec<T, VPL> *>(x + row * k + off) = out;
 }
 
-// Rows handled by k_sweep_long (device list and count), and the length above
+// Rows handled by sweep_long_rows (device list and count), and the length above
 // which k_sweep skips a row.  Default: none, every row in k_sweep.
 // FP64 hub rows (listed only when the caller knows the graph has rows over
 // 256 entries): the sum k_sweep's lane group would form -- entries in stored
@@ -468,15 +496,25 @@ struct SweepShape {
     int32_t kw, ldx, ldy, vpl, u;
 };
 
-// Workgroups of the hub-row kernel (a grid-stride loop over the device-side
-// list of rows over 256 entries).  Graphs averaging 8 or more entries per row
-// (power-law graphs and their dense coarse levels) get 16,384, so that many
-// hub rows are in flight at once: 355 against 377 ms for the 4M-node Chung-Lu
-// hierarchy.  Others get 1,024, since every launch dispatches its workgroups
-// even when the list is empty: 16,384 there cost 1.4 us per sweep.
+// Workgroups for the hub rows (a grid-stride loop over the device-side list
+// of rows over 256 entries; in reduced precision the first workgroups of the
+// sweep's own launch).  Graphs averaging 8 or more entries per row (power-law
+// graphs and their dense coarse levels) get 16,384, so that many hub rows are
+// in flight at once: 355 against 377 ms for the 4M-node Chung-Lu hierarchy.
+// Others get 1,024, since every launch dispatches its workgroups even when
+// the list is empty: 16,384 there cost 1.4 us per sweep.  A multiple of 8.
 inline unsigned long_row_blocks(const sfg_csr *H) { return H->nnz >= 8 * H->n ? 16384u : 1024u; }
 
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER>
+// How k_sweep deals its workgroups to the XCDs (see xcd_remap_chunked): one
+// contiguous range of rows each keeps neighbouring rows in one L2 (meshes,
+// trees), but on a power-law graph numbered by degree it hands XCD 0 most of
+// the entries.  Graphs averaging 8 or more entries per row are dealt in
+// chunks of 64 workgroups instead: one FP32 sweep of 16 vectors on the
+// 4M-node Chung-Lu graph takes 1.44 ms against 3.57, on its 1M-node coarse
+// level 1.19 against 1.82 (chunks of 1 to 64 alike, 256: 1.57).
+inline uint32_t xcd_chunk(const sfg_csr *H) { return H->nnz >= 8 * H->n ? 64u : 0u; }
+
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER, bool LONG>
 void launch_sweep_u(const sfg_csr *H, const SweepShape &sh, const TIN *x, const double *mean, TO *y, double omega,
                     const int32_t *rows, int64_t nrows, const LongRows &lr, hipStream_t s) {
     const int lpr = sh.kw / VPL;
@@ -486,47 +524,41 @@ void launch_sweep_u(const sfg_csr *H, const SweepShape &sh, const TIN *x, const 
     // them or overwrites the rows they read (waiting on a never-recorded event
     // is a no-op)
     if (lr.side) SFG_HIP(hipStreamWaitEvent(s, lr.ez, 0));
-    hipLaunchKernelGGL((k_sweep<TIN, TX, TO, TW, TA, VPL, U, CENTER>), dim3(grid_for(nthreads, 256)), dim3(256), 0, s,
-                       nthreads, lpr, ilog2_exact(lpr), sh.ldx, sh.ldy, lr.max_len, rows, H->rowptr, H->col,
-                       (const TW *)H->val, (const TW *)H->deg, x, mean, y, (TA)(1.0 - omega), (TA)omega);
+    const unsigned nlong = LONG ? long_row_blocks(H) : 0u;
+    hipLaunchKernelGGL((k_sweep<TIN, TX, TO, TW, TA, VPL, U, CENTER, LONG>), dim3(nlong + grid_for(nthreads, 256)),
+                       dim3(256), 0, s, nthreads, lpr, ilog2_exact(lpr), sh.ldx, sh.ldy, lr.max_len, xcd_chunk(H),
+                       nlong, lr.rows, lr.count, rows, H->rowptr, H->col, (const TW *)H->val, (const TW *)H->deg, x,
+                       mean, y, (TA)(1.0 - omega), (TA)omega);
     SFG_LAUNCH_CHECK();
-    // hub rows: on the side stream after the previous main sweep, beside this one
-    hipStream_t zs = s;
-    if (lr.side && lr.rows) {
-        zs = lr.side;
-        SFG_HIP(hipStreamWaitEvent(zs, lr.es, 0));
-    }
+    // FP64 hub rows: on the side stream after the previous main sweep, beside this one
     if constexpr (sizeof(TA) == 8) {
         if (lr.rows) {
+            hipStream_t zs = s;
+            if (lr.side) {
+                zs = lr.side;
+                SFG_HIP(hipStreamWaitEvent(zs, lr.es, 0));
+            }
             hipLaunchKernelGGL((k_sweep_hub64<TIN, TX, TO, CENTER>), dim3(long_row_blocks(H)), dim3(256), 0, zs, sh.kw,
                                sh.ldx, sh.ldy, lr.rows, lr.count, H->rowptr, H->col, (const double *)H->val,
                                (const double *)H->deg, x, mean, y, 1.0 - omega, omega);
             SFG_LAUNCH_CHECK();
+            if (lr.side) {
+                SFG_HIP(hipEventRecord(lr.ez, zs));
+                SFG_HIP(hipEventRecord(lr.es, s));
+            }
         }
-    }
-    if constexpr (sizeof(TA) == 4) {
-        if (lr.rows) {
-            hipLaunchKernelGGL((k_sweep_long<TIN, TX, TO, TW, TA, VPL, CENTER>), dim3(long_row_blocks(H)), dim3(256),
-                               0, zs, lpr, sh.ldx, sh.ldy, lr.rows, lr.count, H->rowptr, H->col, (const TW *)H->val,
-                               (const TW *)H->deg, x, mean, y, (TA)(1.0 - omega), (TA)omega);
-            SFG_LAUNCH_CHECK();
-        }
-    }
-    if (lr.side && lr.rows) {
-        SFG_HIP(hipEventRecord(lr.ez, zs));
-        SFG_HIP(hipEventRecord(lr.es, s));
     }
 }
 
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER, bool LONG>
 void launch_sweep_v(const sfg_csr *H, const SweepShape &sh, const TIN *x, const double *mean, TO *y, double omega,
                     const int32_t *rows, int64_t nrows, const LongRows &lr, hipStream_t s) {
     if (sh.u <= 2)
-        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 2, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
+        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 2, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
     else if (sh.u <= 4)
-        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 4, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
+        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 4, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
     else
-        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 8, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
+        launch_sweep_u<TIN, TX, TO, TW, TA, VPL, 8, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
 }
 
 // Columns per lane: the widest run that divides kw and spans at most maxb
@@ -556,19 +588,20 @@ SweepShape full_shape(const sfg_csr *H, int32_t k) {
     return sh;
 }
 
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, bool CENTER>
+// LONG: lr lists the rows over lr.max_len (reduced precision), and the launch takes them too.
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, bool CENTER, bool LONG = false>
 void launch_sweep(const sfg_csr *H, const SweepShape &sh, const TIN *x, const double *mean, TO *y, double omega,
                   hipStream_t s, const int32_t *rows = nullptr, int64_t nrows = -1, const LongRows &lr = LongRows()) {
     if (nrows < 0) nrows = H->n;
     constexpr int maxv = 64 / (int)sizeof(TX);
     switch (sh.vpl) {
-        case 1: launch_sweep_v<TIN, TX, TO, TW, TA, 1, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
-        case 2: launch_sweep_v<TIN, TX, TO, TW, TA, 2, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
-        case 4: launch_sweep_v<TIN, TX, TO, TW, TA, 4, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
-        case 8: launch_sweep_v<TIN, TX, TO, TW, TA, 8, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
+        case 1: launch_sweep_v<TIN, TX, TO, TW, TA, 1, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
+        case 2: launch_sweep_v<TIN, TX, TO, TW, TA, 2, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
+        case 4: launch_sweep_v<TIN, TX, TO, TW, TA, 4, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
+        case 8: launch_sweep_v<TIN, TX, TO, TW, TA, 8, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s); return;
         case 16:
             if constexpr (maxv >= 16) {
-                launch_sweep_v<TIN, TX, TO, TW, TA, 16, CENTER>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
+                launch_sweep_v<TIN, TX, TO, TW, TA, 16, CENTER, LONG>(H, sh, x, mean, y, omega, rows, nrows, lr, s);
                 return;
             }
             break;
@@ -625,7 +658,7 @@ struct SmoothPlan {
     int32_t *lflag, *lpos, *lrows, *lscan;
 };
 
-constexpr int32_t kLongRow = 256;   // reduced precision: rows above this go to k_sweep_long
+constexpr int32_t kLongRow = 256;   // reduced precision: rows above this go to sweep_long_rows
 
 __global__ void k_long_flag(int64_t n, const int32_t *__restrict__ rowptr, int32_t len, int32_t *flag) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -698,8 +731,7 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
         lr.count = p.lpos + n;
         lr.max_len = kLongRow;
     }
-    // graphs whose hub rows take long (power-law graphs, their dense coarse
-    // levels; FP64 hub rows when listed) sweep them on a side stream
+    // FP64 hub rows, when listed, are swept on a side stream
     struct Side {
         hipEvent_t es = nullptr, ez = nullptr;
         ~Side() {
@@ -707,7 +739,7 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
             if (ez) (void)hipEventDestroy(ez);
         }
     } side;
-    if (lr.rows && sweeps > 0 && (sizeof(TA) == 8 || H->nnz >= 8 * H->n)) {
+    if (sizeof(TA) == 8 && lr.rows && sweeps > 0) {
         lr.side = side_stream();
         SFG_HIP(hipEventCreateWithFlags(&side.es, hipEventDisableTiming));
         SFG_HIP(hipEventCreateWithFlags(&side.ez, hipEventDisableTiming));
@@ -717,6 +749,7 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
     }
     // a3: sweeps, column part by column part; the first sweep of a part
     // centres on the fly from x0, the last writes the part's columns of xout
+    constexpr bool kLong = sizeof(TA) == 4;
     const SweepShape ps = part_shape<TX>(H, k);
     for (int32_t c0 = 0; c0 < k; c0 += ps.kw) {
         SweepShape first = ps, mid = ps;
@@ -728,20 +761,20 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
             TX *dst = (t % 2 == 0) ? b0 : b1;
             if (t == 0) {
                 if (last && final_f32)
-                    launch_sweep<double, TX, float, TW, TA, true>(H, sh, x0 + c0, p.mean + c0,
+                    launch_sweep<double, TX, float, TW, TA, true, kLong>(H, sh, x0 + c0, p.mean + c0,
                                                                   (float *)xout + c0, omega, s, nullptr, -1, lr);
                 else
-                    launch_sweep<double, TX, TX, TW, TA, true>(H, sh, x0 + c0, p.mean + c0,
+                    launch_sweep<double, TX, TX, TW, TA, true, kLong>(H, sh, x0 + c0, p.mean + c0,
                                                                last ? (TX *)xout + c0 : dst, omega, s, nullptr, -1,
                                                                lr);
                 continue;
             }
             const TX *src = (t % 2 == 0) ? b1 : b0;
             if (last && final_f32)
-                launch_sweep<TX, TX, float, TW, TA, false>(H, sh, src, nullptr, (float *)xout + c0, omega, s, nullptr,
+                launch_sweep<TX, TX, float, TW, TA, false, kLong>(H, sh, src, nullptr, (float *)xout + c0, omega, s, nullptr,
                                                            -1, lr);
             else
-                launch_sweep<TX, TX, TX, TW, TA, false>(H, sh, src, nullptr, last ? (TX *)xout + c0 : dst, omega, s,
+                launch_sweep<TX, TX, TX, TW, TA, false, kLong>(H, sh, src, nullptr, last ? (TX *)xout + c0 : dst, omega, s,
                                                         nullptr, -1, lr);
         }
     }
@@ -906,7 +939,7 @@ __global__ __launch_bounds__(64) void k_mpk_build(int64_t n, const int32_t *__re
     using C = MpkCaps<H>;
     using Col = typename C::Col;
     // rows the single sweep forms in entry order: all FP64 rows (sfg_smooth keeps them in k_sweep), reduced
-    // precision rows up to kLongRow entries (longer ones go to k_sweep_long's lane-group sums there)
+    // precision rows up to kLongRow entries (longer ones take sweep_long_rows' lane-group sums there)
     constexpr int kMaxRow = sizeof(TW) == 8 ? C::kEnt : (kLongRow < C::kEnt ? kLongRow : C::kEnt);
     __shared__ int32_t keys[C::kHash];
     __shared__ int32_t vals[C::kHash];
