@@ -40,7 +40,8 @@ void convert_weights(const void *w, sfg_dtype wt, sfg_dtype want, int64_t m, voi
 int64_t spanning_tree_gpu(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
                           const uint8_t *allowed, uint8_t *in_tree, DevArena &A, hipStream_t s);
 void level_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const sfg_csr *G,
-                      const uint8_t *tree, int32_t k, sfg_dtype storage, NodeOrder *no, DevArena &A, hipStream_t s);
+                      const uint8_t *tree, int32_t k, sfg_dtype storage, int32_t max_row, NodeOrder *no, DevArena &A,
+                      hipStream_t s);
 sfg_csr relabel_csr(const sfg_csr *H, const int32_t *order, const int32_t *inv, DevArena &A, hipStream_t s);
 void gather_block(int64_t n, int32_t k, const int32_t *order, const double *src, double *dst, hipStream_t s);
 size_t smooth_ordered_workspace_bytes(int64_t n, int32_t k, sfg_dtype storage);
@@ -458,7 +459,7 @@ void multilevel_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *
         }
         // the sweeps on G_l, in the level's node numbering; affinities per edge id, numbering-free
         NodeOrder &no = ord[l];
-        level_node_order(F.n, F.m, F.u, F.v, F.w64, &G, l == 0 ? tree0 : nullptr, p->k, vt, &no, A, s);
+        level_node_order(F.n, F.m, F.u, F.v, F.w64, &G, l == 0 ? tree0 : nullptr, p->k, vt, max_row, &no, A, s);
         const double *xl = x0 + (size_t)l * n * p->k;
         const int32_t *au = F.u, *av = F.v;
         sfg_csr Gs = G;

@@ -358,18 +358,24 @@ void make_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, c
 // (`tree`: its edges marked 1; nullptr = compute the maximum one) is taken
 // when the level has at least kOrderMinRows nodes, its block of k vectors
 // exceeds kOrderMinBlock bytes (kOrderMinBlockNoTree when the tree would have
-// to be computed first) and more than half of G_l's entries reach beyond
-// kNearRows rows.  The 4M-node Chung-Lu level-0 graph (input ids in
-// expected-degree order) sweeps in 1.38 ms in preorder against 3.57 ms (FP32)
-// and 5.9 against 7.3 ms (FP64); its FP32 hierarchy took 293 ms against 342.
-// Its 1M-node level 1 in FP64 (126 MB block, mostly served from the 256 MB
-// memory-side cache) gained less than its spanning tree and relabelling cost.
-// SFG_NODE_ORDER as above; results do not depend on the choice.
+// to be computed first), its longest row is at most kOrderMaxRow times the
+// average one and more than half of G_l's entries reach beyond kNearRows
+// rows.  On the 2M-point k-NN graph (ids random in space) the FP32 hierarchy
+// with 16 vectors and 20 sweeps takes 32.1 ms in preorder against 34.5 (FP64
+// 39.0 against 38.8).  Power-law graphs have no small-scale locality to gain:
+// the 4M-node Chung-Lu level 0 sweeps in 1.38 ms in preorder against 1.43 in
+// its own numbering (FP32), and the tree layout, relabelled rows and gathered
+// blocks cost its hierarchy 265 ms against 248 (FP64 513 against 460).  Their
+// hubs give them away: longest row 437 times the average, against 3 on the
+// k-NN graph.
+// SFG_NODE_ORDER as above; results do not depend on the choice.  max_row: the
+// longest row, or -1 when the caller does not know it.
 constexpr double kOrderMinBlock = 96.0 * (1 << 20);
 constexpr double kOrderMinBlockNoTree = 256.0 * (1 << 20);
+constexpr int64_t kOrderMaxRow = 32;
 
 void level_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const sfg_csr *G,
-                      const uint8_t *tree, int32_t k, sfg_dtype storage, NodeOrder *no, DevArena &A,
+                      const uint8_t *tree, int32_t k, sfg_dtype storage, int32_t max_row, NodeOrder *no, DevArena &A,
                       hipStream_t s) {
     no->decided = true;
     no->use = false;
@@ -378,6 +384,13 @@ void level_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, 
     if (mode == 2) {
         const double block = (double)n * k * dtype_size(storage);
         if (n < kOrderMinRows || block <= (tree ? kOrderMinBlock : kOrderMinBlockNoTree)) return;
+        if (max_row < 0) {
+            int32_t *mr = A.alloc<int32_t>(1);
+            max_row_length(G, mr, s);
+            SFG_HIP(hipMemcpyAsync(&max_row, mr, 4, hipMemcpyDeviceToHost, s));
+            SFG_HIP(hipStreamSynchronize(s));
+        }
+        if (max_row * n > kOrderMaxRow * G->nnz) return;
         unsigned long long *far = A.alloc<unsigned long long>(1);
         fill_i32((int32_t *)far, 2, 0, s);
         far_entries(G, kNearRows, far, s);
