@@ -183,6 +183,13 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, int32_t *scr
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 void fill_u8(uint8_t *p, int64_t n, uint8_t v, hipStream_t s);
 
+// The included edges of a list, sorted by (larger end, edge id).
+struct EdgeSort {
+    int32_t *v, *e;              // [m + 1] larger end and id, in order
+    const int32_t *count;        // device: how many
+    int32_t *spare0, *spare1;    // [m + 1] buffers the result does not occupy
+};
+
 // Node numbering for the sweeps of a sparsify call or of one hierarchy level
 // (the rules are with score_level and level_node_order).
 struct NodeOrder {
