@@ -159,17 +159,92 @@ __device__ __forceinline__ void load_row(const TIN *p, const double *mo, TA (&ou
     }
 }
 
+// The epilogue of a row whose sum the lanes hold: y = (1 - omega) x + omega s / d.
+template <typename TIN, typename TX, typename TO, typename TA, int VPL, bool CENTER>
+__device__ __forceinline__ void store_row(const TIN *__restrict__ xrow, const double (&mo)[VPL], const TA (&sum)[VPL],
+                                          TA d, TO *__restrict__ yrow, TA keep, TA omega) {
+    TA self[VPL];
+    load_row<TIN, TX, TA, VPL, CENTER>(xrow, mo, self);
+    Vec<TO, VPL> out;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        const TA a = keep * self[i];
+        const TA q = sum[i] / d;
+        const TA bo = omega * q;
+        out.v[i] = cvt<TO>(a + bo);
+    }
+    *reinterpret_cast<Vec<TO, VPL> *>(yrow) = out;
+}
+
 // Rows longer than max_len (hubs of power-law graphs), reduced precision
-// only: one workgroup per row, workgroup `wg` of `nwg` (`part`: 256 VPL
-// values of LDS).  Its 256/lpr lane groups take interleaved entries of the
-// row, four in flight each (a single one left the group waiting for every
-// gather: the 44k-node, 57M-entry coarse level of the 4M-node Chung-Lu graph
-// swept in 499 us against 429), then their partial sums are combined in LDS
-// by a fixed-shape tree, so the result is deterministic (the order differs
-// from the sequential one, which FP64 keeps).
+// only, taken by workgroup `wg` of `nwg` (`part`: 256 VPL values of LDS).  The
+// sum of such a row is defined by 256/lpr lane groups that take interleaved
+// entries and are then combined by a fixed-shape tree, so it is deterministic
+// (the order differs from the sequential one, which FP64 keeps).  Up to
+// kWaveRow entries, where lpr is a power of two, one wavefront forms it: it
+// plays the four wavefronts' groups in turn (four sums per lane, 4 or 8
+// gathers in flight) and combines them with lane shuffles, no barrier; the
+// workgroup's four wavefronts take four rows.  Longer rows, and other lpr,
+// take the whole workgroup.  Both make the same additions.  One FP32 sweep of
+// 16 vectors on the 1M-node coarse level of the 4M-node Chung-Lu graph (36,099
+// such rows) takes 1.12 ms against 1.19 with a workgroup per row, its whole
+// hierarchy 184 ms against 191; with kWaveRow = 1024 the sweeps of the two
+// coarsest levels were 2 to 4% slower.
+constexpr int32_t kWaveRow = 4096;
+
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
-__device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *part, int32_t lpr, int32_t ldx,
-                                                int32_t ldy, const int32_t *__restrict__ long_rows,
+__device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_t ldy, int64_t row, int32_t j0,
+                                                int32_t j1, const int32_t *__restrict__ col,
+                                                const TW *__restrict__ val, const TW *__restrict__ deg,
+                                                const TIN *__restrict__ x, const double *__restrict__ mean,
+                                                TO *__restrict__ y, TA keep, TA omega) {
+    constexpr int kSteps = VPL <= 4 ? 2 : 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int gw = kWave / lpr, g = lane / lpr, off = (lane - g * lpr) * VPL;
+    double mo[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) mo[i] = CENTER ? mean[off + i] : 0.0;
+    TA acc[4][VPL];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) acc[w][i] = TA(0);
+    for (int32_t j = j0 + g; j < j1; j += kSteps * 4 * gw) {
+        int32_t cj[kSteps * 4];
+        TA wj[kSteps * 4], xv[kSteps * 4][VPL];
+#pragma unroll
+        for (int q = 0; q < kSteps * 4; ++q) {
+            const int32_t jj = j + q * gw < j1 ? j + q * gw : j1 - 1;
+            cj[q] = col[jj];
+            wj[q] = cvt<TA>(val[jj]);
+        }
+#pragma unroll
+        for (int q = 0; q < kSteps * 4; ++q)
+            load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[q] * ldx + off, mo, xv[q]);
+#pragma unroll
+        for (int q = 0; q < kSteps * 4; ++q)
+            if (j + q * gw < j1) {
+#pragma unroll
+                for (int i = 0; i < VPL; ++i) acc[q % 4][i] = madd(acc[q % 4][i], wj[q], xv[q][i]);
+            }
+    }
+    for (int st = 1; st < gw; st <<= 1)
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) acc[w][i] += __shfl_down(acc[w][i], st * lpr, kWave);
+    if (g == 0) {
+        TA sum[VPL];
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) sum[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+        store_row<TIN, TX, TO, TA, VPL, CENTER>(x + row * ldx + off, mo, sum, cvt<TA>(deg[row]), y + row * ldy + off,
+                                                keep, omega);
+    }
+}
+
+template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
+__device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *part, int32_t lpr, int32_t lpr_log2,
+                                                int32_t ldx, int32_t ldy, const int32_t *__restrict__ long_rows,
                                                 const int32_t *__restrict__ long_cnt,
                                                 const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                 const TW *__restrict__ val, const TW *__restrict__ deg,
@@ -184,59 +259,66 @@ __device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *par
 #pragma unroll
     for (int i = 0; i < VPL; ++i) mo[i] = (CENTER && active) ? mean[off + i] : 0.0;
     const int32_t cnt = *long_cnt;
-    for (int32_t r = wg; r < cnt; r += nwg) {
-        const int64_t row = long_rows[r];
-        const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-        TA acc[VPL];
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
-        if (active) {
-            // four of the group's entries in flight, added in their order
-            for (int32_t j = j0 + g; j < j1; j += 4 * ngroups) {
-                int32_t cj[4];
-                TA wj[4], xv[4][VPL];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int32_t jj = j + i * ngroups < j1 ? j + i * ngroups : j1 - 1;
-                    cj[i] = col[jj];
-                    wj[i] = cvt<TA>(val[jj]);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (j + i * ngroups < j1) {
-#pragma unroll
-                        for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
-                    }
+    const bool waves = lpr_log2 >= 0 && lpr <= kWave;
+    for (int64_t r0 = wg; r0 < cnt; r0 += 4 * (int64_t)nwg) {
+        if (waves) {
+            const int64_t r = r0 + (int64_t)(t / kWave) * nwg;
+            if (r < cnt) {
+                const int64_t row = long_rows[r];
+                const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+                if (j1 - j0 <= kWaveRow)
+                    sweep_long_wave<TIN, TX, TO, TW, TA, VPL, CENTER>(lpr, ldx, ldy, row, j0, j1, col, val, deg, x,
+                                                                      mean, y, keep, omega);
             }
         }
+        for (int64_t r = r0; r < cnt && r < r0 + 4 * (int64_t)nwg; r += nwg) {
+            const int64_t row = long_rows[r];
+            const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+            if (waves && j1 - j0 <= kWaveRow) continue;
+            TA acc[VPL];
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
-        __syncthreads();
-        for (int st = 1; st < ngroups; st <<= 1) {
-            if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
+            for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
+            if (active) {
+                // four of the group's entries in flight, added in their order
+                for (int32_t j = j0 + g; j < j1; j += 4 * ngroups) {
+                    int32_t cj[4];
+                    TA wj[4], xv[4][VPL];
 #pragma unroll
-                for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
+                    for (int i = 0; i < 4; ++i) {
+                        const int32_t jj = j + i * ngroups < j1 ? j + i * ngroups : j1 - 1;
+                        cj[i] = col[jj];
+                        wj[i] = cvt<TA>(val[jj]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (j + i * ngroups < j1) {
+#pragma unroll
+                            for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
+                        }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
+            __syncthreads();
+            for (int st = 1; st < ngroups; st <<= 1) {
+                if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
+#pragma unroll
+                    for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
+                }
+                __syncthreads();
+            }
+            if (g == 0) {
+                TA sum[VPL];
+#pragma unroll
+                for (int i = 0; i < VPL; ++i) sum[i] = part[l * VPL + i];
+                store_row<TIN, TX, TO, TA, VPL, CENTER>(x + row * ldx + off, mo, sum, cvt<TA>(deg[row]),
+                                                        y + row * ldy + off, keep, omega);
             }
             __syncthreads();
         }
-        if (g == 0) {
-            TA self[VPL];
-            load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
-            const TA d = cvt<TA>(deg[row]);
-            Vec<TO, VPL> out;
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) {
-                const TA a = keep * self[i];
-                const TA q = part[l * VPL + i] / d;
-                const TA bo = omega * q;
-                out.v[i] = cvt<TO>(a + bo);
-            }
-            *reinterpret_cast<Vec<TO, VPL> *>(y + row * ldy + off) = out;
-        }
-        __syncthreads();
     }
 }
 
@@ -256,9 +338,9 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
     if constexpr (LONG) {
         __shared__ TA part[256 * VPL];
         if (blockIdx.x < nlong) {
-            sweep_long_rows<TIN, TX, TO, TW, TA, VPL, CENTER>((int32_t)blockIdx.x, (int32_t)nlong, part, lpr, ldx, ldy,
-                                                             long_rows, long_cnt, rowptr, col, val, deg, x, mean, y,
-                                                             keep, omega);
+            sweep_long_rows<TIN, TX, TO, TW, TA, VPL, CENTER>((int32_t)blockIdx.x, (int32_t)nlong, part, lpr,
+                                                             lpr_log2, ldx, ldy, long_rows, long_cnt, rowptr, col,
+                                                             val, deg, x, mean, y, keep, omega);
             return;
         }
     }
