@@ -439,6 +439,16 @@ void multilevel_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *
         LevelGraph &F = lv[l];
         if (F.n <= 2 || F.m == 0) break;
         const void *wf = f64 ? (const void *)F.w64 : (const void *)F.w32;
+        // what the level leaves behind first; the rest goes back to the arena
+        // at the end of the level, unless the node numbering is made among it
+        LevelGraph &C = lv[l + 1];
+        F.agg = A.alloc<int32_t>(F.n + 1);
+        C.u = A.alloc<int32_t>(F.m + 1);
+        C.v = A.alloc<int32_t>(F.m + 1);
+        C.w64 = A.alloc<double>(F.m + 1);
+        F.crep = A.alloc<int32_t>(F.m + 1);
+        if (!f64) C.w32 = A.alloc<float>(F.m + 1);
+        const DevArena::Mark mark = A.mark();
         int32_t *rowptr = A.alloc<int32_t>(F.n + 1);
         int32_t *col = A.alloc<int32_t>(2 * F.m + 1);
         int32_t *eid = A.alloc<int32_t>(2 * F.m + 1);
@@ -481,12 +491,6 @@ void multilevel_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *
         void *aff = A.raw((F.m + 1) * dtype_size(vt));
         const size_t wsa = affinity_workspace_bytes(F.n, p->k);
         affinity(x, vt, F.n, p->k, F.m, au, av, aff, vt, A.raw(wsa), wsa, s);
-        LevelGraph &C = lv[l + 1];
-        F.agg = A.alloc<int32_t>(F.n + 1);
-        C.u = A.alloc<int32_t>(F.m + 1);
-        C.v = A.alloc<int32_t>(F.m + 1);
-        C.w64 = A.alloc<double>(F.m + 1);
-        F.crep = A.alloc<int32_t>(F.m + 1);
         // the pointer step reads the CSR in the working precision; the coarse
         // weights are always FP64 sums of the FP64 fine weights
         int64_t nc = 0, mc = 0;
@@ -495,10 +499,8 @@ void multilevel_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *
                 wsg, s);
         C.n = nc;
         C.m = mc;
-        if (!f64) {
-            C.w32 = A.alloc<float>(mc + 1);
-            convert_weights(C.w64, SFG_F64, SFG_F32, mc, C.w32, s);
-        }
+        if (!f64) convert_weights(C.w64, SFG_F64, SFG_F32, mc, C.w32, s);
+        if (!no.use) A.release(mark);
         built = l + 2;
         if (nc == F.n) break;   // no progress (cannot happen for a connected graph with n >= 2)
     }

@@ -206,16 +206,23 @@ struct NodeOrder {
 // from chunks of at least 256 MB.  A call that ends with finish() (its stream
 // drained) hands its chunks to a per-device cache (up to 16 GiB) that later
 // calls reuse; otherwise (an error path, work possibly in flight) they are
-// freed stream-ordered.  SFG_FAIL_ALLOC_AFTER=n makes the (n+1)-th buffer
-// request fail, to test the error path.
+// freed stream-ordered.  release(mark()) gives back everything taken since
+// the mark, for later requests of the same call: its users' work must be on
+// the arena's stream (or joined to it), so that the next user runs after them.
+// SFG_FAIL_ALLOC_AFTER=n makes the (n+1)-th buffer request fail, to test the
+// error path.
 struct DevArena {
     struct Chunk {
         void *p;
         size_t size;
     };
     hipStream_t s;
+    struct Mark {
+        size_t chunks, used;
+    };
     std::vector<Chunk> chunks;
-    size_t used = 0;   // bytes carved from the last chunk
+    std::vector<Chunk> spare;   // released chunks of this call
+    size_t used = 0;            // bytes carved from the last of `chunks`
     int dev = 0;
     bool synced = false;
     long fail_after = -1;
@@ -225,6 +232,8 @@ struct DevArena {
     DevArena(const DevArena &) = delete;
     DevArena &operator=(const DevArena &) = delete;
     void *raw(size_t bytes);
+    Mark mark() const { return {chunks.size(), used}; }
+    void release(const Mark &m);
     void finish();   // wait for the stream; the chunks may then be cached
     template <typename T>
     T *alloc(size_t n) {

@@ -110,7 +110,16 @@ void DevArena::finish() {
     synced = true;
 }
 
+void DevArena::release(const Mark &m) {
+    while (chunks.size() > m.chunks) {
+        spare.push_back(chunks.back());
+        chunks.pop_back();
+    }
+    used = m.used;
+}
+
 DevArena::~DevArena() {
+    chunks.insert(chunks.end(), spare.begin(), spare.end());
     if (synced && dev >= 0) {
         std::lock_guard<std::mutex> lk(g_cache_mu);
         for (const Chunk &c : chunks) {
@@ -136,18 +145,20 @@ void *DevArena::raw(size_t bytes) {
         used += need;
         return p;
     }
+    // the smallest released or cached chunk that fits
     Chunk c{nullptr, 0};
-    if (dev >= 0) {   // the smallest cached chunk that fits
+    auto take = [&](std::vector<Chunk> &from) {
+        size_t best = from.size();
+        for (size_t i = 0; i < from.size(); ++i)
+            if (from[i].size >= need && (best == from.size() || from[i].size < from[best].size)) best = i;
+        if (best == from.size()) return false;
+        c = from[best];
+        from.erase(from.begin() + (long)best);
+        return true;
+    };
+    if (!take(spare) && dev >= 0) {
         std::lock_guard<std::mutex> lk(g_cache_mu);
-        auto &cache = g_cache[dev];
-        size_t best = cache.size();
-        for (size_t i = 0; i < cache.size(); ++i)
-            if (cache[i].size >= need && (best == cache.size() || cache[i].size < cache[best].size)) best = i;
-        if (best < cache.size()) {
-            c = cache[best];
-            cache.erase(cache.begin() + (long)best);
-            g_cached[dev] -= c.size;
-        }
+        if (take(g_cache[dev])) g_cached[dev] -= c.size;
     }
     if (!c.p) {
         c.size = need > kChunkBytes ? need : kChunkBytes;
@@ -471,6 +482,10 @@ ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t
 void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const float *w32,
                  const uint8_t *base, const sfg_params *p, const double *x0, uint8_t *keep, sfg_level_report *rep,
                  DevArena &A, hipStream_t s, int64_t k_take, NodeOrder *no) {
+    // the level's buffers go back to the arena at the end, unless the node
+    // numbering, which later levels or batches use, is made among them
+    const bool scoped = !no || no->decided;
+    const DevArena::Mark mark = A.mark();
     const uint8_t *hmask = (p->embed == SFG_EMBED_GRAPH) ? nullptr : base;
     Timer tm(s);
     tm.start();
@@ -604,6 +619,7 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         SFG_LAUNCH_CHECK();
     }
     float ms_select = tm.stop();
+    if (scoped) A.release(mark);
     if (rep) {
         rep->ms_smooth = ms_smooth;
         rep->ms_score = ms_score;
