@@ -50,7 +50,7 @@ int smooth_ordered(const sfg_csr *H, const int32_t *order, int32_t k, int32_t sw
                    hipStream_t s, int32_t max_row);
 void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const float *w32,
                  const uint8_t *base, const sfg_params *p, const double *x0, uint8_t *keep, sfg_level_report *rep,
-                 DevArena &A, hipStream_t s, int64_t k_take, NodeOrder *no);
+                 DevArena &A, hipStream_t s, int64_t k_take, NodeOrder *no, int64_t base_edges);
 
 namespace {
 
@@ -528,7 +528,7 @@ void multilevel_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *
         uint8_t *kp = (l == 1) ? keep : A.alloc<uint8_t>(F.m + 1);
         sfg_level_report *lr = rep ? &rep->level[l - 1] : nullptr;
         score_level(F.n, F.m, F.u, F.v, F.w64, F.w32, base, p, x0 + (size_t)(l - 1) * n * p->k, kp, lr, A, s, -1,
-                    &ord[l - 1]);
+                    &ord[l - 1], -1);
         P = kp;
     }
 }

@@ -183,6 +183,43 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, int32_t *scr
 void fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 void fill_u8(uint8_t *p, int64_t n, uint8_t v, hipStream_t s);
 
+// Scalars read back to pinned host memory.  add() enqueues a copy of one value
+// of at most 8 bytes; wait() blocks until every copy added so far is done
+// (an event, not the stream: work enqueued after the last add() keeps the GPU
+// busy meanwhile), then get() gives the values.  The buffer and its event come
+// from a per-device pool of at most kPoolMax free ones and go back when the
+// object dies (after its copies have landed).
+class HostRead {
+  public:
+    explicit HostRead(hipStream_t s);
+    ~HostRead();
+    HostRead(const HostRead &) = delete;
+    HostRead &operator=(const HostRead &) = delete;
+    template <typename T>
+    int add(const T *device) {
+        static_assert(sizeof(T) <= 8, "one scalar");
+        return add_bytes(device, sizeof(T));
+    }
+    void wait();
+    template <typename T>
+    T get(int slot) const {
+        T v;
+        std::memcpy(&v, static_cast<const char *>(it_.host) + 8 * slot, sizeof(T));
+        return v;
+    }
+    struct Item {
+        void *host = nullptr;
+        hipEvent_t ev = nullptr;
+    };
+
+  private:
+    int add_bytes(const void *device, size_t bytes);
+    Item it_;
+    hipStream_t s_;
+    int dev_ = 0, used_ = 0;
+    bool pending_ = false;
+};
+
 // The included edges of a list, sorted by (larger end, edge id).
 struct EdgeSort {
     int32_t *v, *e;              // [m + 1] larger end and id, in order

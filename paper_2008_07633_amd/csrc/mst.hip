@@ -498,10 +498,10 @@ int64_t boruvka(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const 
             }
             // a round on an empty list hooks nothing, so the rounds after the last one change nothing
             relist(true);
-            int32_t left = 0;
-            SFG_HIP(hipMemcpyAsync(&left, cnt + cur, sizeof(left), hipMemcpyDeviceToHost, s));
-            SFG_HIP(hipStreamSynchronize(s));
-            if (left == 0) break;
+            HostRead left(s);
+            left.add(cnt + cur);
+            left.wait();
+            if (left.get<int32_t>(0) == 0) break;
             SFG_REQUIRE(round < 72, SFG_EHIP, "spanning_tree: too many rounds");
             finish_round();
             ++round;
@@ -509,10 +509,10 @@ int64_t boruvka(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const 
     }
     hipLaunchKernelGGL(k_mst_count, dim3(std::min(grid_for(n, 256), 512u)), dim3(256), 0, s, n, par, cnt + kCntComps);
     SFG_LAUNCH_CHECK();
-    int32_t comps = 0;
-    SFG_HIP(hipMemcpyAsync(&comps, cnt + kCntComps, sizeof(comps), hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
-    return comps;
+    HostRead comps(s);
+    comps.add(cnt + kCntComps);
+    comps.wait();
+    return comps.get<int32_t>(0);
 }
 
 // ------------------------------------------------------------------ small graphs: one workgroup
@@ -647,10 +647,10 @@ int64_t forest(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const T
     int32_t *comps = A.alloc<int32_t>(1);
     if (m <= 8 * kSmallThreads) launch_small<TW, 8>(n, m, u, v, w, allowed, in_tree, comps, s);
     else launch_small<TW, kSmallMaxItems>(n, m, u, v, w, allowed, in_tree, comps, s);
-    int32_t h = 0;
-    SFG_HIP(hipMemcpyAsync(&h, comps, sizeof(h), hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
-    return h;
+    HostRead h(s);
+    h.add(comps);
+    h.wait();
+    return h.get<int32_t>(0);
 }
 
 }  // namespace

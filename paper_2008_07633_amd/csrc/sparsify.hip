@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <functional>
 #include <mutex>
 #include <numeric>
 #include <vector>
@@ -231,8 +232,9 @@ __global__ void k_keep_add(int64_t nc, const int32_t *__restrict__ cand, const u
 
 }  // namespace
 
+// Enqueues the check and the copy of its verdict; check_edges() waits for it.
 void validate_edges(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
-                    DevArena &A, hipStream_t s) {
+                    HostRead &verdict, DevArena &A, hipStream_t s) {
     SFG_REQUIRE(n >= 1 && m >= 0, SFG_EINVAL, "edge list: need n >= 1, m >= 0");
     SFG_REQUIRE(wt == SFG_F64 || wt == SFG_F32, SFG_EINVAL, "edge list: weights must be F64 or F32");
     if (m == 0) return;
@@ -245,17 +247,22 @@ void validate_edges(int64_t n, int64_t m, const int32_t *u, const int32_t *v, co
         hipLaunchKernelGGL(k_validate<float>, dim3(grid_for(m, 256)), dim3(256), 0, s, n, m, u, v, (const float *)w,
                            flag);
     SFG_LAUNCH_CHECK();
-    uint32_t h = 0;
-    SFG_HIP(hipMemcpyAsync(&h, flag, sizeof(h), hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
+    verdict.add(flag);
+}
+
+void check_edges(int64_t m, HostRead &verdict) {
+    if (m == 0) return;
+    verdict.wait();
+    const uint32_t h = verdict.get<uint32_t>(0);
     if (h & 1u) fail(SFG_EINVAL, "edge list: an edge has u >= v or an id out of range");
     if (h & 2u) fail(SFG_EINVAL, "edge list: not sorted by (u, v) or has duplicates");
     if (h & 4u) fail(SFG_EINVAL, "edge list: a weight is not finite and positive");
 }
 
-// Edge ids e with mask[e] == want, ascending; returns their count (synchronises).
-int64_t compact_ids(const uint8_t *mask, uint8_t want, int64_t m, int32_t *out, DevArena &A, hipStream_t s) {
-    if (m == 0) return 0;
+// Edge ids e with mask[e] == want, ascending; enqueues only.  Returns the
+// device address of their count (m >= 1).
+const int32_t *compact_ids_async(const uint8_t *mask, uint8_t want, int64_t m, int32_t *out, DevArena &A,
+                                 hipStream_t s) {
     int32_t *flags = A.alloc<int32_t>(m + 1);
     int32_t *pos = A.alloc<int32_t>(m + 1);
     int32_t *scr = A.alloc<int32_t>(scan_scratch_ints(m + 1));
@@ -264,10 +271,16 @@ int64_t compact_ids(const uint8_t *mask, uint8_t want, int64_t m, int32_t *out, 
     exclusive_scan_i32(flags, pos, m, scr, s);
     hipLaunchKernelGGL(k_scatter_ids, dim3(grid_for(m, 256)), dim3(256), 0, s, m, flags, pos, out);
     SFG_LAUNCH_CHECK();
-    int32_t cnt = 0;
-    SFG_HIP(hipMemcpyAsync(&cnt, pos + m, sizeof(cnt), hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
-    return cnt;
+    return pos + m;
+}
+
+// The same, returning the count (synchronises).
+int64_t compact_ids(const uint8_t *mask, uint8_t want, int64_t m, int32_t *out, DevArena &A, hipStream_t s) {
+    if (m == 0) return 0;
+    HostRead cnt(s);
+    cnt.add(compact_ids_async(mask, want, m, out, A, s));
+    cnt.wait();
+    return cnt.get<int32_t>(0);
 }
 
 void convert_weights(const void *w, sfg_dtype wt, sfg_dtype want, int64_t m, void *out, hipStream_t s) {
@@ -309,6 +322,34 @@ struct Timer {
         float ms = 0;
         SFG_HIP(hipEventElapsedTime(&ms, a, b));
         return ms;
+    }
+};
+
+}  // namespace
+
+namespace {
+
+// Stage times of a scored level: an event at every boundary, read once the
+// last one has completed, so that measuring a stage does not drain the stream.
+struct StageClock {
+    static constexpr int kMax = 5;
+    hipEvent_t ev[kMax] = {};
+    int n = 0;
+    hipStream_t s;
+    explicit StageClock(hipStream_t st) : s(st) {}
+    ~StageClock() {
+        for (int i = 0; i < n; ++i) (void)hipEventDestroy(ev[i]);
+    }
+    void mark() {
+        SFG_HIP(hipEventCreate(&ev[n]));
+        ++n;
+        SFG_HIP(hipEventRecord(ev[n - 1], s));
+    }
+    void wait() { SFG_HIP(hipEventSynchronize(ev[n - 1])); }
+    float ms(int i) {   // from mark i to mark i + 1
+        float t = 0;
+        SFG_HIP(hipEventElapsedTime(&t, ev[i], ev[i + 1]));
+        return t;
     }
 };
 
@@ -424,6 +465,8 @@ namespace {
 // The scoring graph's CSR with values of type vt, in the numbering the sweeps
 // use: the node order is decided at the call's first scored level (see
 // NodeOrder above) and applied by copying rows in their stored entry order.
+// known_nnz: its entries, or -1 (read back then, with what else the host needs;
+// `meanwhile` enqueues more work before the host waits).
 struct ScoringGraph {
     sfg_csr H{};
     int32_t max_row = -1;   // longest row when the values are FP64 (FP64 hub rows are summed through LDS)
@@ -431,7 +474,8 @@ struct ScoringGraph {
 
 ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64,
                            const float *w32, sfg_dtype vt, const uint8_t *hmask, const uint8_t *base,
-                           const sfg_params *p, NodeOrder *no, DevArena &A, hipStream_t s) {
+                           const sfg_params *p, int64_t known_nnz, const std::function<void()> &meanwhile,
+                           NodeOrder *no, DevArena &A, hipStream_t s) {
     const void *wv = vt == SFG_F64 ? (const void *)w64 : (const void *)w32;
     int32_t *rowptr = A.alloc<int32_t>(n + 1);
     int32_t *col = A.alloc<int32_t>(2 * m + 1);
@@ -457,12 +501,16 @@ ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t
         mr = A.alloc<int32_t>(1);
         max_row_length(&G.H, mr, s);
     }
-    int32_t nnz = 0;
+    int64_t nnz = known_nnz;
     unsigned long long far_h = 0;
-    SFG_HIP(hipMemcpyAsync(&nnz, rowptr + n, 4, hipMemcpyDeviceToHost, s));
-    if (far) SFG_HIP(hipMemcpyAsync(&far_h, far, 8, hipMemcpyDeviceToHost, s));
-    if (mr) SFG_HIP(hipMemcpyAsync(&G.max_row, mr, 4, hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
+    HostRead rd(s);
+    const int at_nnz = known_nnz < 0 ? rd.add(rowptr + n) : -1, at_far = far ? rd.add(far) : -1,
+              at_mr = mr ? rd.add(mr) : -1;
+    if (meanwhile) meanwhile();
+    rd.wait();
+    if (at_nnz >= 0) nnz = rd.get<int32_t>(at_nnz);
+    if (far) far_h = rd.get<unsigned long long>(at_far);
+    if (mr) G.max_row = rd.get<int32_t>(at_mr);
     G.H.nnz = nnz;
     if (no && !no->decided) {
         no->decided = true;
@@ -479,25 +527,52 @@ ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t
 // the top k_take of them (k_take < 0: ceil(frac * n_cand)).  Writes keep
 // (1 = base, 2 = added); keep may be base itself.  `no` (may be nullptr):
 // the node numbering of the sweeps, decided here when not decided yet.
+// base_edges: the edges in `base`, or -1.  The host waits for the scoring
+// graph's sizes where they are not known (and for an FP64 graph's longest
+// row) and, at the end, for the threshold; stage times come from events.
 void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const float *w32,
                  const uint8_t *base, const sfg_params *p, const double *x0, uint8_t *keep, sfg_level_report *rep,
-                 DevArena &A, hipStream_t s, int64_t k_take, NodeOrder *no) {
+                 DevArena &A, hipStream_t s, int64_t k_take, NodeOrder *no, int64_t base_edges) {
     // the level's buffers go back to the arena at the end, unless the node
     // numbering, which later levels or batches use, is made among them
     const bool scoped = !no || no->decided;
     const DevArena::Mark mark = A.mark();
     const uint8_t *hmask = (p->embed == SFG_EMBED_GRAPH) ? nullptr : base;
-    Timer tm(s);
-    tm.start();
+    StageClock clock(s);
+    if (rep) clock.mark();
+    // candidates: edges outside the current sparsifier, ascending id, listed
+    // while the host waits for the scoring graph's sizes; the graph's entries
+    // count the base's edges where it is the sparsifier
+    int32_t *cand = A.alloc<int32_t>(m + 1);
+    const int32_t *nc_dev = nullptr;
+    const auto list_candidates = [&] {
+        if (m > 0) nc_dev = compact_ids_async(base, 0, m, cand, A, s);
+    };
+    const int64_t known_nnz = !hmask ? 2 * m : (base_edges >= 0 ? 2 * base_edges : -1);
     // The precision form (reduced-precision storage with an FP64 band) needs the
     // FP64 scoring graph, for the band re-scoring or for the FP64 path the
     // prediction below may send the level to: it is built first, and the
     // reduced-precision values only when that path runs.
     const bool band_form = p->storage != SFG_F64 && p->band > 0.0;
     ScoringGraph G64, G;
-    if (band_form) G64 = scoring_graph(n, m, u, v, w64, w32, SFG_F64, hmask, base, p, no, A, s);
-    else G = scoring_graph(n, m, u, v, w64, w32, p->storage == SFG_F64 ? SFG_F64 : SFG_F32, hmask, base, p, no,
-                           A, s);
+    if (band_form)
+        G64 = scoring_graph(n, m, u, v, w64, w32, SFG_F64, hmask, base, p, known_nnz, list_candidates, no, A, s);
+    else
+        G = scoring_graph(n, m, u, v, w64, w32, p->storage == SFG_F64 ? SFG_F64 : SFG_F32, hmask, base, p, known_nnz,
+                          list_candidates, no, A, s);
+    int64_t nc = 0;
+    if (m > 0) {
+        if (hmask) {
+            nc = m - (band_form ? G64.H.nnz : G.H.nnz) / 2;
+        } else if (base_edges >= 0) {
+            nc = m - base_edges;
+        } else {
+            HostRead rd(s);
+            rd.add(nc_dev);
+            rd.wait();
+            nc = rd.get<int32_t>(0);
+        }
+    }
     // su, sv, sx0: endpoints and start block in the numbering the sweeps use
     const int32_t *su = u, *sv = v;
     const double *sx0 = x0;
@@ -518,17 +593,10 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
     const char *pe = getenv("SFG_PRECISION_PREDICT");
     const bool predict = band_form && !(pe && atoi(pe) == 0) && p->smoother == SFG_SMOOTH_JACOBI;
     bool fallback = false;
-    // candidates: edges outside the current sparsifier, ascending id
-    int32_t *cand = nullptr;
-    int64_t nc = -1;
     if (predict) {
-        cand = A.alloc<int32_t>(m + 1);
-        nc = compact_ids(base, 0, m, cand, A, s);
-        const int32_t *cand0 = cand;
-        const int64_t nc0 = nc;
-        const int64_t ks0 = k_take >= 0 ? k_take : (int64_t)std::ceil(p->frac * (double)nc0);
-        fallback = ks0 > 0 && ks0 < nc0 &&
-                   4.0 * predicted_cone_share(&G64.H, p->sweeps, nc0, cand0, su, sv, p->band, 0.25, A, s) > 1.0;
+        const int64_t ks0 = k_take >= 0 ? k_take : (int64_t)std::ceil(p->frac * (double)nc);
+        fallback = ks0 > 0 && ks0 < nc &&
+                   4.0 * predicted_cone_share(&G64.H, p->sweeps, nc, cand, su, sv, p->band, 0.25, A, s) > 1.0;
     }
     sfg_params p64;
     const sfg_params *q = p;
@@ -540,7 +608,7 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         q = &p64;
         G = G64;
     } else if (band_form) {
-        G = scoring_graph(n, m, u, v, w64, w32, SFG_F32, hmask, base, p, no, A, s);
+        G = scoring_graph(n, m, u, v, w64, w32, SFG_F32, hmask, base, p, G64.H.nnz, nullptr, no, A, s);
     }
     const bool f64 = q->storage == SFG_F64;
     const sfg_dtype vt = f64 ? SFG_F64 : SFG_F32;
@@ -554,8 +622,7 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
     const bool passes = no && no->use && q->smoother == SFG_SMOOTH_JACOBI;
     size_t wss = passes ? smooth_ordered_workspace_bytes(n, q->k, q->storage) : smooth_workspace_bytes(n, q->k, q->storage);
     void *wsm = A.raw(wss);
-    float ms_other = tm.stop();
-    tm.start();
+    if (rep) clock.mark();
     if (q->smoother == SFG_SMOOTH_GAUSS_SEIDEL) {
         int32_t *color = A.alloc<int32_t>(n + 1);
         int32_t *class_rows = A.alloc<int32_t>(n + 1);
@@ -570,17 +637,11 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
     } else {
         smooth(&H, q->k, q->sweeps, q->omega, sx0, q->storage, q->final_f32, x, wsm, wss, s, G.max_row);
     }
-    float ms_smooth = tm.stop();
-    tm.start();
-    if (!cand) {
-        cand = A.alloc<int32_t>(m + 1);
-        nc = compact_ids(base, 0, m, cand, A, s);
-    }
+    if (rep) clock.mark();
     const sfg_dtype st = f64 ? SFG_F64 : SFG_F32;
     void *score = A.raw((nc + 1) * dtype_size(st));
     edge_scores(x, xt, n, q->k, nc, cand, su, sv, wv, vt, score, st, s);
-    float ms_score = tm.stop();
-    tm.start();
+    if (rep) clock.mark();
     const int64_t ksel = k_take >= 0 ? k_take : (int64_t)std::ceil(q->frac * (double)nc);
     SFG_REQUIRE(ksel <= nc, SFG_EINVAL, "sparsify: more edges requested than candidates");
     uint8_t *sel = A.alloc<uint8_t>(nc + 1);
@@ -588,16 +649,22 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
     size_t wsel = select_workspace_bytes(nc);
     void *wse = A.raw(wsel);
     select_topk(score, st, nc, ksel, sel, tau, wse, wsel, s);
+    HostRead rd(s);
+    rd.add(tau);
     double tau_h = 0;
-    SFG_HIP(hipMemcpyAsync(&tau_h, tau, 8, hipMemcpyDeviceToHost, s));
-    SFG_HIP(hipStreamSynchronize(s));
-    if (tau_h != tau_h) fail(SFG_ENUMERIC, "sparsify: NaN or negative edge score");
+    const auto threshold = [&] {
+        rd.wait();
+        tau_h = rd.get<double>(0);
+        if (tau_h != tau_h) fail(SFG_ENUMERIC, "sparsify: NaN or negative edge score");
+    };
+    const bool bands = !f64 && q->band > 0.0 && ksel > 0 && ksel < nc;
+    if (bands) threshold();
     if (rep) {
         rep->n = n;
         rep->m = m;
         rep->n_cand = nc;
         rep->k_sel = ksel;
-        rep->tau = tau_h;
+        rep->tau = tau_h;      // the band re-scoring replaces it; without one it is read at the end
         rep->band = 0;
         rep->band_above = 0;
         rep->band_rounds = 0;
@@ -607,7 +674,7 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         rep->n_scored = nc;
         if (!passes) rep->sweeps_per_pass = 1;
     }
-    if (!f64 && q->band > 0.0 && ksel > 0 && ksel < nc) {
+    if (bands) {
         // precision form: FP64 re-scoring of the edges near the threshold
         band_rescore(&G64.H, q->k, q->sweeps, q->omega, sx0, nc, cand, su, sv, w64, (const float *)score, ksel,
                      tau_h, q->band, sel, rep, A, s);
@@ -618,13 +685,16 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         hipLaunchKernelGGL(k_keep_add, dim3(grid_for(nc, 256)), dim3(256), 0, s, nc, cand, sel, keep);
         SFG_LAUNCH_CHECK();
     }
-    float ms_select = tm.stop();
+    if (rep) clock.mark();
+    if (!bands) threshold();
     if (scoped) A.release(mark);
     if (rep) {
-        rep->ms_smooth = ms_smooth;
-        rep->ms_score = ms_score;
-        rep->ms_select = ms_select;
-        rep->ms_other = ms_other;
+        if (!bands) rep->tau = tau_h;
+        clock.wait();
+        rep->ms_other = clock.ms(0);
+        rep->ms_smooth = clock.ms(1);
+        rep->ms_score = clock.ms(2);
+        rep->ms_select = clock.ms(3);
     }
 }
 
@@ -664,7 +734,8 @@ void single_level_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t
     if (rounds == 1) {
         NodeOrder no;
         no.launches = planned_launches(p, 1);
-        score_level(n, m, u, v, w64, w32, tree, p, x0, keep, rep ? &rep->level[0] : nullptr, A, s, -1, &no);
+        score_level(n, m, u, v, w64, w32, tree, p, x0, keep, rep ? &rep->level[0] : nullptr, A, s, -1, &no,
+                    n - 1);
         return;
     }
     // multi-round densification: the budget of the single pass in near-equal
@@ -677,7 +748,7 @@ void single_level_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t
     for (int32_t r = 0; r < rounds; ++r) {
         const int64_t q = k_total * (r + 1) / rounds - k_total * r / rounds;
         score_level(n, m, u, v, w64, w32, keep, p, x0 + (size_t)r * n * p->k, keep,
-                    rep ? &rep->level[r] : nullptr, A, s, q, &no);
+                    rep ? &rep->level[r] : nullptr, A, s, q, &no, -1);
     }
 }
 
@@ -874,7 +945,7 @@ void sigma_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *v, co
         const int64_t take = std::min(q, n_off - added);
         if (take <= 0) break;
         score_level(n, m, u, v, w64, w32, keep, p, x0 + (size_t)r * n * p->k, keep,
-                    rep ? &rep->level[r] : nullptr, A, s, take, &no);
+                    rep ? &rep->level[r] : nullptr, A, s, take, &no, -1);
         added += take;
         ++r;
         kap = estimate();
@@ -961,7 +1032,8 @@ extern "C" sfg_status sfg_sparsify(int64_t n, int64_t m, const int32_t *u, const
         SFG_REQUIRE(keep, SFG_EINVAL, "sparsify: null pointer");
         if (p->sigma > 0.0) sfg::check_kappa_params(sfg::kappa_defaults(&p->est), n);
         sfg::DevArena A(s);
-        sfg::validate_edges(n, m, u, v, w, wt, A, s);
+        sfg::HostRead verdict(s);
+        sfg::validate_edges(n, m, u, v, w, wt, verdict, A, s);
         if (!x0) {   // draw the blocks on the device: one per level or per round
             const int32_t nb = p->levels > 1   ? p->levels
                                : p->sigma > 0.0 ? (p->rounds > 0 ? p->rounds : 16)
@@ -971,6 +1043,7 @@ extern "C" sfg_status sfg_sparsify(int64_t n, int64_t m, const int32_t *u, const
                 sfg::random_block(n, p->k, p->seed, (uint32_t)b, gen + (size_t)b * n * p->k, s);
             x0 = gen;
         }
+        sfg::check_edges(m, verdict);
         if (rep) std::memset(rep, 0, sizeof(*rep));
         if (p->levels == 1)
             sfg::single_level_sparsify(n, m, u, v, w, wt, p, x0, keep, rep, A, s);

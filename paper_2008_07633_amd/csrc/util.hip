@@ -1,4 +1,7 @@
-// Shared device routines: exclusive scan of int32 counts, fills, last-error.
+// Shared device routines: exclusive scan of int32 counts, fills, scalar
+// read-back, last-error.
+#include <mutex>
+
 #include "common.hpp"
 
 namespace sfg {
@@ -141,6 +144,66 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, int32_t *scr
     SFG_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_tile_rescan, dim3((uint32_t)nt), dim3(kScanThreads), 0, s, in, out, n, scratch, grand);
     SFG_LAUNCH_CHECK();
+}
+
+// ------------------------------------------------------------------ scalar read-back
+
+namespace {
+
+constexpr int kReadSlots = 16;
+constexpr size_t kPoolMax = 64;
+std::mutex g_read_mu;
+std::vector<HostRead::Item> g_read_pool[kMaxDevices];
+
+}  // namespace
+
+HostRead::HostRead(hipStream_t s) : s_(s) {
+    SFG_HIP(hipGetDevice(&dev_));
+    SFG_REQUIRE(dev_ >= 0 && dev_ < kMaxDevices, SFG_EUNSUPPORTED, "device index over 63");
+    {
+        std::lock_guard<std::mutex> lk(g_read_mu);
+        if (!g_read_pool[dev_].empty()) {
+            it_ = g_read_pool[dev_].back();
+            g_read_pool[dev_].pop_back();
+        }
+    }
+    if (it_.host) return;
+    SFG_HIP(hipHostMalloc(&it_.host, 8 * kReadSlots, hipHostMallocDefault));
+    const hipError_t e = hipEventCreateWithFlags(&it_.ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        (void)hipHostFree(it_.host);
+        SFG_HIP(e);
+    }
+}
+
+int HostRead::add_bytes(const void *device, size_t bytes) {
+    SFG_REQUIRE(used_ < kReadSlots, SFG_EHIP, "internal error: too many scalars read back");
+    const int slot = used_++;
+    pending_ = true;
+    SFG_HIP(hipMemcpyAsync(static_cast<char *>(it_.host) + 8 * slot, device, bytes, hipMemcpyDeviceToHost, s_));
+    SFG_HIP(hipEventRecord(it_.ev, s_));
+    return slot;
+}
+
+void HostRead::wait() {
+    if (!pending_) return;
+    SFG_HIP(hipEventSynchronize(it_.ev));
+    pending_ = false;
+}
+
+HostRead::~HostRead() {
+    // left without wait() (an error in between): the copies land before the
+    // buffer goes to the next user
+    if (pending_) (void)hipStreamSynchronize(s_);
+    {
+        std::lock_guard<std::mutex> lk(g_read_mu);
+        if (g_read_pool[dev_].size() < kPoolMax) {
+            g_read_pool[dev_].push_back(it_);
+            return;
+        }
+    }
+    (void)hipEventDestroy(it_.ev);
+    (void)hipHostFree(it_.host);
 }
 
 // ------------------------------------------------------------------ fills
