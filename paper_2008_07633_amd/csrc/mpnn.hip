@@ -18,11 +18,16 @@
 // or z rows as BF16 MFMA operands (K padded to a multiple of 8), multiplies
 // by the BF16 weights with v_mfma_f32_32x32x8_bf16 into FP32 accumulators,
 // and applies the ReLU (and the head's last dot product) in FP32.  Training
-// runs in FP32 on the vector units: weights in LDS, one node or edge per
-// thread, 32-wide accumulators; backward sends per-edge gradients to nodes
-// through an incidence CSR in ascending edge order and reduces weight
-// gradients by fixed-shape block partials: no FP atomics, so training is
-// deterministic.
+// (and FP32 inference) runs on the matrix cores too, in FP32
+// (v_mfma_f32_32x32x2_f32).  One kernel takes the edge head forward and
+// backward, 32 edges per wavefront: predictions, loss, the gradients sent to
+// both ends' nodes and the head's weight gradients, which stay in accumulators
+// over all of a wavefront's tiles.  Per-edge gradients reach the nodes through
+// an incidence CSR in ascending edge order; weight gradients are added over
+// fixed partitions in a fixed order: no FP atomics, so training is
+// deterministic.  One loss and gradient on a 40^3 mesh (64,000 nodes, 123,201
+// edges) took 1.21 ms on the vector units, with every layer's inputs written
+// out for its weight gradient, and takes 0.19.
 #include <cmath>
 #include <vector>
 
@@ -54,15 +59,6 @@ constexpr int kOffW4 = kOffW3 + kZ1 * kH;
 constexpr int kParams = kOffW4 + kH + 1;
 static_assert(kParams == 4865, "parameter count");
 constexpr float kTiny = 1e-30f;
-
-template <typename T>
-__device__ __forceinline__ float ld(const T *p) {
-    return cvt<float>(*p);
-}
-template <>
-__device__ __forceinline__ float ld<float>(const float *p) {
-    return *p;
-}
 
 // ------------------------------------------------------------------ features
 
@@ -187,88 +183,6 @@ __global__ void k_edge_feat(int64_t ne, const int32_t *__restrict__ cand, const 
         if (norm) x = (x - norm[2 * kF + j]) * norm[2 * kF + kE + j];
         ef[i * kE + j] = x;
     }
-}
-
-// ------------------------------------------------------------------ forward
-
-template <typename TIN, typename TOUT, int FIN>
-__global__ __launch_bounds__(256) void k_dense_fwd(int64_t n, const TIN *__restrict__ x, const TIN *__restrict__ a,
-                                                   const float *__restrict__ W, TOUT *__restrict__ h,
-                                                   float *__restrict__ pre, float *__restrict__ uin) {
-    __shared__ float sw[(2 * FIN + 1) * kH];
-    for (int i = threadIdx.x; i < (2 * FIN + 1) * kH; i += blockDim.x) sw[i] = W[i];
-    __syncthreads();
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    float acc[kH];
-#pragma unroll
-    for (int j = 0; j < kH; ++j) acc[j] = sw[2 * FIN * kH + j];
-    for (int i = 0; i < FIN; ++i) {
-        const float xi = ld(x + p * FIN + i);
-        if (uin) uin[p * (2 * FIN + 1) + i] = xi;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) acc[j] = __builtin_fmaf(xi, sw[i * kH + j], acc[j]);
-    }
-    for (int i = 0; i < FIN; ++i) {
-        const float ai = ld(a + p * FIN + i);
-        if (uin) uin[p * (2 * FIN + 1) + FIN + i] = ai;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) acc[j] = __builtin_fmaf(ai, sw[(FIN + i) * kH + j], acc[j]);
-    }
-    if (uin) uin[p * (2 * FIN + 1) + 2 * FIN] = 1.f;
-#pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        if (pre) pre[p * kH + j] = acc[j];
-        h[p * kH + j] = cvt<TOUT>(fmaxf(acc[j], 0.f));
-    }
-}
-
-template <typename TH>
-__global__ __launch_bounds__(256) void k_head_fwd(int64_t ne, const int32_t *__restrict__ cand,
-                                                  const int32_t *__restrict__ u, const int32_t *__restrict__ v,
-                                                  const TH *__restrict__ h, const float *__restrict__ ef,
-                                                  const float *__restrict__ W3, const float *__restrict__ w4,
-                                                  float *__restrict__ pred, float *__restrict__ gsave,
-                                                  float *__restrict__ zsave) {
-    __shared__ float s3[kZ1 * kH];
-    __shared__ float s4[kH + 1];
-    for (int i = threadIdx.x; i < kZ1 * kH; i += blockDim.x) s3[i] = W3[i];
-    for (int i = threadIdx.x; i < kH + 1; i += blockDim.x) s4[i] = w4[i];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ne) return;
-    const int32_t e = cand ? cand[i] : (int32_t)i;
-    const TH *hp = h + (int64_t)u[e] * kH;
-    const TH *hq = h + (int64_t)v[e] * kH;
-    float g[kH];
-#pragma unroll
-    for (int j = 0; j < kH; ++j) g[j] = s3[kZ * kH + j];
-    for (int c = 0; c < kH; ++c) {
-        const float a = ld(hp + c), b = ld(hq + c);
-        const float z0 = fabsf(a - b), z1 = a * b;
-        if (zsave) {
-            zsave[i * kZ1 + c] = z0;
-            zsave[i * kZ1 + kH + c] = z1;
-        }
-#pragma unroll
-        for (int j = 0; j < kH; ++j) g[j] = __builtin_fmaf(z0, s3[c * kH + j], g[j]);
-#pragma unroll
-        for (int j = 0; j < kH; ++j) g[j] = __builtin_fmaf(z1, s3[(kH + c) * kH + j], g[j]);
-    }
-    for (int c = 0; c < kE; ++c) {
-        const float z = ef[i * kE + c];
-        if (zsave) zsave[i * kZ1 + 2 * kH + c] = z;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) g[j] = __builtin_fmaf(z, s3[(2 * kH + c) * kH + j], g[j]);
-    }
-    if (zsave) zsave[i * kZ1 + kZ] = 1.f;
-    float out = s4[kH];
-#pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        if (gsave) gsave[i * kH + j] = g[j];
-        out = __builtin_fmaf(fmaxf(g[j], 0.f), s4[j], out);
-    }
-    pred[i] = out;
 }
 
 // ------------------------------------------------------------------ inference on the matrix cores
@@ -407,180 +321,413 @@ __global__ __launch_bounds__(256) void k_head_mfma(int64_t ne, const int32_t *__
     }
 }
 
-// ------------------------------------------------------------------ backward
+// ------------------------------------------------------------------ FP32 on the matrix cores
+//
+// v_mfma_f32_32x32x2_f32 (one 32 x 32 x 2 block per wavefront), lane l, half
+// h = l / 32:
+//   A (32 x 2):  row l % 32, column h
+//   B (2 x 32):  column l % 32, row h
+//   D (32 x 32): as above: column l % 32, rows tile_row(r, h), r = 0..15
+// The order of the k index is free, so a step may take any two of the k
+// values, one per half, as long as A and B agree: rows of a 32-wide operand
+// are loaded as 16-byte pieces (half h of piece t holds k = 8t + 4h + 0..3),
+// and a sum over the rows of a D tile takes its registers as they are.
+// (Bound by the matrix cores' 64 cycles a step: 116 steps per 32 edges in the
+// head, about 12 us for 123,201 edges on 1024 SIMDs.)
 
-// Per edge: output error, head hidden error, and the edge's contribution to
-// the gradients of H2 at both ends.
-__global__ __launch_bounds__(256) void k_head_bwd(int64_t ne, const int32_t *__restrict__ cand,
-                                                  const int32_t *__restrict__ u, const int32_t *__restrict__ v,
-                                                  const float *__restrict__ h, const float *__restrict__ pred,
-                                                  const float *__restrict__ target, const float *__restrict__ gsave,
-                                                  const float *__restrict__ W3, const float *__restrict__ w4,
-                                                  float scale, float *__restrict__ dg, float *__restrict__ ah1,
-                                                  float *__restrict__ dy, float *__restrict__ dhp,
-                                                  float *__restrict__ dhq) {
-    __shared__ float s3[kZ1 * kH];
-    __shared__ float s4[kH + 1];
-    for (int i = threadIdx.x; i < kZ1 * kH; i += blockDim.x) s3[i] = W3[i];
-    for (int i = threadIdx.x; i < kH + 1; i += blockDim.x) s4[i] = w4[i];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ne) return;
-    const float d = (pred[i] - target[i]) * scale;
-    dy[i] = d;
-    float dgl[kH];
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows need not be 16-byte aligned
+
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ int tile_row(int r, int half) { return 8 * (r / 4) + 4 * half + (r % 4); }
+
+// h = relu([x | a | 1] W), 32 nodes per wavefront.
+template <int FIN>
+__global__ __launch_bounds__(256) void k_dense_f32(int64_t n, const float *__restrict__ x, const float *__restrict__ a,
+                                                   const float *__restrict__ W, float *__restrict__ h) {
+    constexpr int NX = FIN / 8;
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    float wx[NX][4], wa[NX][4];
 #pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        const float gj = gsave[i * kH + j];
-        ah1[i * (kH + 1) + j] = fmaxf(gj, 0.f);
-        dgl[j] = gj > 0.f ? d * s4[j] : 0.f;
-        dg[i * kH + j] = dgl[j];
-    }
-    ah1[i * (kH + 1) + kH] = 1.f;
-    const int32_t e = cand ? cand[i] : (int32_t)i;
-    const float *hp = h + (int64_t)u[e] * kH;
-    const float *hq = h + (int64_t)v[e] * kH;
-    for (int c = 0; c < kH; ++c) {
-        float dz0 = 0.f, dz1 = 0.f;
+    for (int t = 0; t < NX; ++t)
 #pragma unroll
-        for (int j = 0; j < kH; ++j) {
-            dz0 = __builtin_fmaf(dgl[j], s3[c * kH + j], dz0);
-            dz1 = __builtin_fmaf(dgl[j], s3[(kH + c) * kH + j], dz1);
+        for (int q = 0; q < 4; ++q) {
+            wx[t][q] = W[(8 * t + 4 * half + q) * kH + col];
+            wa[t][q] = W[(FIN + 8 * t + 4 * half + q) * kH + col];
         }
-        const float a = hp[c], b = hq[c];
-        const float sg = a > b ? 1.f : (a < b ? -1.f : 0.f);
-        dhp[i * kH + c] = dz0 * sg + dz1 * b;
-        dhq[i * kH + c] = -dz0 * sg + dz1 * a;
+    const float bias = W[2 * FIN * kH + col];
+    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
+    if (base >= n) return;
+    const int64_t row = base + col < n ? base + col : n - 1;      // past the end: computed, not stored
+    f32x4u vx[NX], va[NX];
+#pragma unroll
+    for (int t = 0; t < NX; ++t) {
+        vx[t] = *reinterpret_cast<const f32x4u *>(x + row * FIN + 8 * t + 4 * half);
+        va[t] = *reinterpret_cast<const f32x4u *>(a + row * FIN + 8 * t + 4 * half);
+    }
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = bias;
+#pragma unroll
+    for (int t = 0; t < NX; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = mfma32(vx[t][q], wx[t][q], acc);
+#pragma unroll
+    for (int t = 0; t < NX; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = mfma32(va[t][q], wa[t][q], acc);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t node = base + tile_row(r, half);
+        if (node < n) h[node * kH + col] = fmaxf(acc[r], 0.f);
+    }
+}
+
+// Sum of the workgroup's four wavefronts' tiles (NT accumulator tiles each,
+// rows of the gradient in order) into partial[block][row * 32 + column], the
+// wavefronts added in order.
+template <int NT>
+__device__ __forceinline__ void store_tiles(const f32x16 (&acc)[NT], int rows, float *sh /* 4 x 1056 */,
+                                            float *__restrict__ partial) {
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sh[wv * 1056 + tile_row(r, half) * 33 + col] = acc[t][r];
+        __syncthreads();
+        for (int e = threadIdx.x; e < 1024; e += 256) {
+            const int i = e >> 5, j = e & 31;
+            if (32 * t + i < rows) {
+                const float *q = sh + i * 33 + j;
+                partial[(32 * t + i) * kH + j] = ((q[0] + q[1056]) + q[2112]) + q[3168];
+            }
+        }
+    }
+}
+
+// One number per lane, summed over the workgroup (lanes 0..31 of a wavefront
+// hold 32 columns; both halves are added): partial[0..31].
+__device__ __forceinline__ void store_cols(float v, float *sh /* 4 x 32 */, float *__restrict__ partial) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    v += __shfl_xor(v, 32, 64);
+    __syncthreads();
+    if (lane < 32) sh[wv * 32 + lane] = v;
+    __syncthreads();
+    if (threadIdx.x < 32)
+        partial[threadIdx.x] = ((sh[threadIdx.x] + sh[32 + threadIdx.x]) + sh[64 + threadIdx.x]) + sh[96 + threadIdx.x];
+}
+
+constexpr int kTrainBlocks = 256;     // workgroups of the kernels that leave weight-gradient partials
+constexpr int kNent3 = kZ1 * kH;      // W3 entries of a head partial, then w4's 33, then the loss
+constexpr int kHeadPart = kNent3 + kH + 1 + 1;
+
+// Edge head, 32 edges per wavefront: yhat_e = relu(z_e W3) . w4[0:32] + w4[32].
+// TRAIN: a wavefront takes every 4 gridDim-th tile; besides the predictions it
+// forms the output errors d_e = scale (yhat_e - y_e), the squared errors, the
+// gradients at both ends' H2 rows (dhp, dhq per edge) and the head's weight
+// gradients, its share of which goes to part[block][kHeadPart].
+template <bool TRAIN>
+__global__ __launch_bounds__(256) void k_head_f32(int64_t ne, const int32_t *__restrict__ cand,
+                                                  const int32_t *__restrict__ u, const int32_t *__restrict__ v,
+                                                  const float *__restrict__ h, const float *__restrict__ ef,
+                                                  const float *__restrict__ W3, const float *__restrict__ w4,
+                                                  float *__restrict__ pred, const float *__restrict__ target,
+                                                  float scale, float *__restrict__ dhp, float *__restrict__ dhq,
+                                                  float *__restrict__ part) {
+    static_assert(kH == 32 && kE == 4, "head layout");
+    __shared__ float s_d[4][32 * 33];                       // a wavefront's 32 x 32 tile, transposed through here
+    __shared__ float s_p[TRAIN ? 4 : 1][TRAIN ? 32 * 33 : 1], s_q[TRAIN ? 4 : 1][TRAIN ? 32 * 33 : 1];
+    __shared__ float s_e[TRAIN ? 4 : 1][TRAIN ? 32 * 8 : 1], s_err[TRAIN ? 4 : 1][TRAIN ? 32 : 1];
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, wv = threadIdx.x >> 6;
+    float w0[4][4], w1[4][4], we[4], wt0[TRAIN ? 4 : 1][4], wt1[TRAIN ? 4 : 1][4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 8 * t + 4 * half + q;
+            w0[t][q] = W3[k * kH + col];
+            w1[t][q] = W3[(kH + k) * kH + col];
+            if constexpr (TRAIN) {
+                wt0[t][q] = W3[col * kH + k];
+                wt1[t][q] = W3[(kH + col) * kH + k];
+            }
+        }
+    // the last four k of a half: the edge features, or the bias
+#pragma unroll
+    for (int q = 0; q < 4; ++q) we[q] = half == 0 ? W3[(2 * kH + q) * kH + col] : (q == 0 ? W3[kZ * kH + col] : 0.f);
+    const float w4c = w4[col], w4b = w4[kH];
+    f32x16 gw[TRAIN ? 3 : 1] = {};
+    float g4 = 0.f, g4b = 0.f, loss = 0.f;
+    const int64_t tiles = (ne + 31) / 32;
+    for (int64_t tile = (int64_t)blockIdx.x * 4 + wv; tile < tiles; tile += (int64_t)gridDim.x * 4) {
+        const int64_t base = tile * 32;
+        const bool valid = base + col < ne;
+        const int64_t i = valid ? base + col : ne - 1;
+        const int32_t e = cand ? cand[i] : (int32_t)i;
+        const float *hp = h + (int64_t)u[e] * kH + 4 * half, *hq = h + (int64_t)v[e] * kH + 4 * half;
+        f32x4u a[4], b[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            a[t] = *reinterpret_cast<const f32x4u *>(hp + 8 * t);
+            b[t] = *reinterpret_cast<const f32x4u *>(hq + 8 * t);
+        }
+        const f32x4u f = *reinterpret_cast<const f32x4u *>(ef + i * kE);
+        float y = 0.f;
+        if constexpr (TRAIN) y = target[i];
+        f32x16 acc = {};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                acc = mfma32(fabsf(a[t][q] - b[t][q]), w0[t][q], acc);
+                acc = mfma32(a[t][q] * b[t][q], w1[t][q], acc);
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc = mfma32(half == 0 ? f[q] : (q == 0 ? 1.f : 0.f), we[q], acc);
+        // the last layer: each lane scales its column, then two lanes add a row
+        float *sd = s_d[wv];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sd[tile_row(r, half) * 33 + col] = fmaxf(acc[r], 0.f) * w4c;
+        __builtin_amdgcn_wave_barrier();
+        float o = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o += sd[col * 33 + 16 * half + j];
+        o += __shfl_xor(o, 32, 64);
+        o += w4b;
+        if (half == 0 && valid) pred[i] = o;
+        if constexpr (TRAIN) {
+            float *sp = s_p[wv], *sq = s_q[wv], *se = s_e[wv], *sx = s_err[wv];
+            const float err = valid ? o - y : 0.f;
+            const float d = err * scale;
+            if (half == 0) {
+                loss = __builtin_fmaf(err, err, loss);
+                g4b += d;
+                sx[col] = d;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) se[col * 8 + q] = f[q];
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    sp[col * 33 + 8 * t + 4 * half + q] = a[t][q];
+                    sq[col * 33 + 8 * t + 4 * half + q] = b[t][q];
+                }
+            __builtin_amdgcn_wave_barrier();
+            // dG in the D layout (d is 0 on edges past the end), the w4 gradient, and W3's: z^T dG
+            float dg[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = tile_row(r, half);
+                const float dr = sx[row];
+                g4 = __builtin_fmaf(fmaxf(acc[r], 0.f), dr, g4);
+                dg[r] = acc[r] > 0.f ? dr * w4c : 0.f;
+                const float pa = sp[row * 33 + col], pb = sq[row * 33 + col];
+                const float ze = col < kE ? se[row * 8 + (col & 3)] : (col == kE ? 1.f : 0.f);
+                gw[0] = mfma32(fabsf(pa - pb), dg[r], gw[0]);
+                gw[1] = mfma32(pa * pb, dg[r], gw[1]);
+                gw[2] = mfma32(ze, dg[r], gw[2]);
+            }
+            // dz = dG W3^T needs dG with a row per lane
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sd[tile_row(r, half) * 33 + col] = dg[r];
+            __builtin_amdgcn_wave_barrier();
+            f32x16 dz0 = {}, dz1 = {};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float x = sd[col * 33 + 8 * t + 4 * half + q];
+                    dz0 = mfma32(x, wt0[t][q], dz0);
+                    dz1 = mfma32(x, wt1[t][q], dz1);
+                }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = tile_row(r, half);
+                const float pa = sp[row * 33 + col], pb = sq[row * 33 + col];
+                const float sg = pa > pb ? 1.f : (pa < pb ? -1.f : 0.f);
+                if (base + row < ne) {
+                    dhp[(base + row) * kH + col] = dz0[r] * sg + dz1[r] * pb;
+                    dhq[(base + row) * kH + col] = -dz0[r] * sg + dz1[r] * pa;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();      // the next tile writes over this one's LDS
+        }
+    }
+    if constexpr (TRAIN) {
+        float *out = part + (int64_t)blockIdx.x * kHeadPart;
+        store_tiles<3>(gw, kZ1, &s_d[0][0], out);
+        store_cols(g4, &s_err[0][0], out + kNent3);
+        // w4's bias and the loss: sums over the first half's 32 lanes, then the wavefronts
+        for (int st = 16; st > 0; st >>= 1) {
+            g4b += __shfl_xor(g4b, st, 64);
+            loss += __shfl_xor(loss, st, 64);
+        }
+        __syncthreads();
+        if (lane == 0) {
+            s_err[0][wv] = g4b;
+            s_err[0][4 + wv] = loss;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            const float *q = s_err[0] + 4 * threadIdx.x;
+            out[kNent3 + kH + threadIdx.x] = ((q[0] + q[1]) + q[2]) + q[3];
+        }
     }
 }
 
 // dH2 at each node from its incident candidate edges, in ascending edge
-// order, masked by the layer's ReLU.
+// order, masked by the layer's ReLU (h > 0 exactly where its input was).
 __global__ void k_gather_dh(int64_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
                             const int32_t *__restrict__ eid, const float *__restrict__ dhp,
-                            const float *__restrict__ dhq, const float *__restrict__ pre, float *dpre) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                            const float *__restrict__ dhq, const float *__restrict__ h, float *dpre) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;     // eight lanes a node, four columns each
+    const int64_t p = t >> 3;
+    const int c = (int)(t & 7) * 4;
     if (p >= n) return;
-    float acc[kH];
-#pragma unroll
-    for (int j = 0; j < kH; ++j) acc[j] = 0.f;
-    for (int32_t t = rp[p]; t < rp[p + 1]; ++t) {
-        const int32_t i = eid[t];
-        const float *src = (col[t] > p ? dhp : dhq) + (int64_t)i * kH;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) acc[j] += src[j];
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int32_t j = rp[p]; j < rp[p + 1]; ++j) {
+        const int64_t i = eid[j];
+        const float4 g = *reinterpret_cast<const float4 *>((col[j] > p ? dhp : dhq) + i * kH + c);
+        acc[0] += g.x;
+        acc[1] += g.y;
+        acc[2] += g.z;
+        acc[3] += g.w;
     }
-#pragma unroll
-    for (int j = 0; j < kH; ++j) dpre[p * kH + j] = pre[p * kH + j] > 0.f ? acc[j] : 0.f;
+    const float4 hv = *reinterpret_cast<const float4 *>(h + p * kH + c);
+    *reinterpret_cast<float4 *>(dpre + p * kH + c) =
+        make_float4(hv.x > 0.f ? acc[0] : 0.f, hv.y > 0.f ? acc[1] : 0.f, hv.z > 0.f ? acc[2] : 0.f,
+                    hv.w > 0.f ? acc[3] : 0.f);
 }
 
-// Input gradients of a dense layer: t1 = dP Ws^T and t2 = (dP Wn^T) / D.
-template <int FIN>
-__global__ __launch_bounds__(256) void k_dense_bwd(int64_t n, const float *__restrict__ dpre,
-                                                   const float *__restrict__ W, const float *__restrict__ deg,
-                                                   float *t1, float *t2) {
-    __shared__ float sw[2 * FIN * kH];
-    for (int i = threadIdx.x; i < 2 * FIN * kH; i += blockDim.x) sw[i] = W[i];
-    __syncthreads();
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    float dp[kH];
+// Weight gradients of a dense layer, [x | a | 1]^T dP, as partials per
+// workgroup (a wavefront takes every 4 gridDim-th tile of 32 nodes; rows of
+// the tile two at a time are the k steps).  dP is dpre (layer 2, which also
+// forms its input gradients t1 = dP Ws^T and t2 = (dP Wn^T) / D), or, in layer
+// 1, t1 + c2 where the layer's output h is positive.
+template <int FIN, bool INPUTS>
+__global__ __launch_bounds__(256) void k_dense_grad(int64_t n, const float *__restrict__ x,
+                                                    const float *__restrict__ a, const float *__restrict__ dpre,
+                                                    const float *__restrict__ c2, const float *__restrict__ h,
+                                                    const float *__restrict__ W, const float *__restrict__ deg,
+                                                    float *__restrict__ t1, float *__restrict__ t2,
+                                                    float *__restrict__ part) {
+    constexpr int kRows = 2 * FIN + 1, NT = FIN == kH ? 2 : 1;
+    static_assert(FIN == kH || 2 * FIN + 1 <= 32, "tiles of the weight gradient");
+    __shared__ float sh[4 * 1056];
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, wv = threadIdx.x >> 6;
+    float ws[INPUTS ? 4 : 1][4], wn[INPUTS ? 4 : 1][4];
+    if constexpr (INPUTS) {
 #pragma unroll
-    for (int j = 0; j < kH; ++j) dp[j] = dpre[p * kH + j];
-    const float inv = 1.f / deg[p];
-    for (int i = 0; i < FIN; ++i) {
-        float a = 0.f, b = 0.f;
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int j = 0; j < kH; ++j) {
-            a = __builtin_fmaf(dp[j], sw[i * kH + j], a);
-            b = __builtin_fmaf(dp[j], sw[(FIN + i) * kH + j], b);
-        }
-        t1[p * FIN + i] = a;
-        t2[p * FIN + i] = b * inv;
+            for (int q = 0; q < 4; ++q) {
+                ws[t][q] = W[col * kH + 8 * t + 4 * half + q];
+                wn[t][q] = W[(FIN + col) * kH + 8 * t + 4 * half + q];
+            }
     }
-}
-
-__global__ void k_add_mask(int64_t total, const float *__restrict__ a, const float *__restrict__ b,
-                           const float *__restrict__ pre, float *out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < total) out[i] = pre[i] > 0.f ? a[i] + b[i] : 0.f;
-}
-
-// Partial sums of A^T B over row chunks: partial[b][i*db + j] for chunk b.
-constexpr int kAtbBlocks = 128;
-constexpr int kAtbTile = 16;
-
-__global__ __launch_bounds__(256) void k_atb_partial(int64_t nrows, int da, const float *__restrict__ A, int db,
-                                                     const float *__restrict__ B, float *partial) {
-    __shared__ float ta[kAtbTile][kZ1];
-    __shared__ float tb[kAtbTile][kH + 1];
-    const int64_t chunk = (nrows + gridDim.x - 1) / gridDim.x;
-    const int64_t r0 = (int64_t)blockIdx.x * chunk;
-    const int64_t r1 = r0 + chunk < nrows ? r0 + chunk : nrows;
-    const int nent = da * db;
-    float acc[10];
+    f32x16 gw[NT] = {};
+    float gb = 0.f;
+    const int64_t tiles = (n + 31) / 32;
+    for (int64_t tile = (int64_t)blockIdx.x * 4 + wv; tile < tiles; tile += (int64_t)gridDim.x * 4) {
+        const int64_t base = tile * 32;
+        float dp[16], zx[16], za[16];
 #pragma unroll
-    for (int q = 0; q < 10; ++q) acc[q] = 0.f;
-    for (int64_t base = r0; base < r1; base += kAtbTile) {
-        const int rows = (int)(r1 - base < kAtbTile ? r1 - base : kAtbTile);
-        for (int x = threadIdx.x; x < kAtbTile * da; x += blockDim.x) {
-            const int r = x / da, c = x % da;
-            ta[r][c] = r < rows ? A[(base + r) * da + c] : 0.f;
-        }
-        for (int x = threadIdx.x; x < kAtbTile * db; x += blockDim.x) {
-            const int r = x / db, c = x % db;
-            tb[r][c] = r < rows ? B[(base + r) * db + c] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 10; ++q) {
-            const int e = threadIdx.x + q * 256;
-            if (e < nent) {
-                const int i = e / db, j = e % db;
-                float s = acc[q];
-                for (int r = 0; r < kAtbTile; ++r) s = __builtin_fmaf(ta[r][i], tb[r][j], s);
-                acc[q] = s;
+        for (int r = 0; r < 16; ++r) {
+            const int64_t node = base + 2 * r + half;
+            const bool in = node < n;
+            const int64_t at = (in ? node : n - 1) * kH + col;
+            if constexpr (INPUTS)
+                dp[r] = dpre[at];
+            else
+                dp[r] = h[at] > 0.f ? dpre[at] + c2[at] : 0.f;
+            if (!in) dp[r] = 0.f;
+            const int64_t row = (in ? node : n - 1) * FIN;
+            if constexpr (FIN == kH) {
+                zx[r] = x[row + col];
+                za[r] = a[row + col];
+            } else {
+                zx[r] = col < FIN ? x[row + col] : (col < 2 * FIN ? a[row + col - FIN] : (col == 2 * FIN ? 1.f : 0.f));
+                za[r] = 0.f;
             }
         }
-        __syncthreads();
-    }
 #pragma unroll
-    for (int q = 0; q < 10; ++q) {
-        const int e = threadIdx.x + q * 256;
-        if (e < nent) partial[(int64_t)blockIdx.x * nent + e] = acc[q];
+        for (int r = 0; r < 16; ++r) {
+            gw[0] = mfma32(zx[r], dp[r], gw[0]);
+            if constexpr (FIN == kH) {
+                gw[NT - 1] = mfma32(za[r], dp[r], gw[NT - 1]);
+                gb += dp[r];
+            }
+        }
+        if constexpr (INPUTS) {
+            const int64_t node = base + col < n ? base + col : n - 1;
+            f32x4u d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] = *reinterpret_cast<const f32x4u *>(dpre + node * kH + 8 * t + 4 * half);
+            f32x16 o1 = {}, o2 = {};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    o1 = mfma32(d[t][q], ws[t][q], o1);
+                    o2 = mfma32(d[t][q], wn[t][q], o2);
+                }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t p = base + tile_row(r, half);
+                if (p < n) {
+                    t1[p * kH + col] = o1[r];
+                    t2[p * kH + col] = o2[r] * (1.f / deg[p]);
+                }
+            }
+        }
     }
+    float *out = part + (int64_t)blockIdx.x * kRows * kH;
+    store_tiles<NT>(gw, FIN == kH ? 2 * FIN : kRows, sh, out);
+    if constexpr (FIN == kH) store_cols(gb, sh, out + 2 * FIN * kH);
 }
 
-__global__ void k_sum_partials(int nb, int nent, const float *__restrict__ partial, float *out) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nent) return;
-    float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += partial[(int64_t)b * nent + e];
-    out[e] = s;
-}
-
-__global__ void k_sq_err_partial(int64_t ne, const float *__restrict__ pred, const float *__restrict__ target,
-                                 float *partial) {
-    __shared__ float red[256];
-    float s = 0.f;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ne; i += (int64_t)gridDim.x * blockDim.x) {
-        const float d = pred[i] - target[i];
-        s = __builtin_fmaf(d, d, s);
+// The whole gradient and the loss from the partials: 8 lanes an entry, each
+// adding every eighth partial, then pairs, fours and eights.
+__global__ __launch_bounds__(256) void k_grad_finish(int nb1, int nb2, int nb3, const float *__restrict__ p1,
+                                                     const float *__restrict__ p2, const float *__restrict__ p3,
+                                                     float inv_ne, float *__restrict__ grad, float *__restrict__ loss) {
+    // lanes of an entry are 32 apart, so that a load covers 32 consecutive entries
+    __shared__ float sh[8][32];
+    const int e = blockIdx.x * 32 + (threadIdx.x & 31), g = threadIdx.x >> 5;
+    const float *p = nullptr;
+    int nb = 0, stride = 0;
+    if (e < kOffW2) {
+        p = p1 + e;
+        nb = nb1;
+        stride = kU1 * kH;
+    } else if (e < kOffW3) {
+        p = p2 + (e - kOffW2);
+        nb = nb2;
+        stride = kU2 * kH;
+    } else if (e < kParams + 1) {
+        p = p3 + (e - kOffW3);
+        nb = nb3;
+        stride = kHeadPart;
     }
-    red[threadIdx.x] = s;
+    float s0 = 0.f, s1 = 0.f;
+    int b = g;
+    for (; b + 8 < nb; b += 16) {
+        s0 += p[(int64_t)b * stride];
+        s1 += p[(int64_t)(b + 8) * stride];
+    }
+    if (b < nb) s0 += p[(int64_t)b * stride];
+    sh[g][threadIdx.x & 31] = s0 + s1;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
+    if (g == 0 && e < kParams + 1) {
+        const int l = threadIdx.x;
+        const float t = ((sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l])) + ((sh[4][l] + sh[5][l]) + (sh[6][l] + sh[7][l]));
+        if (e < kParams) grad[e] = t;
+        else *loss = t * inv_ne;
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-__global__ void k_loss_final(int nb, const float *__restrict__ partial, float inv_ne, float *loss) {
-    if (threadIdx.x != 0) return;
-    float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += partial[b];
-    *loss = s * inv_ne;
 }
 
 __global__ void k_gather_uv(int64_t ne, const int32_t *__restrict__ cand, const int32_t *__restrict__ u,
@@ -627,38 +774,35 @@ FwdPlan plan_fwd(Carver &c, int64_t n, sfg_dtype act) {
 }
 
 struct TrainPlan {
-    float *a1, *u1, *pre1, *h1, *a2, *u2, *pre2, *h2, *z, *g, *dg, *ah1, *dy, *dhp, *dhq, *dpre2, *t1, *t2, *c2,
-        *dpre1, *ones_n, *ones_e, *part, *lpart, *incval, *incdeg;
+    float *a1, *h1, *a2, *h2, *dhp, *dhq, *dpre2, *t1, *t2, *c2, *ones_n, *ones_e, *part1, *part2, *part3, *incval,
+        *incdeg;
     int32_t *cu, *cv, *irp, *icol, *ieid;
     void *csr_ws;
 };
 
+// Workgroups of a partial-sum kernel over tiles of 32 rows, four tiles each.
+int train_blocks(int64_t rows) {
+    const int64_t b = (rows + 127) / 128;
+    return (int)(b > kTrainBlocks ? kTrainBlocks : b);
+}
+
 TrainPlan plan_train(Carver &c, int64_t n, int64_t ne) {
     TrainPlan p;
     p.a1 = c.take<float>(n * kF);
-    p.u1 = c.take<float>(n * kU1);
-    p.pre1 = c.take<float>(n * kH);
     p.h1 = c.take<float>(n * kH);
     p.a2 = c.take<float>(n * kH);
-    p.u2 = c.take<float>(n * kU2);
-    p.pre2 = c.take<float>(n * kH);
     p.h2 = c.take<float>(n * kH);
-    p.z = c.take<float>((ne + 1) * kZ1);
-    p.g = c.take<float>((ne + 1) * kH);
-    p.dg = c.take<float>((ne + 1) * kH);
-    p.ah1 = c.take<float>((ne + 1) * (kH + 1));
-    p.dy = c.take<float>(ne + 1);
     p.dhp = c.take<float>((ne + 1) * kH);
     p.dhq = c.take<float>((ne + 1) * kH);
     p.dpre2 = c.take<float>(n * kH);
     p.t1 = c.take<float>(n * kH);
     p.t2 = c.take<float>(n * kH);
     p.c2 = c.take<float>(n * kH);
-    p.dpre1 = c.take<float>(n * kH);
     p.ones_n = c.take<float>(n);
     p.ones_e = c.take<float>(ne + 1);
-    p.part = c.take<float>((size_t)kAtbBlocks * kZ1 * kH);
-    p.lpart = c.take<float>(256);
+    p.part1 = c.take<float>((size_t)kTrainBlocks * kU1 * kH);
+    p.part2 = c.take<float>((size_t)kTrainBlocks * kU2 * kH);
+    p.part3 = c.take<float>((size_t)kTrainBlocks * kHeadPart);
     p.incval = c.take<float>(2 * ne + 1);
     p.incdeg = c.take<float>(n);
     p.cu = c.take<int32_t>(ne + 1);
@@ -668,13 +812,6 @@ TrainPlan plan_train(Carver &c, int64_t n, int64_t ne) {
     p.ieid = c.take<int32_t>(2 * ne + 1);
     p.csr_ws = c.take<char>(csr_workspace_bytes(n, ne));
     return p;
-}
-
-void atb(int64_t nrows, int da, const float *A, int db, const float *B, float *out, float *part, hipStream_t s) {
-    hipLaunchKernelGGL(k_atb_partial, dim3(kAtbBlocks), dim3(256), 0, s, nrows, da, A, db, B, part);
-    SFG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_sum_partials, dim3(grid_for(da * db, 256)), dim3(256), 0, s, kAtbBlocks, da * db, part, out);
-    SFG_LAUNCH_CHECK();
 }
 
 void check_graph(const sfg_csr *G) {
@@ -751,13 +888,13 @@ extern "C" sfg_status sfg_mpnn_forward(const sfg_csr *G, const float *params, co
         const int64_t n = G->n;
         Carver c(ws);
         FwdPlan p = plan_fwd(c, n, act);
-        const dim3 gn(grid_for(n, 256)), b(256);
+        const dim3 b(256);
         // layer 1 (FP32 input features; the aggregate reuses p.a)
         float *a1 = (float *)p.a;
         spmm_rownorm(G, kF, SFG_F32, node_feat, a1, s);
         if (act == SFG_F32)
-            hipLaunchKernelGGL((k_dense_fwd<float, float, kF>), gn, b, 0, s, n, node_feat, a1, params + kOffW1,
-                               (float *)p.h1, nullptr, nullptr);
+            hipLaunchKernelGGL(k_dense_f32<kF>, dim3(grid_for(n, 128)), b, 0, s, n, node_feat, a1, params + kOffW1,
+                               (float *)p.h1);
         else
             hipLaunchKernelGGL((k_dense_mfma<float, kF>), dim3(grid_for(n, 128)), b, 0, s, n, node_feat, a1,
                                params + kOffW1, (__hip_bfloat16 *)p.h1);
@@ -765,8 +902,8 @@ extern "C" sfg_status sfg_mpnn_forward(const sfg_csr *G, const float *params, co
         // layer 2
         spmm_rownorm(G, kH, act, p.h1, p.a, s);
         if (act == SFG_F32)
-            hipLaunchKernelGGL((k_dense_fwd<float, float, kH>), gn, b, 0, s, n, (const float *)p.h1,
-                               (const float *)p.a, params + kOffW2, (float *)p.h2, nullptr, nullptr);
+            hipLaunchKernelGGL(k_dense_f32<kH>, dim3(grid_for(n, 128)), b, 0, s, n, (const float *)p.h1,
+                               (const float *)p.a, params + kOffW2, (float *)p.h2);
         else
             hipLaunchKernelGGL((k_dense_mfma<__hip_bfloat16, kH>), dim3(grid_for(n, 128)), b, 0, s, n,
                                (const __hip_bfloat16 *)p.h1, (const __hip_bfloat16 *)p.a, params + kOffW2,
@@ -774,10 +911,10 @@ extern "C" sfg_status sfg_mpnn_forward(const sfg_csr *G, const float *params, co
         SFG_LAUNCH_CHECK();
         if (ne == 0) return;
         SFG_REQUIRE(u && v && edge_feat && pred, SFG_EINVAL, "mpnn_forward: null pointer");
-        const dim3 ge(grid_for(ne, 256));
         if (act == SFG_F32)
-            hipLaunchKernelGGL(k_head_fwd<float>, ge, b, 0, s, ne, cand, u, v, (const float *)p.h2, edge_feat,
-                               params + kOffW3, params + kOffW4, pred, nullptr, nullptr);
+            hipLaunchKernelGGL(k_head_f32<false>, dim3(grid_for(ne, 128)), b, 0, s, ne, cand, u, v,
+                               (const float *)p.h2, edge_feat, params + kOffW3, params + kOffW4, pred, nullptr, 0.f,
+                               nullptr, nullptr, nullptr);
         else
             hipLaunchKernelGGL(k_head_mfma, dim3(grid_for(ne, 128)), b, 0, s, ne, cand, u, v,
                                (const __hip_bfloat16 *)p.h2, edge_feat, params + kOffW3, params + kOffW4, pred);
@@ -802,39 +939,29 @@ extern "C" sfg_status sfg_mpnn_loss_grad(const sfg_csr *G, const float *params, 
         Carver c(ws);
         TrainPlan p = plan_train(c, n, ne);
         const dim3 gn(grid_for(n, 256)), ge(grid_for(ne, 256)), b(256);
-        // ---- forward, keeping what the backward needs
+        // ---- forward
         spmm_rownorm(G, kF, SFG_F32, node_feat, p.a1, s);
-        hipLaunchKernelGGL((k_dense_fwd<float, float, kF>), gn, b, 0, s, n, node_feat, p.a1, params + kOffW1, p.h1,
-                           p.pre1, p.u1);
+        hipLaunchKernelGGL(k_dense_f32<kF>, dim3(grid_for(n, 128)), b, 0, s, n, node_feat, p.a1, params + kOffW1, p.h1);
         SFG_LAUNCH_CHECK();
         spmm_rownorm(G, kH, SFG_F32, p.h1, p.a2, s);
-        hipLaunchKernelGGL((k_dense_fwd<float, float, kH>), gn, b, 0, s, n, p.h1, p.a2, params + kOffW2, p.h2, p.pre2,
-                           p.u2);
+        hipLaunchKernelGGL(k_dense_f32<kH>, dim3(grid_for(n, 128)), b, 0, s, n, p.h1, p.a2, params + kOffW2, p.h2);
         SFG_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_head_fwd<float>, ge, b, 0, s, ne, cand, u, v, p.h2, edge_feat, params + kOffW3,
-                           params + kOffW4, pred, p.g, p.z);
+        // ---- edge head, forward and backward
+        const int nbe = train_blocks(ne), nbn = train_blocks(n);
+        hipLaunchKernelGGL(k_head_f32<true>, dim3(nbe), b, 0, s, ne, cand, u, v, p.h2, edge_feat, params + kOffW3,
+                           params + kOffW4, pred, target, 2.f / (float)ne, p.dhp, p.dhq, p.part3);
         SFG_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_sq_err_partial, dim3(256), b, 0, s, ne, pred, target, p.lpart);
-        SFG_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, s, 256, p.lpart, 1.f / (float)ne, loss);
-        SFG_LAUNCH_CHECK();
-        // ---- backward: edge head
-        hipLaunchKernelGGL(k_head_bwd, ge, b, 0, s, ne, cand, u, v, p.h2, pred, target, p.g, params + kOffW3,
-                           params + kOffW4, 2.f / (float)ne, p.dg, p.ah1, p.dy, p.dhp, p.dhq);
-        SFG_LAUNCH_CHECK();
-        atb(ne, kZ1, p.z, kH, p.dg, grad + kOffW3, p.part, s);
-        atb(ne, kH + 1, p.ah1, 1, p.dy, grad + kOffW4, p.part, s);
         // edge gradients to nodes through the incidence CSR of the candidate edges
         hipLaunchKernelGGL(k_gather_uv, ge, b, 0, s, ne, cand, u, v, p.cu, p.cv, p.ones_e);
         SFG_LAUNCH_CHECK();
         build_csr(n, ne, p.cu, p.cv, p.ones_e, SFG_F32, nullptr, p.irp, p.icol, p.incval, p.ieid, p.incdeg, p.csr_ws,
                   csr_workspace_bytes(n, ne), s);
-        hipLaunchKernelGGL(k_gather_dh, gn, b, 0, s, n, p.irp, p.icol, p.ieid, p.dhp, p.dhq, p.pre2, p.dpre2);
+        hipLaunchKernelGGL(k_gather_dh, dim3(grid_for(n * 8, 256)), b, 0, s, n, p.irp, p.icol, p.ieid, p.dhp, p.dhq,
+                           p.h2, p.dpre2);
         SFG_LAUNCH_CHECK();
         // ---- layer 2
-        atb(n, kU2, p.u2, kH, p.dpre2, grad + kOffW2, p.part, s);
-        hipLaunchKernelGGL((k_dense_bwd<kH>), gn, b, 0, s, n, p.dpre2, params + kOffW2, (const float *)G->deg, p.t1,
-                           p.t2);
+        hipLaunchKernelGGL((k_dense_grad<kH, true>), dim3(nbn), b, 0, s, n, p.h1, p.a2, p.dpre2, nullptr, nullptr,
+                           params + kOffW2, (const float *)G->deg, p.t1, p.t2, p.part2);
         SFG_LAUNCH_CHECK();
         // A (dP Wn^T / D): the sweep with unit degrees is the plain product
         hipLaunchKernelGGL(k_fill_f32, gn, b, 0, s, n, 1.f, p.ones_n);
@@ -842,10 +969,13 @@ extern "C" sfg_status sfg_mpnn_loss_grad(const sfg_csr *G, const float *params, 
         sfg_csr Gu = *G;
         Gu.deg = p.ones_n;
         spmm_rownorm(&Gu, kH, SFG_F32, p.t2, p.c2, s);
-        hipLaunchKernelGGL(k_add_mask, dim3(grid_for(n * kH, 256)), b, 0, s, n * kH, p.t1, p.c2, p.pre1, p.dpre1);
+        // ---- layer 1, and the sums over the partials
+        hipLaunchKernelGGL((k_dense_grad<kF, false>), dim3(nbn), b, 0, s, n, node_feat, p.a1, p.t1, p.c2, p.h1,
+                           params + kOffW1, nullptr, nullptr, nullptr, p.part1);
         SFG_LAUNCH_CHECK();
-        // ---- layer 1
-        atb(n, kU1, p.u1, kH, p.dpre1, grad + kOffW1, p.part, s);
+        hipLaunchKernelGGL(k_grad_finish, dim3(grid_for(kParams + 1, 32)), b, 0, s, nbn, nbn, nbe, p.part1, p.part2,
+                           p.part3, 1.f / (float)ne, grad, loss);
+        SFG_LAUNCH_CHECK();
     });
 }
 
