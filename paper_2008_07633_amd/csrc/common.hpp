@@ -278,6 +278,20 @@ struct DevArena {
     }
 };
 
+// Buffers of the tree preconditioner inside the conjugate gradients (blocks
+// in the tree's preorder; tree.hip, kappa.hip).
+struct TreePrecond {
+    int64_t n = 0, A = 0;              // nodes, walk steps
+    int32_t k = 0, lanes = 0;          // columns; rows of rz
+    int64_t rtiles = 0, wtiles = 0;    // tiles of block_scan over the rows, over the walk
+    int32_t *step = nullptr;           // [A] i at the step entering node i, ~i at the step leaving it
+    double *S = nullptr, *walk = nullptr;                                            // [n][k], [A][k]
+    double *rsum = nullptr, *wsum = nullptr, *rgroup = nullptr, *wgroup = nullptr;   // tile sums, group sums
+    double *tot = nullptr;             // [k] column totals of r
+    double *rz = nullptr;              // [lanes][k] lane sums of r . z (one lane: their sum, from partials in dot)
+    double *dot = nullptr;
+};
+
 inline uint32_t grid_for(int64_t items, int block) {
     int64_t g = (items + block - 1) / block;
     return (uint32_t)(g < 1 ? 1 : g);

@@ -16,9 +16,9 @@
 // solve after the first started from the Ritz pairs (X = Y diag(theta)).
 // Every block lives in the tree's preorder: G and P are relabelled once, so
 // the tree solve needs no gathers and tree neighbours sit in nearby rows.
-// HBM-bound: per iteration one Laplacian product on P (with p . Ap fused),
-// the CG update (with r . r fused) and the tree solve (two block prefix sums,
-// with r . z fused).
+// Seven launches per iteration: the direction, the Laplacian product on P
+// (with p . Ap), the CG update (with r . r and r's tile sums), the tree
+// solve's three and r . z.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -47,11 +47,14 @@ size_t gram_scratch_doubles(int32_t k);
 void block_gram(int64_t rows, int32_t k, const double *x, const double *y, double *out, double *scratch,
                 hipStream_t s);
 void convert_weights(const void *w, sfg_dtype wt, sfg_dtype want, int64_t m, void *out, hipStream_t s);
-uint32_t lane_grid(int64_t rows, int32_t k);
-size_t lane_partial_doubles(int32_t k);
 void finish_partials(int32_t nb, int32_t k, const double *partial, double *out, hipStream_t s);
-size_t tree_precond_workspace_bytes(int64_t n, int32_t k);
-void tree_precond_pre(const sfg_tree *T, int32_t k, const double *r, double *z, double *rz, void *ws, hipStream_t s);
+size_t tree_precond_bytes(int64_t n, int32_t k);
+TreePrecond make_tree_precond(const sfg_tree *T, int32_t k, void *ws, hipStream_t s);
+void cg_step(const TreePrecond &p, uint32_t active, const uint32_t *dmask, const double *rz, const double *pap,
+             int32_t pap_rows, const double *pd, const double *ap, double *x, double *r, double *rr, hipStream_t s);
+void precond_row_sums(const TreePrecond &p, double *r, hipStream_t s);
+void tree_precond(const sfg_tree *T, const TreePrecond &p, const double *r, double *z, hipStream_t s);
+uint32_t lane_grid(int64_t rows, int32_t k);
 
 namespace {
 
@@ -71,19 +74,6 @@ __global__ void k_lap(int64_t n, int32_t k, const int32_t *__restrict__ rowptr, 
 }
 
 __device__ __forceinline__ double safe_div(double a, double b) { return b != 0.0 ? a / b : 0.0; }
-
-// p = z + beta p with beta_c = rz_new_c / rz_c on active columns (the mask
-// `active`, or *dmask when the device keeps it)
-__global__ void k_cg_dir(int64_t n, int32_t k, uint32_t active, const uint32_t *__restrict__ dmask,
-                         const double *__restrict__ rz_new, const double *__restrict__ rz,
-                         const double *__restrict__ z, double *__restrict__ p) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * k) return;
-    const int c = (int)(t % k);
-    const uint32_t act = dmask ? *dmask : active;
-    if (!((act >> c) & 1u)) return;
-    p[t] = z[t] + safe_div(rz_new[c], rz[c]) * p[t];
-}
 
 // Convergence test on the device, after each iteration: a column whose
 // ||r||^2 is no longer above tol^2 ||z||^2 leaves the mask (the same test, on
@@ -158,81 +148,114 @@ __global__ void k_gather_rows(int64_t n, int32_t k, const int32_t *__restrict__ 
 }
 
 // ---- conjugate-gradient kernels in the row-lane layout: a workgroup is
-// G x k threads (G = 256 / k), thread (g, c) owns column c of rows
-// blockIdx * G + g + j * gridDim * G; per-workgroup column partial sums of a
-// product go to partial[blockIdx][c] (reduced in a fixed order afterwards)
+// G x k/V threads (G = 256 V / k), thread (g, c) owns V columns of rows g,
+// g + G, ... of a grid-strided range; per-workgroup column sums go to
+// partial[workgroup][column]
 
-__device__ __forceinline__ void lane_reduce(double acc, int32_t k, double *sh, double *partial) {
-    sh[threadIdx.x] = acc;
+// sh[c] = (r . z)_c, c < k, from its lane sums ([lanes][k], lanes * k <= 1024)
+// added as k_partials_finish does: four lanes per thread, then pairs.
+__device__ __forceinline__ void lane_total(const double *__restrict__ lane, int32_t lanes, int32_t k, double *sh) {
+    const int four = (lanes + 3) / 4;
+    const int lg = threadIdx.x / k, lc = threadIdx.x % k, step = kB / k;
+    for (int l = lg; l < four && lg < step; l += step) {
+        double v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = 4 * l + i < lanes ? lane[(4 * l + i) * k + lc] : 0.0;
+        sh[l * k + lc] = (v[0] + v[1]) + (v[2] + v[3]);
+    }
     __syncthreads();
-    if ((int)threadIdx.x < k) {
-        const int G = kB / k;
-        double t = 0.0;
-        for (int g = 0; g < G; ++g) t += sh[g * k + threadIdx.x];
-        partial[(int64_t)blockIdx.x * k + threadIdx.x] = t;
+    for (int st = 1; st < four; st <<= 1) {
+        for (int l = lg; l < four && lg < step; l += step)
+            if ((l & (2 * st - 1)) == 0 && l + st < four) sh[l * k + lc] += sh[(l + st) * k + lc];
+        __syncthreads();
     }
 }
 
-// y = L_H x and partial sums of x . y
-__global__ __launch_bounds__(kB) void k_lap_dot(int64_t n, int32_t k, const int32_t *__restrict__ rowptr,
-                                                const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                const double *__restrict__ deg, const double *__restrict__ x,
-                                                double *__restrict__ y, double *__restrict__ partial) {
-    __shared__ double sh[kB];
-    const int G = kB / k;
-    const int g = threadIdx.x / k, c = threadIdx.x % k;
-    double acc = 0.0;
+// y = L_P x and the partial sums of x . y, four neighbours in flight.
+template <int V>
+__global__ __launch_bounds__(kB) void k_cg_lap(int64_t n, int32_t k, const int32_t *__restrict__ rowptr,
+                                               const int32_t *__restrict__ col, const double *__restrict__ val,
+                                               const double *__restrict__ deg, const double *__restrict__ x,
+                                               double *__restrict__ y, double *__restrict__ partial) {
+    __shared__ double sh[V * kB];
+    const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int kv = k / V, G = kB / kv;
+    const int g = threadIdx.x / kv, cv = (threadIdx.x % kv) * V;
+    auto entry = [&](int64_t row, double (&d)[V]) {
+#pragma unroll
+        for (int q = 0; q < V; ++q) d[q] = x[row * k + cv + q];
+    };
+    double acc[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) acc[q] = 0.0;
     if (g < G)
-        for (int64_t p = (int64_t)blockIdx.x * G + g; p < n; p += (int64_t)gridDim.x * G) {
-            double a = 0.0;
-            for (int32_t j = rowptr[p], e = rowptr[p + 1]; j < e; ++j) a += val[j] * x[(int64_t)col[j] * k + c];
-            const double xp = x[p * k + c];
-            const double yp = deg[p] * xp - a;
-            y[p * k + c] = yp;
-            acc += xp * yp;
-        }
-    lane_reduce(acc, k, sh, partial);
-}
-
-// Same for even k, two adjacent columns per thread (16-byte loads and stores);
-// the sums are added in the same order as k_lap_dot's
-__global__ __launch_bounds__(kB) void k_lap_dot2(int64_t n, int32_t k, const int32_t *__restrict__ rowptr,
-                                                 const int32_t *__restrict__ col, const double *__restrict__ val,
-                                                 const double *__restrict__ deg, const double *__restrict__ x,
-                                                 double *__restrict__ y, double *__restrict__ partial) {
-    __shared__ double sh[2 * kB];
-    const int kv = k >> 1;
-    const int G = kB / kv;
-    const int g = threadIdx.x / kv, c2 = threadIdx.x % kv;
-    double acc0 = 0.0, acc1 = 0.0;
-    if (g < G)
-        for (int64_t p = (int64_t)blockIdx.x * G + g; p < n; p += (int64_t)gridDim.x * G) {
-            double a0 = 0.0, a1 = 0.0;
-            for (int32_t j = rowptr[p], e = rowptr[p + 1]; j < e; ++j) {
-                const double w = val[j];
-                const double2 xv = *reinterpret_cast<const double2 *>(x + (int64_t)col[j] * k + 2 * c2);
-                a0 += w * xv.x;
-                a1 += w * xv.y;
+        for (int64_t p = b * G + g; p < n; p += (int64_t)gridDim.x * G) {
+            double a[V], self[V];
+#pragma unroll
+            for (int q = 0; q < V; ++q) a[q] = 0.0;
+            const int32_t j0 = rowptr[p], e = rowptr[p + 1];
+            entry(p, self);
+            for (int32_t j = j0; j < e; j += 4) {       // four neighbours in flight
+                double w[4], d[4][V];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int32_t at = j + i < e ? j + i : e - 1;
+                    w[i] = val[at];
+                    entry(col[at], d[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (j + i < e) {
+#pragma unroll
+                        for (int q = 0; q < V; ++q) a[q] += w[i] * d[i][q];
+                    }
             }
-            const double2 xp = *reinterpret_cast<const double2 *>(x + p * k + 2 * c2);
-            const double d = deg[p];
-            double2 yp;
-            yp.x = d * xp.x - a0;
-            yp.y = d * xp.y - a1;
-            *reinterpret_cast<double2 *>(y + p * k + 2 * c2) = yp;
-            acc0 += xp.x * yp.x;
-            acc1 += xp.y * yp.y;
+            const double dp = deg[p];
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+                const double yq = dp * self[q] - a[q];
+                y[p * k + cv + q] = yq;
+                acc[q] += self[q] * yq;
+            }
         }
-    sh[2 * threadIdx.x] = acc0;
-    sh[2 * threadIdx.x + 1] = acc1;
+#pragma unroll
+    for (int q = 0; q < V; ++q) sh[V * threadIdx.x + q] = acc[q];
     __syncthreads();
     if ((int)threadIdx.x < k) {
-        const int cc = threadIdx.x >> 1, half = threadIdx.x & 1;
+        const int cc = threadIdx.x / V, q = threadIdx.x % V;
         double t = 0.0;
-        for (int gg = 0; gg < G; ++gg) t += sh[2 * (gg * kv + cc) + half];
-        partial[(int64_t)blockIdx.x * k + threadIdx.x] = t;
+#pragma unroll 8
+        for (int gg = 0; gg < G; ++gg) t += sh[V * (gg * kv + cc) + q];
+        partial[b * k + threadIdx.x] = t;
     }
 }
+
+// The direction p = z + beta p on active columns (p = z in the first
+// iteration), beta_c = (r . z)_c / rz_old_c with r . z from its lane sums in
+// every workgroup; the first one leaves it in rz_cur.  A product that formed
+// its neighbours' directions itself saved this launch (4 % of an iteration
+// over 90,000 rows of 8) and took 51 us for 36 over 380,000.
+__global__ __launch_bounds__(kB) void k_cg_dir(int64_t n, int32_t k, int32_t first, uint32_t active,
+                                               const uint32_t *__restrict__ dmask,
+                                               const double *__restrict__ rz_lane, int32_t lanes,
+                                               const double *__restrict__ rz_old, double *__restrict__ rz_cur,
+                                               const double *__restrict__ z, double *__restrict__ p) {
+    __shared__ double sh[2 * kB];
+    lane_total(rz_lane, lanes, k, sh);
+    if (blockIdx.x == 0 && (int)threadIdx.x < k) rz_cur[threadIdx.x] = sh[threadIdx.x];
+    const int G = kB / k, g = threadIdx.x / k, c = threadIdx.x % k;
+    const uint32_t act = dmask ? *dmask : active;
+    if (g >= G || !(first || ((act >> c) & 1u))) return;
+    const double beta = first ? 0.0 : safe_div(sh[c], rz_old[c]);
+    const int64_t stride = (int64_t)gridDim.x * G * k;
+#pragma unroll 4
+    for (int64_t t = (int64_t)blockIdx.x * G * k + threadIdx.x; t < n * k; t += stride)
+        p[t] = first ? z[t] : z[t] + beta * p[t];
+}
+
+// The update's workgroups add up to this many partial sums of p . Ap each
+// (8 columns: 128 KB); more are added by a launch of their own.
+constexpr int32_t kPapRows = 2048;
 
 // r = z - L_H x
 __global__ void k_lap_resid(int64_t n, int32_t k, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
@@ -245,33 +268,6 @@ __global__ void k_lap_resid(int64_t n, int32_t k, const int32_t *__restrict__ ro
     double a = 0.0;
     for (int32_t j = rowptr[p], e = rowptr[p + 1]; j < e; ++j) a += val[j] * x[(int64_t)col[j] * k + c];
     r[t] = z[t] - (deg[p] * x[t] - a);
-}
-
-// x += alpha p, r -= alpha Ap (alpha_c = rz_c / pAp_c on active columns) and partial sums of r . r
-__global__ __launch_bounds__(kB) void k_cg_step_rr(int64_t n, int32_t k, uint32_t active,
-                                                   const uint32_t *__restrict__ dmask,
-                                                   const double *__restrict__ rz, const double *__restrict__ pap,
-                                                   const double *__restrict__ p, const double *__restrict__ ap,
-                                                   double *__restrict__ x, double *__restrict__ r,
-                                                   double *__restrict__ partial) {
-    __shared__ double sh[kB];
-    const int G = kB / k;
-    const int g = threadIdx.x / k, c = threadIdx.x % k;
-    const bool on = ((dmask ? *dmask : active) >> c) & 1u;
-    const double a = on ? safe_div(rz[c], pap[c]) : 0.0;
-    double acc = 0.0;
-    if (g < G)
-        for (int64_t i = (int64_t)blockIdx.x * G + g; i < n; i += (int64_t)gridDim.x * G) {
-            const int64_t t = i * k + c;
-            double ri = r[t];
-            if (on) {
-                x[t] += a * p[t];
-                ri -= a * ap[t];
-                r[t] = ri;
-            }
-            acc += ri * ri;
-        }
-    lane_reduce(acc, k, sh, partial);
 }
 
 // x = y diag(theta): the Ritz pairs' image under L_P^+ L_G, a warm start
@@ -411,11 +407,12 @@ struct KappaEstimator {
     int32_t *t_order, *t_parent, *t_size, *t_tdown, *t_tup, *inv;
     double *t_pw;
     sfg_tree T;
-    void *csr_ws, *pre_ws;
+    void *csr_ws;
+    TreePrecond M;
     size_t csr_wsb;
     // n x k blocks in preorder
     double *Y, *Z, *X, *R, *Zp, *Pd, *AP, *W, *VP;
-    double *small, *part, *gram_scr;
+    double *small, *part, *rrpart, *gram_scr;
 
     PreCsr alloc_pre(DevArena &A) {
         PreCsr c;
@@ -469,11 +466,12 @@ struct KappaEstimator {
         G = alloc_pre(A);
         P = alloc_pre(A);
         build_pre(nullptr, G);
-        pre_ws = A.raw(tree_precond_workspace_bytes(n, k));
+        M = make_tree_precond(&T, k, A.raw(tree_precond_bytes(n, k)), s);
         double **blocks[] = {&Y, &Z, &X, &R, &Zp, &Pd, &AP, &W, &VP};
         for (double **bl : blocks) *bl = A.alloc<double>(nk + 1);
         small = A.alloc<double>(16 * 64 + 3 * 32 * 32);
-        part = A.alloc<double>(lane_partial_doubles(k));
+        part = A.alloc<double>(std::max<size_t>((size_t)lane_grid(n, k) * k, colsum_scratch_doubles(k)) + 64);
+        rrpart = A.alloc<double>((size_t)M.rtiles * k + 64);
         gram_scr = A.alloc<double>(gram_scratch_doubles(k));
     }
 
@@ -501,8 +499,7 @@ struct KappaEstimator {
     int64_t solve(double tol, int32_t max_iter, const double *theta, bool *hit_cap, int check_every = 4) {
         double *rz0 = small, *rz1 = small + 64, *pap = small + 128, *rr = small + 192, *zz = small + 256;
         const dim3 g(grid_for(n * k, kB)), b(kB);
-        const uint32_t lg = lane_grid(n, k);
-        const uint32_t lg2 = k % 2 == 0 ? lane_grid(n, k / 2) : lg;   // two columns per thread
+        const int32_t lb = (int32_t)lane_grid(n, k % 2 == 0 ? k / 2 : k);   // two columns per thread
         block_dot(n, k, Z, Z, zz, part, s);
         if (theta) {
             hipLaunchKernelGGL(k_scale_cols, g, b, 0, s, n, k, Y, theta, X);
@@ -521,8 +518,8 @@ struct KappaEstimator {
             if (h0[c] > tol * tol * hz[c]) active |= 1u << c;
         *hit_cap = false;
         if (!active) return 0;
-        tree_precond_pre(&T, k, R, Zp, rz0, pre_ws, s);
-        SFG_HIP(hipMemcpyAsync(Pd, Zp, (size_t)n * k * sizeof(double), hipMemcpyDeviceToDevice, s));
+        precond_row_sums(M, R, s);
+        tree_precond(&T, M, R, Zp, s);
         const bool dev_check = check_every == 0;
         const int kCheck = dev_check ? kPoll : (check_every < 1 ? 1 : check_every);
         uint32_t *dmask = nullptr;
@@ -541,22 +538,24 @@ struct KappaEstimator {
                 break;
             }
             ++it;
+            const int32_t first = it == 1 ? 1 : 0;
+            hipLaunchKernelGGL(k_cg_dir, dim3((uint32_t)std::min<int64_t>(2048, lane_grid(n, k))), b, 0, s, n, k, first,
+                               active, dmask, M.rz, M.lanes, rz0, rz1, Zp, Pd);
+            SFG_LAUNCH_CHECK();
             if (k % 2 == 0)
-                hipLaunchKernelGGL(k_lap_dot2, dim3(lg2), dim3(kB), 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
+                hipLaunchKernelGGL(k_cg_lap<2>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
                                    part);
             else
-                hipLaunchKernelGGL(k_lap_dot, dim3(lg), dim3(kB), 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
+                hipLaunchKernelGGL(k_cg_lap<1>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
                                    part);
             SFG_LAUNCH_CHECK();
-            finish_partials((int32_t)(k % 2 == 0 ? lg2 : lg), k, part, pap, s);
-            hipLaunchKernelGGL(k_cg_step_rr, dim3(lg), dim3(kB), 0, s, n, k, active, dmask, rz0, pap, Pd, AP, X, R,
-                               part);
-            SFG_LAUNCH_CHECK();
-            finish_partials((int32_t)lg, k, part, rr, s);
-            tree_precond_pre(&T, k, R, Zp, rz1, pre_ws, s);
-            hipLaunchKernelGGL(k_cg_dir, g, b, 0, s, n, k, active, dmask, rz1, rz0, Zp, Pd);
-            SFG_LAUNCH_CHECK();
-            std::swap(rz0, rz1);
+            std::swap(rz0, rz1);      // rz0: this iteration's r . z
+            if (lb > kPapRows) finish_partials(lb, k, part, pap, s);
+            cg_step(M, active, dmask, rz0, lb > kPapRows ? pap : part, lb > kPapRows ? 0 : lb, Pd, AP, X, R, rrpart,
+                    s);
+            const bool test = dev_check || it % kCheck == 0 || it == max_iter;
+            if (test) finish_partials((int32_t)M.rtiles, k, rrpart, rr, s);
+            tree_precond(&T, M, R, Zp, s);
             if (dev_check) {
                 hipLaunchKernelGGL(k_cg_check, dim3(1), dim3(64), 0, s, k, rr, zz, tol2, dmask, dit);
                 SFG_LAUNCH_CHECK();

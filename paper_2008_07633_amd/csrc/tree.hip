@@ -306,12 +306,14 @@ __global__ __launch_bounds__(kB) void k_colsum(int64_t rows, int32_t k, const do
     }
 }
 
-// stage 2: out[c] = scale * sum of the partials, in workgroup order
+// stage 2: out[c] = scale * sum of the partials, in workgroup order (sixteen
+// loads in flight: 512 partials one after the other took 77 us, now 13)
 __global__ void k_colsum_finish(int32_t nb, int32_t k, const double *__restrict__ partial, double scale,
                                 double *__restrict__ out) {
     const int c = threadIdx.x;
     if (c >= k) return;
     double t = 0.0;
+#pragma unroll 16
     for (int b = 0; b < nb; ++b) t += partial[(int64_t)b * k + c];
     out[c] = t * scale;
 }
@@ -371,6 +373,7 @@ __global__ void k_gram_finish(int32_t nb, int32_t P, const double *__restrict__ 
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= P) return;
     double t = 0.0;
+#pragma unroll 16
     for (int b = 0; b < nb; ++b) t += partial[(int64_t)b * P + e];
     out[e] = t;
 }
@@ -531,49 +534,6 @@ __global__ void k_scatter_centre(int64_t n, int32_t k, const int32_t *__restrict
     x[(int64_t)order[i] * k + c] = xp[t] - mean[c];
 }
 
-// Preconditioner form (blocks already in preorder): the edge drops use the
-// column means from the scan totals instead of a centred copy of b.
-__global__ void k_edge_drop_pre(int64_t n, int32_t k, const int32_t *__restrict__ size, const double *__restrict__ pw,
-                                const int32_t *__restrict__ tdown, const int32_t *__restrict__ tup,
-                                const double *__restrict__ S, const double *__restrict__ totals,
-                                double *__restrict__ walk) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * k || t < k) return;
-    const int64_t i = t / k;
-    const int c = (int)(t - i * k);
-    const int32_t sz = size[i];
-    const double mean = totals[c] / (double)n;
-    const double f = (S[(i + sz - 1) * k + c] - S[(i - 1) * k + c]) - (double)sz * mean;
-    const double d = f / pw[i];
-    walk[(int64_t)tdown[i] * k + c] = d;
-    walk[(int64_t)tup[i] * k + c] = -d;
-}
-
-// z[i] = prefix of the walk at i's down step (0 at the root), and per-column
-// partial sums of r . z.  Row-lane layout: workgroup of G x k threads,
-// thread (g, c) walks rows blockIdx * G + g + j * gridDim * G.
-__global__ __launch_bounds__(kB) void k_potential_dot(int64_t n, int32_t k, const int32_t *__restrict__ tdown,
-                                                      const double *__restrict__ U, const double *__restrict__ r,
-                                                      double *__restrict__ z, double *__restrict__ partial) {
-    __shared__ double sh[kB];
-    const int G = lanes_g(k);
-    const int g = threadIdx.x / k, c = threadIdx.x % k;
-    double acc = 0.0;
-    if (g < G)
-        for (int64_t i = (int64_t)blockIdx.x * G + g; i < n; i += (int64_t)gridDim.x * G) {
-            const double zi = i == 0 ? 0.0 : U[(int64_t)tdown[i] * k + c];
-            z[i * k + c] = zi;
-            acc += r[i * k + c] * zi;
-        }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.x < k) {
-        double t = 0.0;
-        for (int gg = 0; gg < G; ++gg) t += sh[gg * k + threadIdx.x];
-        partial[(int64_t)blockIdx.x * k + threadIdx.x] = t;
-    }
-}
-
 // out[c] = sum of nb partials of column c: one workgroup of 1024 threads,
 // lane (g, c) adds partials g, g + G, ... into four accumulators (loads in
 // flight), then a fixed pairwise tree over the lanes
@@ -667,11 +627,6 @@ size_t scan_scratch_doubles(int64_t rows, int32_t k) {
     return (size_t)(scan_tiles(rows, k) + scan_groups(rows, k) + 1) * k + 64;
 }
 
-// column totals of the last block_scan that used this scratch
-const double *scan_totals(int64_t rows, int32_t k, const double *scratch) {
-    return scratch + (size_t)(scan_tiles(rows, k) + scan_groups(rows, k)) * k;
-}
-
 // inclusive prefix sums down the rows of a rows x k block; y must not alias x
 void block_scan(int64_t rows, int32_t k, const double *x, double *y, double *scratch, hipStream_t s) {
     if (rows <= 0) return;
@@ -697,51 +652,502 @@ uint32_t lane_grid(int64_t rows, int32_t k) {
     return (uint32_t)(nb < 1 ? 1 : (nb > kLaneBlocks ? kLaneBlocks : nb));
 }
 
-size_t lane_partial_doubles(int32_t k) { return (size_t)kLaneBlocks * k + 64; }
-
 void finish_partials(int32_t nb, int32_t k, const double *partial, double *out, hipStream_t s) {
     hipLaunchKernelGGL(k_partials_finish, dim3(1), dim3(kFinish), 0, s, nb, k, partial, out);
     SFG_LAUNCH_CHECK();
 }
 
-size_t tree_precond_workspace_bytes(int64_t n, int32_t k) {
+// ------------------------------------------------------------------ the preconditioner inside the conjugate gradients
+//
+// z = L_T^+ r up to a constant per column, for blocks in the tree's preorder
+// (row i is node order[i]; constants are in the kernel of every Laplacian, so
+// they change neither the iterates' residuals nor r . z for r orthogonal to
+// the all-one vector).  Four launches after the kernel that updates r, which
+// leaves r's tile sums: prefix sums S of r; the walk's potential drops, each
+// step gathering its edge's two entries of S, with their tile sums; prefix
+// sums along the walk, written at the steps that enter a node as z; r . z.
+// All of them read a few MB, and an iteration is bound by the launches' own
+// latency, so a launch's small sums are added up by the workgroups of the
+// next one.  Conjugate gradients stopped at a loose tolerance carry the
+// rounding of every sum into their result, so each sum keeps the order that
+// block_scan and k_partials_finish give it, whatever launch it is in.
+// On the 300 x 300 power grid (90,000 nodes, 8 columns) an iteration takes
+// 73 us in seven launches; it took 98 us in sixteen.
+
+namespace {
+
+constexpr int kT = 1024;               // threads of the kernels below: four per thread of block_scan's
+constexpr int kTE = 4;                 // elements of a tile per thread
+constexpr int kTileLds = kB * (kRpt + 1);
+
+// e / k for e < 4352 and k <= 32 (error e / 2^18 < 1 / k): an integer division
+// is some thirty instructions, and these kernels would need a dozen each.
+struct ByK {
+    int32_t k;
+    uint32_t m;
+    explicit ByK(int32_t k_) : k(k_), m((1u << 18) / (uint32_t)k_ + 1) {}
+    __device__ __forceinline__ int div(int e) const { return (int)(((uint32_t)e * m) >> 18); }
+    __device__ __forceinline__ int mod(int e) const { return e - div(e) * k; }
+};
+
+// A tile in LDS: element e = row * k + column, with a gap of k after every
+// kRpt rows, so that the threads that add kRpt rows each hit different banks.
+__device__ __forceinline__ int tile_lds(int e, const ByK &by) { return e + (by.div(e) / kRpt) * by.k; }
+
+// Partial sums of k columns ([rows][k]) added in the order of
+// k_partials_finish by a workgroup of kT threads; sh[c] = sum, c < k.
+__device__ __forceinline__ void finish_rows(const double *__restrict__ partial, int32_t nb, const ByK &by, double *sh) {
+    const int k = by.k, G = by.div(kFinish);
+    const int g = by.div(threadIdx.x), c = by.mod(threadIdx.x);
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    if (g < G) {
+        int b = g;
+        for (; b + 3 * G < nb; b += 4 * G) {
+            a0 += partial[(int64_t)b * k + c];
+            a1 += partial[(int64_t)(b + G) * k + c];
+            a2 += partial[(int64_t)(b + 2 * G) * k + c];
+            a3 += partial[(int64_t)(b + 3 * G) * k + c];
+        }
+        for (; b < nb; b += G) a0 += partial[(int64_t)b * k + c];
+    }
+    sh[threadIdx.x] = (a0 + a1) + (a2 + a3);
+    __syncthreads();
+    for (int st = 1; st < G; st <<= 1) {
+        if (g < G && (g & (2 * st - 1)) == 0 && g + st < G) sh[g * k + c] += sh[(g + st) * k + c];
+        __syncthreads();
+    }
+}
+
+// sh[0] + sh[k] + ... (rows terms), added in that order from 0 with eight
+// reads in flight: one read after the other is 32 LDS latencies.
+__device__ __forceinline__ double sum_lds(const double *sh, int rows, int k) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int i = 0; i < rows; ++i) t += sh[i * k];
+    return t;
+}
+
+// Column sums of a tile in LDS in the order of k_scan_tiles; SQ: of the squares as well.
+template <bool SQ>
+__device__ __forceinline__ void tile_totals(const double *tile, const ByK &by, double *sh, double *__restrict__ out,
+                                            double *__restrict__ out_sq) {
+    const int k = by.k, G = by.div(kB);
+    const int g = by.div(threadIdx.x), c = by.mod(threadIdx.x);
+    const bool lane = threadIdx.x < kB && g < G;
+    double acc = 0.0, sq = 0.0;
+    if (lane)
+        for (int r = 0; r < kRpt; ++r) {
+            const double v = tile[(g * (kRpt + 1) + r) * k + c];
+            acc += v;
+            sq += v * v;
+        }
+    if (threadIdx.x < kB) {
+        sh[threadIdx.x] = acc;
+        sh[kB + threadIdx.x] = sq;
+    }
+    __syncthreads();
+    const int h = threadIdx.x / 64, t = threadIdx.x % 64;
+    if (h < (SQ ? 2 : 1) && t < k) {
+        (h ? out_sq : out)[(int64_t)blockIdx.x * k + t] = sum_lds(sh + h * kB + t, G, k);
+    }
+}
+
+// off[c] = the sum before this workgroup's tile.  Direct form: from the tile
+// sums, at most four groups of tiles, one to a quarter of the workgroup, in
+// the order of k_scan_mid and k_scan_top; tot[c] then gets the sum of all
+// tiles up to this workgroup's group.  Else from those kernels' offsets.
+__device__ __forceinline__ void tile_offset(int64_t tiles, const double *__restrict__ tile_sum,
+                                            const double *__restrict__ group_off, const ByK &by, double *sh, double *off,
+                                            double *tot) {
+    const int k = by.k, G = by.div(kB);
+    const int64_t b = blockIdx.x, tpg = (int64_t)G * kTpl;
+    if (group_off) {
+        const int64_t groups = (tiles + tpg - 1) / tpg;
+        if ((int)threadIdx.x < k) {
+            off[threadIdx.x] = group_off[(b / tpg) * k + threadIdx.x] + tile_sum[b * k + threadIdx.x];
+            tot[threadIdx.x] = group_off[groups * k + threadIdx.x];
+        }
+        __syncthreads();
+        return;
+    }
+    const int quarter = threadIdx.x / kB, lt = threadIdx.x % kB;
+    const int g = by.div(lt), c = by.mod(lt);
+    const int64_t t0 = ((int64_t)quarter * G + g) * kTpl;
+    const int64_t mine = b / kTpl - (int64_t)quarter * G;          // lane of this tile, if in this quarter's group
+    const int qb = (int)(b / tpg);
+    double v[kTpl];
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < kTpl; ++q) {
+        v[q] = (g < G && quarter <= qb && t0 + q < tiles) ? tile_sum[(t0 + q) * k + c] : 0.0;
+        acc += v[q];
+    }
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    if (g == G - 1 || (g < G && g == mine)) {
+        double run = sum_lds(sh + quarter * kB + c, g, k);
+        double at = 0.0;
+#pragma unroll
+        for (int q = 0; q < kTpl; ++q) {
+            if (q == (int)(b % kTpl)) at = run;
+            run += v[q];
+        }
+        if (g == mine) off[c] = at;
+        if (g == G - 1) tot[quarter * k + c] = run;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < k) {
+        double base = 0.0;
+        for (int q = 0; q < qb; ++q) base += tot[q * k + threadIdx.x];
+        off[threadIdx.x] = base + off[threadIdx.x];
+        tot[threadIdx.x] = base + tot[qb * k + threadIdx.x];
+    }
+    __syncthreads();
+}
+
+// Inclusive prefix sums down a tile in LDS, in place, in the order of
+// k_scan_apply; sh: kB doubles.
+__device__ __forceinline__ void tile_prefix(double *tile, const ByK &by, const double *off, double *sh) {
+    const int k = by.k, G = by.div(kB);
+    const int g = by.div(threadIdx.x), c = by.mod(threadIdx.x);
+    const bool lane = threadIdx.x < kB && g < G;
+    double v[kRpt];
+    double acc = 0.0;
+#pragma unroll
+    for (int r = 0; r < kRpt; ++r) {
+        v[r] = lane ? tile[(g * (kRpt + 1) + r) * k + c] : 0.0;
+        acc += v[r];
+    }
+    if (threadIdx.x < kB) sh[threadIdx.x] = acc;
+    __syncthreads();
+    if (lane) {
+        double run = off[c];
+        for (int gg = 0; gg < g; ++gg) run += sh[gg * k + c];
+#pragma unroll
+        for (int r = 0; r < kRpt; ++r) {
+            run += v[r];
+            tile[(g * (kRpt + 1) + r) * k + c] = run;
+        }
+    }
+    __syncthreads();
+}
+
+__global__ void k_step_nodes(int64_t n, const int32_t *__restrict__ tdown, const int32_t *__restrict__ tup,
+                             int32_t *__restrict__ step) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n || i == 0) return;
+    step[tdown[i]] = (int32_t)i;
+    step[tup[i]] = ~(int32_t)i;
+}
+
+// The conjugate-gradient update x += alpha p, r -= alpha Ap (alpha_c = rz_c /
+// pAp_c on active columns) with the tile sums of r and of r . r.  pap_rows:
+// rows of partial sums of p . Ap, or 0: they are added up.  UPDATE = false:
+// the tile sums of r alone.
+template <bool UPDATE>
+__global__ __launch_bounds__(kT) void k_cg_step(int64_t n, ByK by, uint32_t active,
+                                                const uint32_t *__restrict__ dmask, const double *__restrict__ rz,
+                                                const double *__restrict__ pap, int32_t pap_rows,
+                                                const double *__restrict__ p, const double *__restrict__ ap,
+                                                double *__restrict__ x, double *__restrict__ r,
+                                                double *__restrict__ rr, double *__restrict__ tile_sum) {
+    __shared__ double tile[kTileLds], sh[kT], alpha[32];
+    const int k = by.k, E = by.div(kB) * kRpt * k;
+    const int64_t t0 = (int64_t)blockIdx.x * E, nk = n * k;
+    double rv[kTE], xv[kTE], pv[kTE], av[kTE];
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        const bool in = e < E && t0 + e < nk;
+        rv[q] = in ? r[t0 + e] : 0.0;
+        if constexpr (UPDATE) {
+            xv[q] = in ? x[t0 + e] : 0.0;
+            pv[q] = in ? p[t0 + e] : 0.0;
+            av[q] = in ? ap[t0 + e] : 0.0;
+        }
+    }
+    if constexpr (UPDATE) {
+        if (pap_rows) {
+            finish_rows(pap, pap_rows, by, sh);
+        } else {
+            if ((int)threadIdx.x < k) sh[threadIdx.x] = pap[threadIdx.x];
+            __syncthreads();
+        }
+        if ((int)threadIdx.x < k) {
+            const double d = sh[threadIdx.x];
+            alpha[threadIdx.x] = d != 0.0 ? rz[threadIdx.x] / d : 0.0;
+        }
+        __syncthreads();
+        const uint32_t act = dmask ? *dmask : active;
+#pragma unroll
+        for (int q = 0; q < kTE; ++q) {
+            const int e = (int)threadIdx.x + q * kT;
+            if (e >= E || t0 + e >= nk) continue;
+            const int c = by.mod(e);
+            if (!((act >> c) & 1u)) continue;
+            const double a = alpha[c];
+            xv[q] += a * pv[q];
+            rv[q] -= a * av[q];
+            x[t0 + e] = xv[q];
+            r[t0 + e] = rv[q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        if (e < E) tile[tile_lds(e, by)] = rv[q];
+    }
+    __syncthreads();
+    tile_totals<UPDATE>(tile, by, sh, tile_sum, rr);
+}
+
+// S = inclusive prefix sums of r down the rows; the last tile leaves the column totals.
+__global__ __launch_bounds__(kT) void k_rows_prefix(int64_t n, ByK by, const double *__restrict__ r,
+                                                    const double *__restrict__ tile_sum,
+                                                    const double *__restrict__ group_off, double *__restrict__ S,
+                                                    double *__restrict__ totals) {
+    __shared__ double tile[kTileLds], sh[kT], off[32], tot[4 * 32];
+    const int k = by.k, E = by.div(kB) * kRpt * k;
+    const int64_t t0 = (int64_t)blockIdx.x * E, nk = n * k;
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        if (e < E) tile[tile_lds(e, by)] = t0 + e < nk ? r[t0 + e] : 0.0;
+    }
+    tile_offset(gridDim.x, tile_sum, group_off, by, sh, off, tot);
+    if (blockIdx.x + 1 == gridDim.x && (int)threadIdx.x < k) totals[threadIdx.x] = tot[threadIdx.x];
+    tile_prefix(tile, by, off, sh);
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        if (e < E && t0 + e < nk) S[t0 + e] = tile[tile_lds(e, by)];
+    }
+}
+
+// The walk's potential drops: the step entering node i takes its parent edge's
+// drop (net demand below the edge over its weight), the step leaving it the
+// negative.  The demand's column mean comes off through the totals.
+__global__ __launch_bounds__(kT) void k_walk_drops(int64_t n, int64_t A, ByK by, const int32_t *__restrict__ step,
+                                                   const int32_t *__restrict__ size, const double *__restrict__ pw,
+                                                   const double *__restrict__ S, const double *__restrict__ totals,
+                                                   double *__restrict__ walk, double *__restrict__ tile_sum) {
+    __shared__ double tile[kTileLds], sh[kT], mean[32];
+    const int k = by.k, E = by.div(kB) * kRpt * k;
+    if ((int)threadIdx.x < k) mean[threadIdx.x] = totals[threadIdx.x] / (double)n;
+    const int64_t t0 = (int64_t)blockIdx.x * E, ak = A * k, row0 = (int64_t)blockIdx.x * by.div(kB) * kRpt;
+    int32_t nd[kTE], sz[kTE];
+    double w[kTE], lo[kTE], hi[kTE];
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        nd[q] = e < E && t0 + e < ak ? step[row0 + by.div(e)] : 1;      // node 1 exists wherever the walk has a step
+    }
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int64_t i = nd[q] >= 0 ? nd[q] : ~nd[q];
+        sz[q] = size[i];
+        w[q] = pw[i];
+    }
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int64_t i = nd[q] >= 0 ? nd[q] : ~nd[q];
+        const int c = by.mod((int)threadIdx.x + q * kT);
+        hi[q] = S[(i + sz[q] - 1) * k + c];
+        lo[q] = S[(i - 1) * k + c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        const double f = (hi[q] - lo[q]) - (double)sz[q] * mean[by.mod(e)];
+        const double d = f / w[q];
+        const bool in = e < E && t0 + e < ak;
+        const double y = in ? (nd[q] >= 0 ? d : -d) : 0.0;
+        if (in) walk[t0 + e] = y;
+        if (e < E) tile[tile_lds(e, by)] = y;
+    }
+    __syncthreads();
+    tile_totals<false>(tile, by, sh, tile_sum, nullptr);
+}
+
+// z at the nodes the walk enters: the prefix sum of the drops (the root's is 0).
+__global__ __launch_bounds__(kT) void k_walk_prefix(int64_t A, ByK by, const double *__restrict__ walk,
+                                                    const int32_t *__restrict__ step,
+                                                    const double *__restrict__ tile_sum,
+                                                    const double *__restrict__ group_off, double *__restrict__ z) {
+    __shared__ double tile[kTileLds], sh[kT], off[32], tot[4 * 32];
+    const int k = by.k, E = by.div(kB) * kRpt * k;
+    const int64_t t0 = (int64_t)blockIdx.x * E, ak = A * k, row0 = (int64_t)blockIdx.x * by.div(kB) * kRpt;
+    int32_t nd[kTE];
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        const bool in = e < E && t0 + e < ak;
+        nd[q] = in ? step[row0 + by.div(e)] : -1;
+        if (e < E) tile[tile_lds(e, by)] = in ? walk[t0 + e] : 0.0;
+    }
+    tile_offset(gridDim.x, tile_sum, group_off, by, sh, off, tot);
+    tile_prefix(tile, by, off, sh);
+#pragma unroll
+    for (int q = 0; q < kTE; ++q) {
+        const int e = (int)threadIdx.x + q * kT;
+        if (nd[q] >= 0) z[(int64_t)nd[q] * k + by.mod(e)] = tile[tile_lds(e, by)];
+    }
+    if (blockIdx.x == 0 && (int)threadIdx.x < k) z[threadIdx.x] = 0.0;
+}
+
+// r . z over nb groups of rows (group b: rows b * G + g, then every nb * G
+// further), as far as lane blockIdx.x of k_partials_finish adds them: groups
+// blockIdx.x, + L, ... for L = kFinish / k lanes.  lane_sum: [lanes][k].
+constexpr int kDotGroups = 24;         // groups in LDS at a time: 48 KB
+
+__global__ __launch_bounds__(kT) void k_dot_lanes(int64_t n, ByK by, int32_t nb, const double *__restrict__ r,
+                                                  const double *__restrict__ z, double *__restrict__ lane_sum) {
+    __shared__ double prod[kDotGroups * kB], part[kDotGroups * 32];
+    const int k = by.k, G = by.div(kB), L = by.div(kFinish);
+    const int quarter = threadIdx.x / kB, lt = threadIdx.x % kB;
+    const int32_t cnt = (nb - (int32_t)blockIdx.x + L - 1) / L;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int32_t i0 = 0; i0 < cnt; i0 += kDotGroups) {
+        const int here = cnt - i0 < kDotGroups ? cnt - i0 : kDotGroups;
+#pragma unroll
+        for (int q = 0; q < kDotGroups / 4; ++q) {
+            const int i = quarter + 4 * q;
+            const int64_t b = blockIdx.x + (int64_t)(i0 + i) * L;
+            double acc = 0.0;
+            if (i < here && lt < G * k)
+                for (int64_t t = b * G * k + lt; t < n * k; t += (int64_t)nb * G * k) acc += r[t] * z[t];
+            prod[i * kB + lt] = acc;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < here * k) {
+            const int i = by.div(threadIdx.x), c = by.mod(threadIdx.x);
+            part[threadIdx.x] = sum_lds(prod + i * kB + c, G, k);
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < k)
+            for (int i = 0; i < here; ++i) {
+                const int at = i0 + i, q = at < cnt / 4 * 4 ? at % 4 : 0;
+                const double v = part[i * k + threadIdx.x];
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if (w == q) a[w] += v;
+            }
+    }
+    if ((int)threadIdx.x < k) lane_sum[(int64_t)blockIdx.x * k + threadIdx.x] = (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// r . z, per-workgroup partial sums (finished by k_partials_finish)
+__global__ __launch_bounds__(kB) void k_dot_partials(int64_t n, ByK by, const double *__restrict__ r,
+                                                     const double *__restrict__ z, double *__restrict__ partial) {
+    __shared__ double sh[kB];
+    const int k = by.k, G = by.div(kB);
+    double acc = 0.0;
+    if ((int)threadIdx.x < G * k)
+        for (int64_t t = (int64_t)blockIdx.x * G * k + threadIdx.x; t < n * k; t += (int64_t)gridDim.x * G * k)
+            acc += r[t] * z[t];
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    if ((int)threadIdx.x < k) partial[(int64_t)blockIdx.x * k + threadIdx.x] = sum_lds(sh + threadIdx.x, G, k);
+}
+
+// k_dot_lanes has kFinish / k workgroups.  It saves a launch, and loses more
+// than that where each has many elements: r . z over 380,000 rows of 8 takes
+// 16 us (20 in two launches), over 552,000 of 32, on 32 workgroups, 292 (66).
+constexpr int64_t kDotPerLane = 32768;
+
+// Four groups of tiles are added up by the kernels that need the offsets (8
+// columns: 524,000 rows, at most 64 KB read per workgroup); more get
+// k_scan_mid and k_scan_top.
+constexpr int64_t kDirectGroups = 4;
+
+}  // namespace
+
+static TreePrecond plan_tree_precond(Carver &c, int64_t n, int32_t k) {
+    TreePrecond p;
+    p.n = n;
+    p.k = k;
+    p.A = 2 * (n - 1);
+    const int64_t A1 = p.A > 0 ? p.A : 1;
+    p.rtiles = scan_tiles(n, k);
+    p.wtiles = scan_tiles(A1, k);
+    const bool by_lane = n * k <= kDotPerLane * (kFinish / k);
+    p.lanes = by_lane ? kFinish / k : 1;
+    p.step = c.take<int32_t>(A1);
+    p.S = c.take<double>((size_t)n * k);
+    p.walk = c.take<double>((size_t)A1 * k);
+    p.rsum = c.take<double>((size_t)p.rtiles * k);
+    p.wsum = c.take<double>((size_t)p.wtiles * k);
+    p.rgroup = c.take<double>((size_t)(scan_groups(n, k) + 1) * k);
+    p.wgroup = c.take<double>((size_t)(scan_groups(A1, k) + 1) * k);
+    p.tot = c.take<double>(64);
+    p.rz = c.take<double>((size_t)p.lanes * k);
+    p.dot = by_lane ? nullptr : c.take<double>((size_t)lane_grid(n, k) * k);
+    return p;
+}
+
+size_t tree_precond_bytes(int64_t n, int32_t k) {
     Carver c(nullptr);
-    const int64_t A = 2 * (n - 1) > 0 ? 2 * (n - 1) : 1;
-    c.take<double>((size_t)n * k);
-    c.take<double>((size_t)A * k);
-    c.take<double>((size_t)A * k);
-    c.take<double>(scan_scratch_doubles(A > n ? A : n, k));
-    c.take<double>(lane_partial_doubles(k));
+    plan_tree_precond(c, n, k);
     return c.used + 256;
 }
 
-// z = L_T^+ r up to a constant per column, for blocks in the tree's preorder
-// (row i is node order[i]), and rz[c] = sum_i r[i][c] z[i][c]: the
-// conjugate-gradient preconditioner (constants are in the kernel of every
-// Laplacian, so they change neither the iterates' residuals nor r . z for r
-// orthogonal to the all-one vector).
-void tree_precond_pre(const sfg_tree *T, int32_t k, const double *r, double *z, double *rz, void *ws,
-                      hipStream_t s) {
-    const int64_t n = T->n;
-    const int64_t A = 2 * (n - 1) > 0 ? 2 * (n - 1) : 1;
+TreePrecond make_tree_precond(const sfg_tree *T, int32_t k, void *ws, hipStream_t s) {
     Carver c(ws);
-    double *S = c.take<double>((size_t)n * k);
-    double *walk = c.take<double>((size_t)A * k);
-    double *U = c.take<double>((size_t)A * k);
-    double *sscr = c.take<double>(scan_scratch_doubles(A > n ? A : n, k));
-    double *part = c.take<double>(lane_partial_doubles(k));
-    if (n > 1) {
-        block_scan(n, k, r, S, sscr, s);
-        // the column totals of r stay in the scratch until the walk scan reuses it
-        hipLaunchKernelGGL(k_edge_drop_pre, dim3(grid_for(n * k, kB)), dim3(kB), 0, s, n, k, T->size, T->pw,
-                           T->tdown, T->tup, S, scan_totals(n, k, sscr), walk);
-        SFG_LAUNCH_CHECK();
-        block_scan(A, k, walk, U, sscr, s);
-    }
-    const uint32_t nb = lane_grid(n, k);
-    hipLaunchKernelGGL(k_potential_dot, dim3(nb), dim3(kB), 0, s, n, k, T->tdown, U, r, z, part);
+    TreePrecond p = plan_tree_precond(c, T->n, k);
+    hipLaunchKernelGGL(k_step_nodes, dim3(grid_for(T->n, kB)), dim3(kB), 0, s, T->n, T->tdown, T->tup, p.step);
     SFG_LAUNCH_CHECK();
-    finish_partials((int32_t)nb, k, part, rz, s);
+    return p;
+}
+
+// rr: p.rtiles rows of partial sums.
+void cg_step(const TreePrecond &p, uint32_t active, const uint32_t *dmask, const double *rz, const double *pap,
+             int32_t pap_rows, const double *pd, const double *ap, double *x, double *r, double *rr, hipStream_t s) {
+    hipLaunchKernelGGL(k_cg_step<true>, dim3((uint32_t)p.rtiles), dim3(kT), 0, s, p.n, ByK(p.k), active, dmask, rz, pap,
+                       pap_rows, pd, ap, x, r, rr, p.rsum);
+    SFG_LAUNCH_CHECK();
+}
+
+// The tile sums of r alone (before the first iteration).
+void precond_row_sums(const TreePrecond &p, double *r, hipStream_t s) {
+    hipLaunchKernelGGL(k_cg_step<false>, dim3((uint32_t)p.rtiles), dim3(kT), 0, s, p.n, ByK(p.k), 0u, nullptr, nullptr,
+                       nullptr, 0, nullptr, nullptr, nullptr, r, nullptr, p.rsum);
+    SFG_LAUNCH_CHECK();
+}
+
+// z, and r . z as p.lanes rows of lane sums in p.rz, from r and its tile sums.
+void tree_precond(const sfg_tree *T, const TreePrecond &p, const double *r, double *z, hipStream_t s) {
+    const int32_t k = p.k;
+    const ByK by(k);
+    auto offsets = [&](int64_t tiles, double *sum, double *group) -> const double * {
+        const int64_t tpg = (int64_t)(kB / k) * kTpl, groups = (tiles + tpg - 1) / tpg;
+        if (groups <= kDirectGroups) return nullptr;
+        hipLaunchKernelGGL(k_scan_mid, dim3((uint32_t)groups), dim3(kB), 0, s, tiles, k, sum, group);
+        SFG_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kB), 0, s, groups, k, group);
+        SFG_LAUNCH_CHECK();
+        return group;
+    };
+    const double *ro = offsets(p.rtiles, p.rsum, p.rgroup);
+    hipLaunchKernelGGL(k_rows_prefix, dim3((uint32_t)p.rtiles), dim3(kT), 0, s, p.n, by, r, p.rsum, ro, p.S, p.tot);
+    SFG_LAUNCH_CHECK();
+    if (p.A > 0) {
+        hipLaunchKernelGGL(k_walk_drops, dim3((uint32_t)p.wtiles), dim3(kT), 0, s, p.n, p.A, by, p.step, T->size,
+                           T->pw, p.S, p.tot, p.walk, p.wsum);
+        SFG_LAUNCH_CHECK();
+    }
+    const double *wo = offsets(p.wtiles, p.wsum, p.wgroup);
+    hipLaunchKernelGGL(k_walk_prefix, dim3((uint32_t)p.wtiles), dim3(kT), 0, s, p.A, by, p.walk, p.step, p.wsum, wo, z);
+    SFG_LAUNCH_CHECK();
+    const int32_t nb = (int32_t)lane_grid(p.n, k);
+    if (p.lanes > 1) {
+        hipLaunchKernelGGL(k_dot_lanes, dim3((uint32_t)p.lanes), dim3(kT), 0, s, p.n, by, nb, r, z, p.rz);
+        SFG_LAUNCH_CHECK();
+    } else {
+        hipLaunchKernelGGL(k_dot_partials, dim3((uint32_t)nb), dim3(kB), 0, s, p.n, by, r, z, p.dot);
+        SFG_LAUNCH_CHECK();
+        finish_partials(nb, k, p.dot, p.rz, s);
+    }
 }
 
 // ------------------------------------------------------------------ tree layout
