@@ -12,12 +12,12 @@
 // block stacks the self weights, the neighbour weights and the bias, so a
 // weight gradient is one product U^T dP of the layer's input [x | a | 1].
 //
-// Kernels: the aggregations reuse the smoothing sweep (omega = 1).
-// Inference (BF16 activations) runs the dense layers and the edge head on the
-// matrix cores: a wavefront takes 32 nodes or edges, builds their [x | a | 1]
-// or z rows as BF16 MFMA operands (K padded to a multiple of 8), multiplies
-// by the BF16 weights with v_mfma_f32_32x32x8_bf16 into FP32 accumulators,
-// and applies the ReLU (and the head's last dot product) in FP32.  Training
+// Kernels: FP32 aggregations reuse the smoothing sweep (omega = 1).
+// Inference (BF16 activations) runs the layers, each with its aggregation, and
+// the edge head on the matrix cores: a wavefront takes 16 nodes or edges,
+// builds their x, a or z rows as BF16 MFMA operands, multiplies by the BF16
+// weights into FP32 accumulators, and applies the ReLU (and the head's last
+// dot product) in FP32.  Training
 // (and FP32 inference) runs on the matrix cores too, in FP32
 // (v_mfma_f32_32x32x2_f32).  One kernel takes the edge head forward and
 // backward, 32 edges per wavefront: predictions, loss, the gradients sent to
@@ -28,6 +28,7 @@
 // deterministic.  One loss and gradient on a 40^3 mesh (64,000 nodes, 123,201
 // edges) took 1.21 ms on the vector units, with every layer's inputs written
 // out for its weight gradient, and takes 0.19.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -37,7 +38,7 @@
 
 namespace sfg {
 
-void spmm_rownorm(const sfg_csr *H, int32_t k, sfg_dtype t, const void *x, void *y, hipStream_t s);
+void spmm_rownorm_f32(const sfg_csr *H, int32_t k, const float *x, float *y, hipStream_t s);
 size_t csr_workspace_bytes(int64_t n, int64_t m);
 void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
                const uint8_t *mask, int32_t *rowptr, int32_t *col, void *val, int32_t *eid, void *deg, void *ws,
@@ -187,137 +188,440 @@ __global__ void k_edge_feat(int64_t ne, const int32_t *__restrict__ cand, const 
 
 // ------------------------------------------------------------------ inference on the matrix cores
 //
-// v_mfma_f32_32x32x8_bf16 (one 32 x 32 x 8 block per wavefront), lane l:
-//   A (32 x 8):  row l % 32, columns 4 * (l / 32) + 0..3
-//   B (8 x 32):  column l % 32, rows 4 * (l / 32) + 0..3
-//   D (32 x 32): column l % 32, rows 8 * (r / 4) + 4 * (l / 32) + r % 4, r = 0..15
+// A wavefront takes 16 nodes or edges; lane l works for item l % 16 as its
+// quarter q = l / 16.  Products are formed transposed (hidden x item), so that
+// a lane ends up with runs of four hidden values of its own item:
+//   v_mfma_f32_16x16x32_bf16: A (16 x 32): row l % 16, columns 8 q + 0..7
+//                             B (32 x 16): column l % 16, rows 8 q + 0..7
+//   v_mfma_f32_16x16x16_bf16: the same with 4 q + 0..3
+//   D (16 x 16): column l % 16, rows 4 q + 0..3
+// with the weights as A (two blocks of 16 hidden values), which a wavefront
+// keeps in registers over all its tiles, and the items' values as B.  The
+// layers' products run in the order of the inputs with the bias last: what
+// they leave is rounded to BF16, and a sum in another order rounds some of it
+// to the other side.
+//
+// The aggregation is part of the layer: the four lanes of a node gather the
+// eight columns of its neighbours' rows that their quarter of B needs, where a
+// sweep of its own wrote the aggregate and the layer read it back.  The layers
+// are bound by memory and as much by the vector units (conversions, addresses,
+// the aggregate's divisions), all three by latency until a wavefront loaded
+// its next tiles ahead.  On the 128^3 mesh (2.1 million nodes, 12.5 million
+// entries, 4.2 million edges; floors at the rate of a large copy): layer 1 90
+// (sweep) + 48 -> 76 us (58), layer 2 150 + 116 -> 118 us (71), head 182 ->
+// 90 us (51).
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bfx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bfx8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ short bf16_bits(float x) {
-    const __hip_bfloat16 b = cvt<__hip_bfloat16>(x);
-    short r;
-    __builtin_memcpy(&r, &b, sizeof(r));
+// two values rounded to BF16, the first in the low half
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const bfx2 r = __builtin_convertvector((f32x2){a, b}, bfx2);
+    uint32_t o;
+    __builtin_memcpy(&o, &r, sizeof(o));
+    return o;
+}
+
+__device__ __forceinline__ bfx8 operand8(const uint32_t (&w)[4]) {
+    bfx8 r;
+    __builtin_memcpy(&r, w, sizeof(r));
     return r;
 }
 
-__device__ __forceinline__ float bits_float(short r) {
-    __hip_bfloat16 b;
-    __builtin_memcpy(&b, &r, sizeof(r));
-    return cvt<float>(b);
+__device__ __forceinline__ bf16x4 operand4(uint32_t a, uint32_t b) {
+    const uint32_t w[2] = {a, b};
+    bf16x4 r;
+    __builtin_memcpy(&r, w, sizeof(r));
+    return r;
 }
 
-// four consecutive values as BF16 operand bits
-__device__ __forceinline__ bf16x4 load4(const float *p) {
-    const float4 f = *reinterpret_cast<const float4 *>(p);
-    return bf16x4{bf16_bits(f.x), bf16_bits(f.y), bf16_bits(f.z), bf16_bits(f.w)};
-}
-__device__ __forceinline__ bf16x4 load4(const __hip_bfloat16 *p) {
-    return *reinterpret_cast<const bf16x4 *>(p);
+// eight BF16 values of a row (16 bytes) to FP32
+__device__ __forceinline__ void unpack8(const uint4 &r, float (&f)[8]) {
+    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f[2 * i] = __uint_as_float(w[i] << 16);
+        f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
 }
 
-// B operands of a (rows x 32) FP32 weight block, K padded with zeros
-template <int NCH>
-__device__ __forceinline__ void load_weights(const float *__restrict__ W, int rows, int half, int col,
-                                             bf16x4 (&wb)[NCH]) {
+// Rows 4 q .. 4 q + 3 from r0 of a (rows x 32) FP32 weight block, hidden value
+// 16 b + l % 16, as two words of an A operand
+__device__ __forceinline__ void weights4(const float *__restrict__ W, int r0, int q, int b, int c, uint32_t *w) {
+    const float *at = W + (r0 + 4 * q) * kH + 16 * b + c;
+    w[0] = pack2(at[0], at[kH]);
+    w[1] = pack2(at[2 * kH], at[3 * kH]);
+}
+
+// [b][r] = v[16 b + 4 q + r]: a lane's hidden values
+__device__ __forceinline__ void hidden8(const float *__restrict__ v, int q, f32x4 (&o)[2]) {
 #pragma unroll
-    for (int t = 0; t < NCH; ++t) {
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 8 * t + 4 * half + i;
-            wb[t][i] = bf16_bits(k < rows ? W[k * kH + col] : 0.f);
+        for (int r = 0; r < 4; ++r) o[b][r] = v[16 * b + 4 * q + r];
+}
+
+// h[node] = relu(acc): hidden value 16 b + 4 q + r lies at 8 q + 4 b + r of its
+// row, so that a lane stores, and gathers, 16 bytes.
+__device__ __forceinline__ void store_relu(const f32x4 (&acc)[2], int q, __hip_bfloat16 *__restrict__ hrow) {
+    uint4 o;
+    o.x = pack2(fmaxf(acc[0][0], 0.f), fmaxf(acc[0][1], 0.f));
+    o.y = pack2(fmaxf(acc[0][2], 0.f), fmaxf(acc[0][3], 0.f));
+    o.z = pack2(fmaxf(acc[1][0], 0.f), fmaxf(acc[1][1], 0.f));
+    o.w = pack2(fmaxf(acc[1][2], 0.f), fmaxf(acc[1][3], 0.f));
+    *reinterpret_cast<uint4 *>(hrow + 8 * q) = o;
+}
+
+// The bias as one more row of the product, after the others: the first of
+// quarter 0's four, whose item value is 1
+__device__ __forceinline__ bf16x4 bias_row(float v, int q) { return operand4(q == 0 ? pack2(v, 0.f) : 0u, 0u); }
+
+// Wavefronts per SIMD, and so workgroups per CU, that the kernels below are
+// compiled for; the grid is that many workgroups on every CU and no more, so
+// that the weights are loaded once, all workgroups run from start to end and
+// neighbouring tiles stay close in time (the head with 5 workgroups per CU
+// took 96 us, with 6 89; with 5.5, its last ones alone at the end, 147).  One
+// wavefront more than here spills.
+constexpr int kLayerWaves(int U) { return U <= 4 ? 5 : (U <= 6 ? 4 : 3); }
+constexpr int kHeadWaves = 6;
+
+inline uint32_t tile_grid(uint32_t nvb, int waves) { return std::min(nvb, 256u * (uint32_t)waves); }
+
+// One row of the graph on its way through a wavefront's tiles: its extent is
+// loaded two tiles ahead, its first U entries one tile ahead, so that only the
+// gathered rows themselves are waited for.
+template <int U>
+struct RowAhead {
+    int32_t j0, j1, c[U];
+    float w[U], d;
+
+    __device__ __forceinline__ void extent(int64_t p, const int32_t *__restrict__ rowptr) {
+        j0 = rowptr[p];
+        j1 = rowptr[p + 1];
+    }
+    // A short row's U entries run into the next rows' (valid, and masked where
+    // they are used); only the graph's last rows are clamped.
+    __device__ __forceinline__ void entries(int64_t p, int32_t nnz, const int32_t *__restrict__ col,
+                                            const float *__restrict__ val, const float *__restrict__ deg) {
+        d = deg[p];
+        if (j0 + U <= nnz) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                c[i] = col[j0 + i];
+                w[i] = val[j0 + i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                c[i] = j0 + i < nnz ? col[j0 + i] : (int32_t)p;
+                w[i] = j0 + i < nnz ? val[j0 + i] : 0.f;
+            }
         }
     }
-}
 
-// h = relu([x | a | 1] W) for 32 nodes per wavefront; BF16 output.
-template <typename TIN, int FIN>
-__global__ __launch_bounds__(256) void k_dense_mfma(int64_t n, const TIN *__restrict__ x, const TIN *__restrict__ a,
-                                                    const float *__restrict__ W, __hip_bfloat16 *__restrict__ h) {
-    static_assert(FIN % 8 == 0, "feature width must be a multiple of 8");
-    constexpr int NX = FIN / 8, NCH = 2 * NX + 1;
-    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-    bf16x4 wb[NCH];
-    load_weights<NCH>(W, 2 * FIN + 1, half, col, wb);
-    const int64_t base = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-    if (base >= n) return;
-    const int64_t row = base + col;
-    const bool valid = row < n;
-    const bf16x4 zero = {0, 0, 0, 0};
-    f32x16 acc = {};
+    // every lane's row has at least U entries: no masks
+    __device__ __forceinline__ bool full() const { return __all(j1 - j0 >= U); }
+};
+
+// acc[i] += w x[i] over entries j0 + U, j0 + U + 1, ... of a row, U in flight
+template <int V, int U, typename LOAD>
+__device__ __forceinline__ void gather_rest(int32_t j0, int32_t j1, const int32_t *__restrict__ col,
+                                            const float *__restrict__ val, LOAD load, float (&acc)[V]) {
+    for (int32_t j = j0 + U; j < j1; j += U) {
+        int32_t cj[U];
+        float wj[U], xv[U][V];
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
-        const bf16x4 av = valid ? load4(x + row * FIN + 8 * t + 4 * half) : zero;
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, wb[t], acc, 0, 0, 0);
-    }
+        for (int i = 0; i < U; ++i) {
+            const int32_t jj = j + i < j1 ? j + i : j1 - 1;
+            cj[i] = col[jj];
+            wj[i] = val[jj];
+        }
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
-        const bf16x4 av = valid ? load4(a + row * FIN + 8 * t + 4 * half) : zero;
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, wb[NX + t], acc, 0, 0, 0);
-    }
-    {   // the bias column: k = 2 FIN
-        const bf16x4 av = (valid && half == 0) ? bf16x4{bf16_bits(1.f), 0, 0, 0} : zero;
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(av, wb[2 * NX], acc, 0, 0, 0);
-    }
+        for (int i = 0; i < U; ++i) load(cj[i], xv[i]);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t node = base + 8 * (r / 4) + 4 * half + (r % 4);
-        if (node < n) h[node * kH + col] = cvt<__hip_bfloat16>(fmaxf(acc[r], 0.f));
+        for (int i = 0; i < U; ++i)
+            if (j + i < j1) {
+#pragma unroll
+                for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(wj[i], xv[i][c], acc[c]);
+            }
     }
 }
 
-// yhat_e = relu(z_e W3) . w4[0:32] + w4[32] for 32 candidate edges per wavefront.
-__global__ __launch_bounds__(256) void k_head_mfma(int64_t ne, const int32_t *__restrict__ cand,
+// a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1.  One IEEE
+// reciprocal for all eight columns: with r = 1 / d and q = acc r both rounded
+// to nearest, q + r (acc - q d) is the rounded quotient (Markstein) as long as
+// nothing over- or underflows on the way; other rows divide.
+__device__ __forceinline__ void row_mean(const float (&acc)[8], const float (&self)[8], float d, float (&a)[8]) {
+    float m = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) m = fmaxf(m, fabsf(acc[t]));
+    float s = 0.f;      // NaN passes fmaxf by
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s += acc[t];
+    const float big = 0x1p60f;
+    if (__all(m < big && s == s && d > 1.f / big && d < big)) {
+        const float r = 1.f / d;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const float q = acc[t] * r;
+            a[t] = __builtin_fmaf(__builtin_fmaf(-q, d, acc[t]), r, q) + 0.f * self[t];
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) a[t] = acc[t] / d + 0.f * self[t];
+    }
+}
+
+// h1 = relu([x | D^-1 A x | 1] W1).  A wavefront takes 64 nodes, one per lane
+// (a row of x is 32 bytes), and turns their [x | a] rows through LDS into the
+// operands of four tiles.
+template <int U>
+__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, uint32_t nvb, uint32_t chunk,
+                                                     const int32_t *__restrict__ rowptr,
+                                                     const int32_t *__restrict__ col, const float *__restrict__ val,
+                                                     const float *__restrict__ deg, const float *__restrict__ x,
+                                                     const float *__restrict__ W, __hip_bfloat16 *__restrict__ h) {
+    static_assert(kF == 8, "[x | a] is one product of 16");
+    __shared__ uint32_t turn[4][64][10];      // 40-byte rows: 8-byte aligned, spread over the banks
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15, wv = threadIdx.x >> 6;
+    bf16x4 wa[2], wb[2];
+    const bf16x4 one = bias_row(1.f, q);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        uint32_t w[2];
+        weights4(W, 0, q, b, c, w);
+        wa[b] = operand4(w[0], w[1]);
+        wb[b] = bias_row(W[2 * kF * kH + 16 * b + c], q);
+    }
+    auto load = [&](int64_t row, float (&o)[8]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = x[row * kF + i];
+    };
+    auto first = [&](uint32_t vb) { return ((int64_t)xcd_remap_chunked(vb, nvb, chunk) * 4 + wv) * 64; };
+    auto row_of = [&](uint32_t vb) {
+        const int64_t p = (vb < nvb ? first(vb) : 0) + lane;
+        return p < n ? p : n - 1;
+    };
+    RowAhead<U> cur, nxt;
+    int64_t p = row_of(blockIdx.x), pn = row_of(blockIdx.x + gridDim.x);
+    const int32_t nnz = rowptr[n];
+    cur.extent(p, rowptr);
+    nxt.extent(pn, rowptr);
+    cur.entries(p, nnz, col, val, deg);
+    for (uint32_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
+        float self[8], xv[U][8], acc[8];
+        load(p, self);
+#pragma unroll
+        for (int i = 0; i < U; ++i) load(cur.c[i], xv[i]);
+        nxt.entries(pn, nnz, col, val, deg);
+        RowAhead<U> after;
+        const int64_t pa = row_of(vb + 2 * gridDim.x);
+        after.extent(pa, rowptr);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = 0.f;
+        auto add = [&](int i) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] = __builtin_fmaf(cur.w[i], xv[i][t], acc[t]);
+        };
+        if (cur.full()) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) add(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (cur.j0 + i < cur.j1) add(i);
+        }
+        gather_rest<8, U>(cur.j0, cur.j1, col, val, load, acc);
+        float a[8];
+        row_mean(acc, self, cur.d, a);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            turn[wv][lane][t] = pack2(self[2 * t], self[2 * t + 1]);
+            turn[wv][lane][4 + t] = pack2(a[2 * t], a[2 * t + 1]);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t base = first(vb);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int64_t node = base + 16 * g + c;
+            const uint32_t *t = turn[wv][16 * g + c];
+            const bf16x4 bv = operand4(t[2 * q], t[2 * q + 1]);
+            f32x4 out[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[b], bv, f32x4{}, 0, 0, 0);
+                out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb[b], one, out[b], 0, 0, 0);
+            }
+            if (node < n) store_relu(out, q, h + node * kH);
+        }
+        __builtin_amdgcn_wave_barrier();
+        cur = nxt;
+        nxt = after;
+        p = pn;
+        pn = pa;
+    }
+}
+
+// h2 = relu([h1 | D^-1 A h1 | 1] W2): lane quarter q holds columns 4q .. 4q + 3
+// and 16 + 4q .. 16 + 4q + 3.
+template <int U>
+__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, uint32_t nvb, uint32_t chunk,
+                                                     const int32_t *__restrict__ rowptr,
+                                                     const int32_t *__restrict__ col, const float *__restrict__ val,
+                                                     const float *__restrict__ deg,
+                                                     const __hip_bfloat16 *__restrict__ h1,
+                                                     const float *__restrict__ W, __hip_bfloat16 *__restrict__ h2) {
+    static_assert(kH == 32, "eight columns per lane");
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15, wv = threadIdx.x >> 6;
+    bf16x4 wa[4][2], wb[2];      // rows 16 t .. 16 t + 15 of W2: two of h1, two of the aggregate
+    const bf16x4 one = bias_row(1.f, q);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t w[2];
+            weights4(W, 16 * t, q, b, c, w);
+            wa[t][b] = operand4(w[0], w[1]);
+        }
+        wb[b] = bias_row(W[2 * kH * kH + 16 * b + c], q);
+    }
+    auto raw = [&](int64_t row) { return *reinterpret_cast<const uint4 *>(h1 + row * kH + 8 * q); };
+    auto load = [&](int64_t row, float (&o)[8]) { unpack8(raw(row), o); };
+    auto first = [&](uint32_t vb) { return ((int64_t)xcd_remap_chunked(vb, nvb, chunk) * 4 + wv) * 16; };
+    auto row_of = [&](uint32_t vb) {
+        const int64_t p = (vb < nvb ? first(vb) : 0) + c;
+        return p < n ? p : n - 1;
+    };
+    RowAhead<U> cur, nxt;
+    int64_t p = row_of(blockIdx.x), pn = row_of(blockIdx.x + gridDim.x);
+    const int32_t nnz = rowptr[n];
+    cur.extent(p, rowptr);
+    nxt.extent(pn, rowptr);
+    cur.entries(p, nnz, col, val, deg);
+    for (uint32_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
+        uint4 xr[U];
+        const uint4 own = raw(p);
+#pragma unroll
+        for (int i = 0; i < U; ++i) xr[i] = raw(cur.c[i]);
+        nxt.entries(pn, nnz, col, val, deg);
+        RowAhead<U> after;
+        const int64_t pa = row_of(vb + 2 * gridDim.x);
+        after.extent(pa, rowptr);
+        float self[8], acc[8], a[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = 0.f;
+        auto add = [&](int i) {
+            float xv[8];
+            unpack8(xr[i], xv);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] = __builtin_fmaf(cur.w[i], xv[t], acc[t]);
+        };
+        if (cur.full()) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) add(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (cur.j0 + i < cur.j1) add(i);
+        }
+        gather_rest<8, U>(cur.j0, cur.j1, col, val, load, acc);
+        unpack8(own, self);
+        row_mean(acc, self, cur.d, a);
+        const bf16x4 item[4] = {operand4(own.x, own.y), operand4(own.z, own.w),
+                                operand4(pack2(a[0], a[1]), pack2(a[2], a[3])),
+                                operand4(pack2(a[4], a[5]), pack2(a[6], a[7]))};
+        f32x4 out[2] = {};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[t][b], item[t], out[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb[b], one, out[b], 0, 0, 0);
+        const int64_t node = first(vb) + c;
+        if (node < n) store_relu(out, q, h2 + node * kH);
+        cur = nxt;
+        nxt = after;
+        p = pn;
+        pn = pa;
+    }
+}
+
+// yhat_e = relu(z_e W3) . w4[0:32] + w4[32]; lane quarter q holds eight columns
+// of |hp - hq| and of hp * hq (as k_layer2_mfma left them) and edge feature q.
+// Candidates are loaded two tiles ahead, their ends one tile ahead.  All of an
+// accumulator's products have one shape: with the edge features' as a
+// 16x16x16 after the 16x16x32 ones the sums came out wrong.
+__global__ __launch_bounds__(256, kHeadWaves) void k_head_mfma(int64_t ne, uint32_t nvb, const int32_t *__restrict__ cand,
                                                    const int32_t *__restrict__ u, const int32_t *__restrict__ v,
                                                    const __hip_bfloat16 *__restrict__ h,
                                                    const float *__restrict__ ef, const float *__restrict__ W3,
                                                    const float *__restrict__ w4, float *__restrict__ pred) {
-    constexpr int NCH = (kZ1 + 7) / 8;      // 9: |hp - hq| (4), hp * hq (4), edge features + bias (1)
-    static_assert(kH == 32 && kE == 4 && NCH == 9, "head layout");
-    __shared__ float red[4][32][33];
-    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, wv = threadIdx.x >> 6;
-    bf16x4 wb[NCH];
-    load_weights<NCH>(W3, kZ1, half, col, wb);
-    const float w4c = w4[col];
-    const int64_t base = ((int64_t)blockIdx.x * 4 + wv) * 32;
-    if (base >= ne) return;
-    const int64_t i = base + col;
-    const bool valid = i < ne;
-    const int32_t e = valid ? (cand ? cand[i] : (int32_t)i) : 0;
-    const __hip_bfloat16 *hp = h + (int64_t)(valid ? u[e] : 0) * kH;
-    const __hip_bfloat16 *hq = h + (int64_t)(valid ? v[e] : 0) * kH;
-    const bf16x4 zero = {0, 0, 0, 0};
-    f32x16 acc = {};
+    static_assert(kH == 32 && kE == 4, "head layout");
+    const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15, wv = threadIdx.x >> 6;
+    bfx8 wd[2], wp[2], we[2];
+    f32x4 bias[2], last[2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        bf16x4 d = zero, p = zero;
-        if (valid) {
-            const bf16x4 ra = load4(hp + 8 * t + 4 * half), rb = load4(hq + 8 * t + 4 * half);
+    for (int b = 0; b < 2; ++b) {
+        uint32_t w[4];
+        weights4(W3, 0, q, b, c, w);
+        weights4(W3, 16, q, b, c, w + 2);
+        wd[b] = operand8(w);
+        weights4(W3, kH, q, b, c, w);
+        weights4(W3, kH + 16, q, b, c, w + 2);
+        wp[b] = operand8(w);
+        const uint32_t f[4] = {pack2(W3[(2 * kH + q) * kH + 16 * b + c], 0.f), 0u, 0u, 0u};
+        we[b] = operand8(f);
+    }
+    hidden8(W3 + kZ * kH, q, bias);
+    hidden8(w4, q, last);
+    const float w0 = w4[kH];
+    auto item = [&](uint32_t vb) {
+        const int64_t i = (vb < nvb ? ((int64_t)xcd_remap(vb, nvb) * 4 + wv) * 16 : 0) + c;
+        return i < ne ? i : ne - 1;
+    };
+    auto edge = [&](int64_t i) { return cand ? cand[i] : (int32_t)i; };
+    int64_t in = item(blockIdx.x + gridDim.x);
+    int32_t e = edge(item(blockIdx.x)), en = edge(in);
+    int32_t pu = u[e], pv = v[e];
+    float f = ef[item(blockIdx.x) * kE + q];
+    for (uint32_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
+        const uint4 rp = *reinterpret_cast<const uint4 *>(h + (int64_t)pu * kH + 8 * q);
+        const uint4 rq = *reinterpret_cast<const uint4 *>(h + (int64_t)pv * kH + 8 * q);
+        const int32_t nu = u[en], nv = v[en];
+        const float nf = ef[in * kE + q];
+        in = item(vb + 2 * gridDim.x);
+        en = edge(in);
+        float hp[8], hq[8];
+        unpack8(rp, hp);
+        unpack8(rq, hq);
+        uint32_t dw[4], pw[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float fa = bits_float(ra[q]), fb = bits_float(rb[q]);
-                d[q] = bf16_bits(fabsf(fa - fb));
-                p[q] = bf16_bits(fa * fb);
-            }
+        for (int t = 0; t < 4; ++t) {
+            dw[t] = pack2(hp[2 * t] - hq[2 * t], hp[2 * t + 1] - hq[2 * t + 1]) & 0x7fff7fffu;
+            pw[t] = pack2(hp[2 * t] * hq[2 * t], hp[2 * t + 1] * hq[2 * t + 1]);
         }
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(d, wb[t], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(p, wb[4 + t], acc, 0, 0, 0);
-    }
-    {   // k = 64..67 edge features (lanes of the first half), k = 68 bias
-        bf16x4 z = zero;
-        if (valid) z = half == 0 ? load4(ef + i * kE) : bf16x4{bf16_bits(1.f), 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(z, wb[8], acc, 0, 0, 0);
-    }
-    // the last layer: each lane scales its column, then lane m < 32 adds row m
-    // in column order
+        const uint32_t ew[4] = {pack2(f, 0.f), 0u, 0u, 0u};
+        const bfx8 bd = operand8(dw), bp = operand8(pw), be = operand8(ew);
+        float o = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wv][8 * (r / 4) + 4 * half + (r % 4)][col] = fmaxf(acc[r], 0.f) * w4c;
-    __builtin_amdgcn_wave_barrier();
-    if (half == 0 && valid) {
-        float o = w4[kH];
-        for (int j = 0; j < kH; ++j) o += red[wv][col][j];
-        pred[i] = o;
+        for (int b = 0; b < 2; ++b) {
+            f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wd[b], bd, bias[b], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[b], bp, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(we[b], be, acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o = __builtin_fmaf(fmaxf(acc[r], 0.f), last[b][r], o);
+        }
+        o += __shfl_xor(o, 16);
+        o += __shfl_xor(o, 32);
+        const int64_t i = ((int64_t)xcd_remap(vb, nvb) * 4 + wv) * 16 + c;
+        if (i < ne && q == 0) pred[i] = o + w0;
+        pu = nu;
+        pv = nv;
+        f = nf;
     }
 }
 
@@ -889,35 +1193,47 @@ extern "C" sfg_status sfg_mpnn_forward(const sfg_csr *G, const float *params, co
         Carver c(ws);
         FwdPlan p = plan_fwd(c, n, act);
         const dim3 b(256);
-        // layer 1 (FP32 input features; the aggregate reuses p.a)
-        float *a1 = (float *)p.a;
-        spmm_rownorm(G, kF, SFG_F32, node_feat, a1, s);
-        if (act == SFG_F32)
-            hipLaunchKernelGGL(k_dense_f32<kF>, dim3(grid_for(n, 128)), b, 0, s, n, node_feat, a1, params + kOffW1,
-                               (float *)p.h1);
-        else
-            hipLaunchKernelGGL((k_dense_mfma<float, kF>), dim3(grid_for(n, 128)), b, 0, s, n, node_feat, a1,
-                               params + kOffW1, (__hip_bfloat16 *)p.h1);
-        SFG_LAUNCH_CHECK();
-        // layer 2
-        spmm_rownorm(G, kH, act, p.h1, p.a, s);
-        if (act == SFG_F32)
-            hipLaunchKernelGGL(k_dense_f32<kH>, dim3(grid_for(n, 128)), b, 0, s, n, (const float *)p.h1,
-                               (const float *)p.a, params + kOffW2, (float *)p.h2);
-        else
-            hipLaunchKernelGGL((k_dense_mfma<__hip_bfloat16, kH>), dim3(grid_for(n, 128)), b, 0, s, n,
-                               (const __hip_bfloat16 *)p.h1, (const __hip_bfloat16 *)p.a, params + kOffW2,
-                               (__hip_bfloat16 *)p.h2);
-        SFG_LAUNCH_CHECK();
+        if (act == SFG_F32) {
+            float *a = (float *)p.a, *h1 = (float *)p.h1, *h2 = (float *)p.h2;
+            spmm_rownorm_f32(G, kF, node_feat, a, s);
+            hipLaunchKernelGGL(k_dense_f32<kF>, dim3(grid_for(n, 128)), b, 0, s, n, node_feat, a, params + kOffW1, h1);
+            SFG_LAUNCH_CHECK();
+            spmm_rownorm_f32(G, kH, h1, a, s);
+            hipLaunchKernelGGL(k_dense_f32<kH>, dim3(grid_for(n, 128)), b, 0, s, n, h1, a, params + kOffW2, h2);
+            SFG_LAUNCH_CHECK();
+        } else {
+            __hip_bfloat16 *h1 = (__hip_bfloat16 *)p.h1, *h2 = (__hip_bfloat16 *)p.h2;
+            // the first U entries of a row are in flight together: the average row of a lattice (6), 4 below, 8 above;
+            // the XCDs' shares are the sweep's
+            const uint32_t chunk = G->nnz >= 8 * n ? 64u : 0u;
+            auto layers = [&](auto ut) {
+                constexpr int U = decltype(ut)::value;
+                const uint32_t nb1 = grid_for(n, 256), nb2 = grid_for(n, 64);
+                hipLaunchKernelGGL(k_layer1_mfma<U>, dim3(tile_grid(nb1, kLayerWaves(U))), b, 0, s, n, nb1, chunk, G->rowptr, G->col,
+                                   (const float *)G->val, (const float *)G->deg, node_feat, params + kOffW1, h1);
+                SFG_LAUNCH_CHECK();
+                hipLaunchKernelGGL(k_layer2_mfma<U>, dim3(tile_grid(nb2, kLayerWaves(U))), b, 0, s, n, nb2, chunk, G->rowptr, G->col,
+                                   (const float *)G->val, (const float *)G->deg, h1, params + kOffW2, h2);
+                SFG_LAUNCH_CHECK();
+            };
+            if (G->nnz <= 4 * n)
+                layers(std::integral_constant<int, 4>());
+            else if (G->nnz <= 6 * n)
+                layers(std::integral_constant<int, 6>());
+            else
+                layers(std::integral_constant<int, 8>());
+        }
         if (ne == 0) return;
         SFG_REQUIRE(u && v && edge_feat && pred, SFG_EINVAL, "mpnn_forward: null pointer");
-        if (act == SFG_F32)
+        if (act == SFG_F32) {
             hipLaunchKernelGGL(k_head_f32<false>, dim3(grid_for(ne, 128)), b, 0, s, ne, cand, u, v,
                                (const float *)p.h2, edge_feat, params + kOffW3, params + kOffW4, pred, nullptr, 0.f,
                                nullptr, nullptr, nullptr);
-        else
-            hipLaunchKernelGGL(k_head_mfma, dim3(grid_for(ne, 128)), b, 0, s, ne, cand, u, v,
+        } else {
+            const uint32_t nvb = grid_for(ne, 64);
+            hipLaunchKernelGGL(k_head_mfma, dim3(tile_grid(nvb, kHeadWaves)), b, 0, s, ne, nvb, cand, u, v,
                                (const __hip_bfloat16 *)p.h2, edge_feat, params + kOffW3, params + kOffW4, pred);
+        }
         SFG_LAUNCH_CHECK();
     });
 }
@@ -940,10 +1256,10 @@ extern "C" sfg_status sfg_mpnn_loss_grad(const sfg_csr *G, const float *params, 
         TrainPlan p = plan_train(c, n, ne);
         const dim3 gn(grid_for(n, 256)), ge(grid_for(ne, 256)), b(256);
         // ---- forward
-        spmm_rownorm(G, kF, SFG_F32, node_feat, p.a1, s);
+        spmm_rownorm_f32(G, kF, node_feat, p.a1, s);
         hipLaunchKernelGGL(k_dense_f32<kF>, dim3(grid_for(n, 128)), b, 0, s, n, node_feat, p.a1, params + kOffW1, p.h1);
         SFG_LAUNCH_CHECK();
-        spmm_rownorm(G, kH, SFG_F32, p.h1, p.a2, s);
+        spmm_rownorm_f32(G, kH, p.h1, p.a2, s);
         hipLaunchKernelGGL(k_dense_f32<kH>, dim3(grid_for(n, 128)), b, 0, s, n, p.h1, p.a2, params + kOffW2, p.h2);
         SFG_LAUNCH_CHECK();
         // ---- edge head, forward and backward
@@ -968,7 +1284,7 @@ extern "C" sfg_status sfg_mpnn_loss_grad(const sfg_csr *G, const float *params, 
         SFG_LAUNCH_CHECK();
         sfg_csr Gu = *G;
         Gu.deg = p.ones_n;
-        spmm_rownorm(&Gu, kH, SFG_F32, p.t2, p.c2, s);
+        spmm_rownorm_f32(&Gu, kH, p.t2, p.c2, s);
         // ---- layer 1, and the sums over the partials
         hipLaunchKernelGGL((k_dense_grad<kF, false>), dim3(nbn), b, 0, s, n, node_feat, p.a1, p.t1, p.c2, p.h1,
                            params + kOffW1, nullptr, nullptr, nullptr, p.part1);
