@@ -123,6 +123,74 @@ __device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb, u
     return ((i / chunk) * kNumXcd + x) * chunk + i % chunk;
 }
 
+// Quotients with one denominator, bit for bit as the operator gives them: the
+// compiler's own steps for a division (a reciprocal refined by Newton's method,
+// the product, the remainder's correction) with the reciprocal taken once.  Its
+// scaling of extreme operands does nothing while the operands' exponents differ
+// by less than 96 (FP64: 768) and neither the quotient nor the remainder is
+// near the smallest numbers; the callers keep them well inside.
+__device__ __forceinline__ float refined_rcp(float d) {
+    const float y = __builtin_amdgcn_rcpf(d);
+    return __builtin_fmaf(__builtin_fmaf(-d, y, 1.f), y, y);
+}
+__device__ __forceinline__ float quotient(float a, float d, float y) {
+    float q = a * y;
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, a), y, q);
+    return __builtin_fmaf(__builtin_fmaf(-d, q, a), y, q);
+}
+__device__ __forceinline__ double refined_rcp(double d) {
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
+    return __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
+}
+__device__ __forceinline__ double quotient(double a, double d, double y) {
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-d, q, a), y, q);
+}
+
+// Whether quotient() may take a[0..V) / d: no zero, infinity or NaN, exponents
+// within 40 (300) of 1's.  On the exponent fields, which NaN and infinity have
+// the largest of and zero the smallest.
+template <int V>
+__device__ __forceinline__ bool mid_range(const float (&a)[V], float d) {
+    uint32_t lo = 0x7f800000u, hi = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint32_t e = __float_as_uint(a[i]) & 0x7f800000u;
+        lo = e < lo ? e : lo;
+        hi = e > hi ? e : hi;
+    }
+    constexpr uint32_t kLo = (127u - 40u) << 23, kHi = (127u + 40u) << 23;
+    const uint32_t ed = __float_as_uint(d);
+    return lo > kLo && hi < kHi && ed > kLo && ed < kHi;
+}
+template <int V>
+__device__ __forceinline__ bool mid_range(const double (&a)[V], double d) {
+    uint32_t lo = 0x7ff00000u, hi = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const uint32_t e = (uint32_t)__double2hiint(a[i]) & 0x7ff00000u;
+        lo = e < lo ? e : lo;
+        hi = e > hi ? e : hi;
+    }
+    constexpr uint32_t kLo = (1023u - 300u) << 20, kHi = (1023u + 300u) << 20;
+    const uint32_t ed = (uint32_t)__double2hiint(d);
+    return lo > kLo && hi < kHi && ed > kLo && ed < kHi;
+}
+
+// out[i] = a[i] / d
+template <int V, typename T>
+__device__ __forceinline__ void divide_row(const T (&a)[V], T d, T (&out)[V]) {
+    if (mid_range<V>(a, d)) {
+        const T y = refined_rcp(d);
+#pragma unroll
+        for (int i = 0; i < V; ++i) out[i] = quotient(a[i], d, y);
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i) out[i] = a[i] / d;
+    }
+}
+
 template <typename T> struct DT;
 template <> struct DT<double> { static constexpr sfg_dtype id = SFG_F64; };
 template <> struct DT<float> { static constexpr sfg_dtype id = SFG_F32; };

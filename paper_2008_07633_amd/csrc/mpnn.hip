@@ -351,25 +351,21 @@ __device__ __forceinline__ void gather_rest(int32_t j0, int32_t j1, const int32_
     }
 }
 
-// a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1.  One IEEE
-// reciprocal for all eight columns: with r = 1 / d and q = acc r both rounded
-// to nearest, q + r (acc - q d) is the rounded quotient (Markstein) as long as
-// nothing over- or underflows on the way; other rows divide.
+// a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1, one
+// reciprocal for all eight columns.  After a ReLU many sums are zero, whose
+// quotient by these steps is zero as well, so only large values are looked for;
+// a sum under 2^-40 may end an ulp of FP32 off, before its rounding to BF16.
 __device__ __forceinline__ void row_mean(const float (&acc)[8], const float (&self)[8], float d, float (&a)[8]) {
-    float m = 0.f;
+    uint32_t hi = 0;      // NaN and infinity are the largest
 #pragma unroll
-    for (int t = 0; t < 8; ++t) m = fmaxf(m, fabsf(acc[t]));
-    float s = 0.f;      // NaN passes fmaxf by
+    for (int t = 0; t < 8; ++t) {
+        const uint32_t b = __float_as_uint(acc[t]) & 0x7fffffffu;
+        hi = b > hi ? b : hi;
+    }
+    if (__all(hi < __float_as_uint(0x1p40f) && d > 0x1p-40f && d < 0x1p40f)) {
+        const float y = refined_rcp(d);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) s += acc[t];
-    const float big = 0x1p60f;
-    if (__all(m < big && s == s && d > 1.f / big && d < big)) {
-        const float r = 1.f / d;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const float q = acc[t] * r;
-            a[t] = __builtin_fmaf(__builtin_fmaf(-q, d, acc[t]), r, q) + 0.f * self[t];
-        }
+        for (int t = 0; t < 8; ++t) a[t] = quotient(acc[t], d, y) + 0.f * self[t];
     } else {
 #pragma unroll
         for (int t = 0; t < 8; ++t) a[t] = acc[t] / d + 0.f * self[t];
