@@ -308,7 +308,7 @@ struct RowAhead {
     __device__ __forceinline__ void entries(int64_t p, int32_t nnz, const int32_t *__restrict__ col,
                                             const float *__restrict__ val, const float *__restrict__ deg) {
         d = deg[p];
-        if (j0 + U <= nnz) {
+        if (nnz - j0 >= U) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 c[i] = col[j0 + i];
@@ -317,8 +317,8 @@ struct RowAhead {
         } else {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
-                c[i] = j0 + i < nnz ? col[j0 + i] : (int32_t)p;
-                w[i] = j0 + i < nnz ? val[j0 + i] : 0.f;
+                c[i] = i < nnz - j0 ? col[j0 + i] : (int32_t)p;
+                w[i] = i < nnz - j0 ? val[j0 + i] : 0.f;
             }
         }
     }
@@ -331,6 +331,7 @@ struct RowAhead {
 template <int V, int U, typename LOAD>
 __device__ __forceinline__ void gather_rest(int32_t j0, int32_t j1, const int32_t *__restrict__ col,
                                             const float *__restrict__ val, LOAD load, float (&acc)[V]) {
+    if (j1 - j0 <= U) return;
     for (int32_t j = j0 + U; j < j1; j += U) {
         int32_t cj[U];
         float wj[U], xv[U][V];
