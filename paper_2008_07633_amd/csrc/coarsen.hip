@@ -108,11 +108,11 @@ __global__ __launch_bounds__(256) void k_pointer_long(const int32_t *__restrict_
     const int32_t cnt = *long_cnt;
     for (int32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
         const int32_t p = long_rows[r];
-        const int32_t j0 = rowptr[p], j1 = rowptr[p + 1];
+        const uint32_t j0 = rowptr[p], j1 = rowptr[p + 1];     // unsigned: j steps over j1
         TA ba = TA(-1);
         TW bw = TW(0);
         int32_t bc = 0x7fffffff;
-        for (int32_t j = j0 + t; j < j1; j += 256) {
+        for (uint32_t j = j0 + t; j < j1; j += 256) {
             const TA a = aff[eid[j]];
             const TW w = val[j];
             const int32_t c = col[j];

@@ -573,9 +573,9 @@ __global__ __launch_bounds__(256) void k_degree_long(const int32_t *__restrict__
     const int32_t cnt = *long_cnt;
     for (int32_t r = blockIdx.x * 4 + wv; r < cnt; r += gridDim.x * 4) {
         const int32_t row = long_rows[r];
-        const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+        const uint32_t j0 = rowptr[row], j1 = rowptr[row + 1];     // unsigned: c steps over j1
         double d = 0.0;
-        for (int32_t c = j0; c < j1; c += kChunk) {
+        for (uint32_t c = j0; c < j1; c += kChunk) {
             const int32_t len = (j1 - c) < kChunk ? (j1 - c) : kChunk;
             // one wavefront runs in program order: the first lane reads what
             // all lanes wrote, and the next chunk is written after it is done

@@ -193,19 +193,21 @@ __global__ __launch_bounds__(kB) void k_cg_lap(int64_t n, int32_t k, const int32
             double a[V], self[V];
 #pragma unroll
             for (int q = 0; q < V; ++q) a[q] = 0.0;
-            const int32_t j0 = rowptr[p], e = rowptr[p + 1];
+            const int32_t j0 = rowptr[p], len = rowptr[p + 1] - j0;     // counted from the row's first entry: no wrap
+            const int32_t *cr = col + j0;
+            const double *vr = val + j0;
             entry(p, self);
-            for (int32_t j = j0; j < e; j += 4) {       // four neighbours in flight
+            for (int32_t j = 0; j < len; j += 4) {       // four neighbours in flight
                 double w[4], d[4][V];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int32_t at = j + i < e ? j + i : e - 1;
-                    w[i] = val[at];
-                    entry(col[at], d[i]);
+                    const int32_t at = j + i < len ? j + i : len - 1;
+                    w[i] = vr[at];
+                    entry(cr[at], d[i]);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (j + i < e) {
+                    if (j + i < len) {
 #pragma unroll
                         for (int q = 0; q < V; ++q) a[q] += w[i] * d[i][q];
                     }

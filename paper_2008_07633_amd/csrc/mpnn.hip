@@ -327,17 +327,19 @@ struct RowAhead {
     __device__ __forceinline__ bool full() const { return __all(j1 - j0 >= U); }
 };
 
-// acc[i] += w x[i] over entries j0 + U, j0 + U + 1, ... of a row, U in flight
+// acc[i] += w x[i] over entries U, U + 1, ... of a row of len entries (counted
+// from its first: at 2^31 - 2 entries the last rows' indices step over 2^31), U
+// in flight
 template <int V, int U, typename LOAD>
-__device__ __forceinline__ void gather_rest(int32_t j0, int32_t j1, const int32_t *__restrict__ col,
+__device__ __forceinline__ void gather_rest(int32_t len, const int32_t *__restrict__ col,
                                             const float *__restrict__ val, LOAD load, float (&acc)[V]) {
-    if (j1 - j0 <= U) return;
-    for (int32_t j = j0 + U; j < j1; j += U) {
+    if (len <= U) return;
+    for (int32_t j = U; j < len; j += U) {
         int32_t cj[U];
         float wj[U], xv[U][V];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const int32_t jj = j + i < j1 ? j + i : j1 - 1;
+            const int32_t jj = j + i < len ? j + i : len - 1;
             cj[i] = col[jj];
             wj[i] = val[jj];
         }
@@ -345,7 +347,7 @@ __device__ __forceinline__ void gather_rest(int32_t j0, int32_t j1, const int32_
         for (int i = 0; i < U; ++i) load(cj[i], xv[i]);
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            if (j + i < j1) {
+            if (j + i < len) {
 #pragma unroll
                 for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(wj[i], xv[i][c], acc[c]);
             }
@@ -430,9 +432,9 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
         } else {
 #pragma unroll
             for (int i = 0; i < U; ++i)
-                if (cur.j0 + i < cur.j1) add(i);
+                if (i < cur.j1 - cur.j0) add(i);
         }
-        gather_rest<8, U>(cur.j0, cur.j1, col, val, load, acc);
+        gather_rest<8, U>(cur.j1 - cur.j0, col + cur.j0, val + cur.j0, load, acc);
         float a[8];
         row_mean(acc, self, cur.d, a);
 #pragma unroll
@@ -523,9 +525,9 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
         } else {
 #pragma unroll
             for (int i = 0; i < U; ++i)
-                if (cur.j0 + i < cur.j1) add(i);
+                if (i < cur.j1 - cur.j0) add(i);
         }
-        gather_rest<8, U>(cur.j0, cur.j1, col, val, load, acc);
+        gather_rest<8, U>(cur.j1 - cur.j0, col + cur.j0, val + cur.j0, load, acc);
         unpack8(own, self);
         row_mean(acc, self, cur.d, a);
         const bf16x4 item[4] = {operand4(own.x, own.y), operand4(own.z, own.w),

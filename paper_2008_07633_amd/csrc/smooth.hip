@@ -159,6 +159,9 @@ __device__ __forceinline__ void load_row(const TIN *p, const double *mo, TA (&ou
     }
 }
 
+// Entries are counted from their row's first: a graph may have 2^31 - 2 of
+// them, and an index that steps over the end of its last rows would wrap.
+
 // The epilogue of a row whose sum the lanes hold: y = (1 - omega) x + omega s / d.
 template <typename TIN, typename TX, typename TO, typename TA, int VPL, bool CENTER>
 __device__ __forceinline__ void store_row(const TIN *__restrict__ xrow, const double (&mo)[VPL], const TA (&sum)[VPL],
@@ -193,9 +196,9 @@ __device__ __forceinline__ void store_row(const TIN *__restrict__ xrow, const do
 constexpr int32_t kWaveRow = 4096;
 
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
-__device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_t ldy, int64_t row, int32_t j0,
-                                                int32_t j1, const int32_t *__restrict__ col,
-                                                const TW *__restrict__ val, const TW *__restrict__ deg,
+__device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_t ldy, int64_t row, int32_t len,
+                                                const int32_t *__restrict__ col, const TW *__restrict__ val,
+                                                const TW *__restrict__ deg,
                                                 const TIN *__restrict__ x, const double *__restrict__ mean,
                                                 TO *__restrict__ y, TA keep, TA omega) {
     constexpr int kSteps = VPL <= 4 ? 2 : 1;
@@ -209,12 +212,12 @@ __device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_
     for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int i = 0; i < VPL; ++i) acc[w][i] = TA(0);
-    for (int32_t j = j0 + g; j < j1; j += kSteps * 4 * gw) {
+    for (int32_t j = g; j < len; j += kSteps * 4 * gw) {
         int32_t cj[kSteps * 4];
         TA wj[kSteps * 4], xv[kSteps * 4][VPL];
 #pragma unroll
         for (int q = 0; q < kSteps * 4; ++q) {
-            const int32_t jj = j + q * gw < j1 ? j + q * gw : j1 - 1;
+            const int32_t jj = j + q * gw < len ? j + q * gw : len - 1;
             cj[q] = col[jj];
             wj[q] = cvt<TA>(val[jj]);
         }
@@ -223,7 +226,7 @@ __device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_
             load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[q] * ldx + off, mo, xv[q]);
 #pragma unroll
         for (int q = 0; q < kSteps * 4; ++q)
-            if (j + q * gw < j1) {
+            if (j + q * gw < len) {
 #pragma unroll
                 for (int i = 0; i < VPL; ++i) acc[q % 4][i] = madd(acc[q % 4][i], wj[q], xv[q][i]);
             }
@@ -265,36 +268,38 @@ __device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *par
             const int64_t r = r0 + (int64_t)(t / kWave) * nwg;
             if (r < cnt) {
                 const int64_t row = long_rows[r];
-                const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-                if (j1 - j0 <= kWaveRow)
-                    sweep_long_wave<TIN, TX, TO, TW, TA, VPL, CENTER>(lpr, ldx, ldy, row, j0, j1, col, val, deg, x,
-                                                                      mean, y, keep, omega);
+                const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
+                if (len <= kWaveRow)
+                    sweep_long_wave<TIN, TX, TO, TW, TA, VPL, CENTER>(lpr, ldx, ldy, row, len, col + j0, val + j0, deg,
+                                                                      x, mean, y, keep, omega);
             }
         }
         for (int64_t r = r0; r < cnt && r < r0 + 4 * (int64_t)nwg; r += nwg) {
             const int64_t row = long_rows[r];
-            const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-            if (waves && j1 - j0 <= kWaveRow) continue;
+            const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
+            if (waves && len <= kWaveRow) continue;
+            const int32_t *cr = col + j0;
+            const TW *vr = val + j0;
             TA acc[VPL];
 #pragma unroll
             for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
             if (active) {
                 // four of the group's entries in flight, added in their order
-                for (int32_t j = j0 + g; j < j1; j += 4 * ngroups) {
+                for (int32_t j = g; j < len; j += 4 * ngroups) {
                     int32_t cj[4];
                     TA wj[4], xv[4][VPL];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int32_t jj = j + i * ngroups < j1 ? j + i * ngroups : j1 - 1;
-                        cj[i] = col[jj];
-                        wj[i] = cvt<TA>(val[jj]);
+                        const int32_t jj = j + i * ngroups < len ? j + i * ngroups : len - 1;
+                        cj[i] = cr[jj];
+                        wj[i] = cvt<TA>(vr[jj]);
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (j + i * ngroups < j1) {
+                        if (j + i * ngroups < len) {
 #pragma unroll
                             for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
                         }
@@ -354,20 +359,22 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
     double mo[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) mo[i] = CENTER ? mean[off + i] : 0.0;
-    const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
-    if (j1 - j0 > max_len) return;      // a long row: taken by the workgroups above (FP64: k_sweep_hub64)
+    const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
+    if (len > max_len) return;      // a long row: taken by the workgroups above (FP64: k_sweep_hub64)
+    col += j0;
+    val += j0;
     TA self[VPL];
     load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
     const TA d = cvt<TA>(deg[row]);
     TA acc[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
-    for (int32_t j = j0; j < j1; j += U) {
+    for (int32_t j = 0; j < len; j += U) {
         int32_t cj[U];
         TA wj[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const int32_t jj = (j + i < j1) ? j + i : j1 - 1;     // clamped: a valid, cached entry
+            const int32_t jj = (j + i < len) ? j + i : len - 1;     // clamped: a valid, cached entry
             cj[i] = col[jj];
             wj[i] = cvt<TA>(val[jj]);
         }
@@ -376,7 +383,7 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
         for (int i = 0; i < U; ++i) load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            if (j + i < j1) {
+            if (j + i < len) {
 #pragma unroll
                 for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
             }
@@ -411,19 +418,21 @@ __global__ __launch_bounds__(256) void k_sweep_color(int64_t nthreads, int32_t l
     const int32_t off = (int32_t)(t - ri * lpr) * VPL;
     const int64_t row = rows[ri];
     const double mo[VPL] = {};
-    const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+    const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
+    col += j0;
+    val += j0;
     T self[VPL];
     load_row<T, T, T, VPL, false>(x + row * k + off, mo, self);
     const T d = deg[row];
     T acc[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) acc[i] = T(0);
-    for (int32_t j = j0; j < j1; j += U) {
+    for (int32_t j = 0; j < len; j += U) {
         int32_t cj[U];
         T wj[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const int32_t jj = (j + i < j1) ? j + i : j1 - 1;
+            const int32_t jj = (j + i < len) ? j + i : len - 1;
             cj[i] = col[jj];
             wj[i] = val[jj];
         }
@@ -432,7 +441,7 @@ __global__ __launch_bounds__(256) void k_sweep_color(int64_t nthreads, int32_t l
         for (int i = 0; i < U; ++i) load_row<T, T, T, VPL, false>(x + (int64_t)cj[i] * k + off, mo, xv[i]);
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            if (j + i < j1) {
+            if (j + i < len) {
 #pragma unroll
                 for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
             }
@@ -478,12 +487,12 @@ __global__ __launch_bounds__(256) void k_sweep_hub64(int32_t kw, int32_t ldx, in
     const int32_t cnt = *hub_cnt;
     for (int32_t r = blockIdx.x; r < cnt; r += gridDim.x) {
         const int64_t row = hub_rows[r];
-        const int32_t j0 = rowptr[row], j1 = rowptr[row + 1];
+        const uint32_t j0 = rowptr[row], j1 = rowptr[row + 1];
         double mo[1] = {0.0};
         if (CENTER && t < kw) mo[0] = mean[t];
         double acc = 0.0;
-        for (int32_t jc = j0; jc < j1; jc += chunk) {
-            const int32_t len = (j1 - jc) < chunk ? (j1 - jc) : chunk;
+        for (uint32_t jc = j0; jc < j1; jc += chunk) {
+            const int32_t len = (j1 - jc) < (uint32_t)chunk ? (int32_t)(j1 - jc) : chunk;
             // the chunk's columns and weights, then its neighbour values: every thread's loads in flight
             // before its LDS stores
             if (t < len) {
