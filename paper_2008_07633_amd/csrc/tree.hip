@@ -81,31 +81,71 @@ __device__ __forceinline__ void walk_arc(int32_t a, int32_t p, const int32_t *__
     next[a] = (q == 0 && nx == q0) ? kNil : (uint32_t)nx;
 }
 
-// A thread takes the arcs of one row; rows over kArcRow arcs are taken by
-// their whole workgroup.  (Finding each arc's row by binary search over
-// rowptr took 141 us for the 150^3 mesh's 6.7M arcs, this takes 71.)
+// A thread takes the arcs of a row of up to kArcRow.  Longer rows (the hubs of
+// stars and power-law trees) are listed, a wavefront's arcs at a time, for the
+// whole grid of the next launch, since each arc is a chain of dependent reads
+// that one workgroup would take in turn.  (Finding every arc's row by binary
+// search over rowptr took 141 us for the 150^3 mesh's 6.7M arcs, this takes
+// 71.  With long rows left to the workgroup that holds their nodes, the layout
+// of a spanning tree of the 500,000-node Chung-Lu graph, whose 256 first nodes
+// have 131 arcs each, took WALK_CL.)
 constexpr int32_t kArcRow = 16;
+constexpr int32_t kOwnPieces = 8;      // a row of more pieces is listed by its whole workgroup
+constexpr uint32_t kLongArcBlocks = 512;
+
+struct ArcPiece {
+    int32_t row, first;
+};
 
 __global__ __launch_bounds__(kB) void k_walk_init(int64_t n, const int32_t *__restrict__ rowptr,
                                                   const int32_t *__restrict__ col, int32_t *__restrict__ rev,
-                                                  int32_t *__restrict__ src, uint32_t *__restrict__ next) {
-    __shared__ int32_t rows[kB];
-    __shared__ int32_t nrows;
-    if (threadIdx.x == 0) nrows = 0;
+                                                  int32_t *__restrict__ src, uint32_t *__restrict__ next,
+                                                  ArcPiece *__restrict__ pieces, int32_t *__restrict__ count) {
+    __shared__ int32_t row[kB], first[kB], num[kB], at[kB];
+    __shared__ int32_t nrows, total, base;
+    if (threadIdx.x == 0) nrows = total = 0;
     __syncthreads();
     const int64_t p = (int64_t)blockIdx.x * kB + threadIdx.x;
+    int32_t j0 = 0, cnt = 0, to = 0;
     if (p < n) {
-        const int32_t j0 = rowptr[p], j1 = rowptr[p + 1];
-        if (j1 - j0 > kArcRow)
-            rows[atomicAdd(&nrows, 1)] = (int32_t)p;
-        else
-            for (int32_t a = j0; a < j1; ++a) walk_arc(a, (int32_t)p, rowptr, col, rev, src, next);
+        j0 = rowptr[p];
+        const int32_t len = rowptr[p + 1] - j0;
+        if (len <= kArcRow) {
+            for (int32_t i = 0; i < len; ++i) walk_arc(j0 + i, (int32_t)p, rowptr, col, rev, src, next);
+        } else {
+            cnt = (len - 1) / kWave + 1;
+            to = atomicAdd(&total, cnt);
+        }
     }
     __syncthreads();
-    const int32_t cnt = nrows;
-    for (int32_t i = 0; i < cnt; ++i) {
-        const int32_t r = rows[i], j1 = rowptr[r + 1];
-        for (int32_t a = rowptr[r] + (int32_t)threadIdx.x; a < j1; a += kB) walk_arc(a, r, rowptr, col, rev, src, next);
+    if (total == 0) return;
+    if (threadIdx.x == 0) base = atomicAdd(count, total);
+    __syncthreads();
+    to += base;
+    if (cnt <= kOwnPieces) {
+        for (int32_t i = 0; i < cnt; ++i) pieces[to + i] = ArcPiece{(int32_t)p, j0 + i * kWave};
+    } else {
+        const int32_t s = atomicAdd(&nrows, 1);
+        row[s] = (int32_t)p;
+        first[s] = j0;
+        num[s] = cnt;
+        at[s] = to;
+    }
+    __syncthreads();
+    const int32_t listed = nrows;
+    for (int32_t s = 0; s < listed; ++s)
+        for (int32_t i = threadIdx.x; i < num[s]; i += kB) pieces[at[s] + i] = ArcPiece{row[s], first[s] + i * kWave};
+}
+
+__global__ __launch_bounds__(kB) void k_walk_long(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                                  int32_t *__restrict__ rev, int32_t *__restrict__ src,
+                                                  uint32_t *__restrict__ next, const ArcPiece *__restrict__ pieces,
+                                                  const int32_t *__restrict__ count) {
+    const int32_t lane = threadIdx.x % kWave, cnt = *count;
+    for (int64_t w = (int64_t)blockIdx.x * (kB / kWave) + threadIdx.x / kWave; w < cnt;
+         w += (int64_t)gridDim.x * (kB / kWave)) {
+        const ArcPiece t = pieces[w];
+        if (lane < rowptr[t.row + 1] - t.first) walk_arc(t.first + lane, t.row, rowptr, col, rev, src, next);
     }
 }
 
@@ -1153,8 +1193,10 @@ void tree_precond(const sfg_tree *T, const TreePrecond &p, const double *r, doub
 // ------------------------------------------------------------------ tree layout
 
 struct TreePlan {
-    int32_t *rowptr, *col, *eid, *rev, *src, *pos, *down_at, *dbefore, *scan_scr, *pre_of, *parnode, *count,
-        *bad;      // bad[1]: a walk of the list ranking was over its bound
+    int32_t *rowptr, *col, *eid, *rev, *src, *pos, *down_at, *dbefore, *scan_scr, *pre_of, *parnode;
+    // one range, cleared at the start: marked edges; pieces of long rows; bad (bad[1]: a walk of the list ranking was
+    // over its bound)
+    int32_t *count, *pieces, *bad;
     uint32_t *next, *dist;
     double *val, *deg;
     uint64_t *link0, *link1;
@@ -1167,8 +1209,9 @@ static TreePlan plan_tree(Carver &c, int64_t n, int64_t m) {
     const int64_t A = 2 * (n - 1) > 0 ? 2 * (n - 1) : 0;
     TreePlan p;
     p.mask = c.take<uint8_t>(m + 1);
-    p.count = c.take<int32_t>(2);
-    p.bad = c.take<int32_t>(2);
+    p.count = c.take<int32_t>(4);
+    p.pieces = p.count + 1;
+    p.bad = p.count + 2;
     p.rowptr = c.take<int32_t>(n + 1);
     p.col = c.take<int32_t>(A + 1);
     p.eid = c.take<int32_t>(A + 1);
@@ -1211,7 +1254,7 @@ void tree_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const 
     Carver c(ws);
     TreePlan p = plan_tree(c, n, m);
     const int64_t A = 2 * (n - 1);
-    fill_i32(p.count, 2, 0, s);
+    fill_i32(p.count, 4, 0, s);
     if (m > 0) {
         hipLaunchKernelGGL(k_mask_eq, dim3(std::min(grid_for(m, kB), kMaskBlocks)), dim3(kB), 0, s, m, keep,
                            (uint8_t)1, p.mask, p.count);
@@ -1228,9 +1271,13 @@ void tree_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const 
     // tree CSR with FP64 weights, columns ascending per row
     build_csr(n, m, u, v, w, SFG_F64, p.mask, p.rowptr, p.col, p.val, p.eid, p.deg, p.csr_ws, p.csr_wsb, s);
     const dim3 ga(grid_for(A, kB)), gn(grid_for(n, kB)), b(kB);
-    hipLaunchKernelGGL(k_walk_init, gn, b, 0, s, n, p.rowptr, p.col, p.rev, p.src, p.next);
+    // pieces of long rows: at most A / 64 + A / 17 of two words, in what later holds the walk positions
+    ArcPiece *pieces = reinterpret_cast<ArcPiece *>(p.pos);
+    hipLaunchKernelGGL(k_walk_init, gn, b, 0, s, n, p.rowptr, p.col, p.rev, p.src, p.next, pieces, p.pieces);
     SFG_LAUNCH_CHECK();
-    fill_i32(p.bad, 2, 0, s);
+    hipLaunchKernelGGL(k_walk_long, dim3(std::min(grid_for(A, kB * kArcRow), kLongArcBlocks)), b, 0, s, p.rowptr, p.col,
+                       p.rev, p.src, p.next, pieces, p.pieces);
+    SFG_LAUNCH_CHECK();
     // jumping over `len` packed words: the result is in a0
     uint64_t *a0 = p.link0, *a1 = p.link1;
     auto jump = [&](int64_t len) {

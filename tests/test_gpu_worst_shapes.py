@@ -1,0 +1,49 @@
+"""Calls on shapes that a kernel's usual case does not cover take times of the usual order: hub rows that share one
+workgroup's nodes in a tree's layout."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def canonical(n, a, b):
+    """(u, v) in order, and the place of every given edge in it."""
+    key = np.minimum(a, b).astype(np.int64) * n + np.maximum(a, b)
+    o = np.argsort(key)
+    return (key[o] // n).astype(np.int32), (key[o] % n).astype(np.int32), o
+
+
+def micros(f):
+    """The shortest of five calls after two."""
+    out = []
+    for i in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        out.append(1e3 * a.elapsed_time(b))
+    return min(out[2:])
+
+
+def test_layout_of_hub_rows():
+    # 256 hubs with the last ids (one workgroup of nodes), the other nodes on their rows: against a tree of random
+    # parents.  One workgroup took the hubs' arcs in 4,096 steps of dependent reads, several times all of the rest.
+    from paper_2008_07633_amd import sfg as S
+
+    n, rng = 1 << 20, np.random.default_rng(910)
+    i = np.arange(1, n)
+    random, ids = rng.integers(0, i), rng.permutation(n)
+    leaf = np.arange(n - 256)
+    hubs = (np.r_[leaf, np.arange(n - 256, n - 1)], np.r_[n - 256 + rng.integers(0, 256, n - 256), np.arange(n - 255, n)])
+    w, keep, t = dev(np.ones(n - 1)), torch.ones(n - 1, dtype=torch.uint8, device="cuda"), {}
+    for name, (a, b) in {"random": (ids[i], ids[random]), "hubs": hubs}.items():
+        u, v, _ = canonical(n, a, b)
+        u, v = dev(u), dev(v)
+        t[name] = micros(lambda: S.sfg_tree_order(n, u, v, w, keep))
+    assert t["hubs"] <= 2.0 * t["random"], t
