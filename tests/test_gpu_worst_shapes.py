@@ -1,5 +1,5 @@
 """Calls on shapes that a kernel's usual case does not cover take times of the usual order: hub rows that share one
-workgroup's nodes in a tree's layout."""
+workgroup's nodes in a tree's layout, chains of hooks as long as the graph in the spanning forest."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +47,19 @@ def test_layout_of_hub_rows():
         u, v = dev(u), dev(v)
         t[name] = micros(lambda: S.sfg_tree_order(n, u, v, w, keep))
     assert t["hubs"] <= 2.0 * t["random"], t
+
+
+@pytest.mark.parametrize("n", [200000, 400000, 500000, 1000000])
+def test_forest_of_one_chain(n):
+    # a path of shuffled ids: weights rising along it (every node hooks onto the next: one chain) against random ones
+    from paper_2008_07633_amd import sfg as S
+
+    rng = np.random.default_rng(911)
+    ids, t = rng.permutation(n), {}
+    u, v, o = canonical(n, ids[:-1], ids[1:])
+    for name, w in {"chain": (1.0 + o / n), "random": rng.uniform(1.0, 2.0, n - 1)}.items():
+        a = (n, dev(u), dev(v), dev(w))
+        tree, comps = S.sfg_spanning_tree(*a)
+        assert comps == 1 and int(tree.sum()) == n - 1
+        t[name] = micros(lambda: S.sfg_spanning_tree(*a))
+    assert t["chain"] <= 3.0 * t["random"], t
