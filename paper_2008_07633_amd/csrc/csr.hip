@@ -26,6 +26,8 @@
 //  5. one thread per row sums its weights in column order, in FP64; rows
 //     over 256 entries (hubs) are staged through LDS by a wavefront and
 //     summed by one of its lanes in the same order
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace sfg {
@@ -68,7 +70,7 @@ constexpr int64_t kSortMinEdges = int64_t(1) << 18;
 
 bool csr_sorts(int64_t n, int64_t m) { return m > kSortDensity * n && m >= kSortMinEdges; }
 
-CsrPlan plan_csr(Carver &c, int64_t n, int64_t m) {
+CsrPlan plan_csr(Carver &c, int64_t n, int64_t m, bool sorts) {
     CsrPlan p;
     p.estart = c.take<int32_t>(n + 1);
     p.up = c.take<int32_t>(n + 1);
@@ -80,7 +82,6 @@ CsrPlan plan_csr(Carver &c, int64_t n, int64_t m) {
     p.long_cnt = p.walk_cnt + 1;
     p.deg_cnt = p.walk_cnt + 2;
     p.tot = c.take<int32_t>(n + 1);
-    const bool sorts = csr_sorts(n, m);
     p.tmp = sorts ? nullptr : c.take<int32_t>(2 * m + 1);
     p.walk_rows = c.take<int32_t>(n + 1);
     p.long_rows = c.take<int32_t>(n + 1);
@@ -769,10 +770,13 @@ void max_row_length(const sfg_csr *H, int32_t *out, hipStream_t s) {
     SFG_LAUNCH_CHECK();
 }
 
+// For every form that a graph of m edges and at most n nodes may take, so that
+// a workspace serves smaller graphs as well.
 size_t csr_workspace_bytes(int64_t n, int64_t m) {
-    Carver c(nullptr);
-    plan_csr(c, n, m);
-    return c.used + 256;
+    Carver walks(nullptr), sorted(nullptr);
+    plan_csr(walks, n, m, false);
+    if (m >= kSortMinEdges) plan_csr(sorted, n, m, true);
+    return std::max(walks.used, sorted.used) + 256;
 }
 
 void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
@@ -786,13 +790,13 @@ void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const v
     SFG_REQUIRE(rowptr && deg && (m == 0 || (u && v && w && col && val && eid)), SFG_EINVAL,
                 "laplacian_csr: null pointer");
     Carver c(ws);
-    CsrPlan p = plan_csr(c, n, m);
+    const bool walk = m <= kWalkDensity * n, sorts = csr_sorts(n, m);
+    CsrPlan p = plan_csr(c, n, m, sorts);
     const dim3 gn(grid_for(n, 256)), b(256);
     fill_i32(p.zeroed, p.zeroed_len, 0, s);
     hipLaunchKernelGGL(k_estart, dim3(grid_for((m + kEdgesPerThread) / kEdgesPerThread, 256)), b, 0, s, n, m,
                        nullptr, u, p.estart);
     SFG_LAUNCH_CHECK();
-    const bool walk = m <= kWalkDensity * n, sorts = csr_sorts(n, m);
     EdgeSort es{};
     if (walk) {
         hipLaunchKernelGGL(k_walk_count, gn, b, 0, s, n, m, p.estart, v, mask, p.up, p.cnt_lo, p.walk_rows,

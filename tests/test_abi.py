@@ -177,3 +177,21 @@ def test_header_compiles_as_c_and_cpp(tmp_path):
         if shutil.which(cc) is None:
             pytest.skip(f"no {cc}")
         subprocess.run([cc, std, "-Wall", "-Werror", "-pedantic", "-fsyntax-only", "-I", inc, str(src)], check=True)
+
+
+@pytest.mark.parametrize("m", [1 << 18, 1000000, 40000000])
+@pytest.mark.parametrize("op", ["OP_LAPLACIAN_CSR", "OP_TREE_ORDER", "OP_MPNN_TRAIN", "OP_COARSEN"])
+def test_a_workspace_serves_smaller_graphs(L, op, m):
+    """Sized for a program's largest graph: fewer nodes or fewer edges need no more, whichever form builds the CSR
+    (8 edges a node and 2^18 edges are where it changes)."""
+    from paper_2008_07633_amd import sfg
+
+    def need(n, edges):
+        return sfg.sfg_workspace_bytes(getattr(sfg, op), n, edges, 16, sfg.F32)
+
+    at = m // 8
+    sizes = [at // 2, at - 1, at, at + 1, at + 2, 2 * at]
+    for small, large in zip(sizes, sizes[1:]):
+        assert need(small, m) <= need(large, m), (small, large)
+    for n in sizes:
+        assert need(n, m - 1) <= need(n, m) <= need(n, m + 1)
