@@ -218,14 +218,19 @@ __global__ void k_f32_to_f64(int64_t m, const float *__restrict__ a, double *__r
 }
 
 // keep from the base sparsifier: 0 stays 0, an earlier round's addition (2)
-// stays 2, any other member is 1
-__global__ void k_keep_init(int64_t m, const uint8_t *__restrict__ base, uint8_t *keep) {
+// stays 2, any other member is 1.  Neither kernel touches keep when the
+// selection's threshold (tau, may be nullptr) is NaN: the call fails then, and
+// the host learns of it only after these have run.
+__global__ void k_keep_init(int64_t m, const uint8_t *__restrict__ base, uint8_t *keep,
+                            const double *__restrict__ tau) {
+    if (tau && *tau != *tau) return;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < m) keep[e] = base[e] == 2 ? 2 : (base[e] ? 1 : 0);
 }
 
 __global__ void k_keep_add(int64_t nc, const int32_t *__restrict__ cand, const uint8_t *__restrict__ sel,
-                           uint8_t *keep) {
+                           uint8_t *keep, const double *__restrict__ tau) {
+    if (tau && *tau != *tau) return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nc && sel[i]) keep[cand[i]] = 2;
 }
@@ -658,13 +663,13 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         if (tau_h != tau_h) fail(SFG_ENUMERIC, "sparsify: NaN or negative edge score");
     };
     const bool bands = !f64 && q->band > 0.0 && ksel > 0 && ksel < nc;
-    if (bands) threshold();
-    if (rep) {
+    const auto report = [&] {
+        if (!rep) return;
         rep->n = n;
         rep->m = m;
         rep->n_cand = nc;
         rep->k_sel = ksel;
-        rep->tau = tau_h;      // the band re-scoring replaces it; without one it is read at the end
+        rep->tau = tau_h;
         rep->band = 0;
         rep->band_above = 0;
         rep->band_rounds = 0;
@@ -673,23 +678,27 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
         rep->node_order = (no && no->use) ? 1 : 0;
         rep->n_scored = nc;
         if (!passes) rep->sweeps_per_pass = 1;
-    }
+    };
     if (bands) {
+        threshold();
+        report();
         // precision form: FP64 re-scoring of the edges near the threshold
         band_rescore(&G64.H, q->k, q->sweeps, q->omega, sx0, nc, cand, su, sv, w64, (const float *)score, ksel,
                      tau_h, q->band, sel, rep, A, s);
     }
-    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, base, keep);
+    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, base, keep, tau);
     SFG_LAUNCH_CHECK();
     if (nc > 0) {
-        hipLaunchKernelGGL(k_keep_add, dim3(grid_for(nc, 256)), dim3(256), 0, s, nc, cand, sel, keep);
+        hipLaunchKernelGGL(k_keep_add, dim3(grid_for(nc, 256)), dim3(256), 0, s, nc, cand, sel, keep, tau);
         SFG_LAUNCH_CHECK();
     }
     if (rep) clock.mark();
-    if (!bands) threshold();
+    if (!bands) {
+        threshold();
+        report();
+    }
     if (scoped) A.release(mark);
     if (rep) {
-        if (!bands) rep->tau = tau_h;
         clock.wait();
         rep->ms_other = clock.ms(0);
         rep->ms_smooth = clock.ms(1);
@@ -741,7 +750,7 @@ void single_level_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t
     // multi-round densification: the budget of the single pass in near-equal
     // quotas, each scored on the sparsifier grown so far (keep is its own base)
     const int64_t k_total = (int64_t)std::ceil(p->frac * (double)(m - (n - 1)));
-    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep);
+    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep, nullptr);
     SFG_LAUNCH_CHECK();
     NodeOrder no;
     no.launches = planned_launches(p, rounds);
@@ -873,10 +882,10 @@ bool surrogate_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *v
     SFG_HIP(hipMemcpyAsync(&tau_h, tau, 8, hipMemcpyDeviceToHost, s));
     SFG_HIP(hipStreamSynchronize(s));
     if (tau_h != tau_h) fail(SFG_ENUMERIC, "sparsify: NaN or negative edge score");
-    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep);
+    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep, nullptr);
     SFG_LAUNCH_CHECK();
     if (ne > 0) {
-        hipLaunchKernelGGL(k_keep_add, dim3(grid_for(ne, 256)), dim3(256), 0, s, ne, cand_e, sel, keep);
+        hipLaunchKernelGGL(k_keep_add, dim3(grid_for(ne, 256)), dim3(256), 0, s, ne, cand_e, sel, keep, nullptr);
         SFG_LAUNCH_CHECK();
     }
     float ms_select = tm.stop();
@@ -911,7 +920,7 @@ void check_kappa_params(const sfg_kappa_params &p, int64_t n);
 void sigma_sparsify(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const float *w32,
                     const uint8_t *tree, const sfg_params *p, const double *x0, uint8_t *keep, sfg_report *rep,
                     DevArena &A, hipStream_t s) {
-    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep);
+    hipLaunchKernelGGL(k_keep_init, dim3(grid_for(m, 256)), dim3(256), 0, s, m, tree, keep, nullptr);
     SFG_LAUNCH_CHECK();
     const sfg_kappa_params kp = kappa_defaults(&p->est);
     struct Holder {
