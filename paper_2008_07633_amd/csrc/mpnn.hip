@@ -354,18 +354,19 @@ __device__ __forceinline__ void gather_rest(int32_t len, const int32_t *__restri
     }
 }
 
-// a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1, one
-// reciprocal for all eight columns.  After a ReLU many sums are zero, whose
-// quotient by these steps is zero as well, so only large values are looked for;
-// a sum under 2^-40 may end an ulp of FP32 off, before its rounding to BF16.
+// a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1, bit for bit,
+// with one reciprocal for all eight columns in divide_row's range.  After a
+// ReLU many sums are zero (+0), whose quotient by these steps is +0 as well.
 __device__ __forceinline__ void row_mean(const float (&acc)[8], const float (&self)[8], float d, float (&a)[8]) {
-    uint32_t hi = 0;      // NaN and infinity are the largest
+    uint32_t lo = 0x7f800000u, hi = 0;      // NaN and infinity are the largest
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        const uint32_t b = __float_as_uint(acc[t]) & 0x7fffffffu;
-        hi = b > hi ? b : hi;
+        const uint32_t b = __float_as_uint(acc[t]), mag = b & 0x7fffffffu;
+        hi = mag > hi ? mag : hi;
+        const uint32_t low = b == 0 ? 0x7f800000u : mag;
+        lo = low < lo ? low : lo;
     }
-    if (__all(hi < __float_as_uint(0x1p40f) && d > 0x1p-40f && d < 0x1p40f)) {
+    if (__all(lo > __float_as_uint(0x1p-40f) && hi < __float_as_uint(0x1p40f) && d > 0x1p-40f && d < 0x1p40f)) {
         const float y = refined_rcp(d);
 #pragma unroll
         for (int t = 0; t < 8; ++t) a[t] = quotient(acc[t], d, y) + 0.f * self[t];
@@ -552,8 +553,10 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
 // yhat_e = relu(z_e W3) . w4[0:32] + w4[32]; lane quarter q holds eight columns
 // of |hp - hq| and of hp * hq (as k_layer2_mfma left them) and edge feature q.
 // Candidates are loaded two tiles ahead, their ends one tile ahead.  All of an
-// accumulator's products have one shape: with the edge features' as a
-// 16x16x16 after the 16x16x32 ones the sums came out wrong.
+// accumulator's products have one shape: the compiler (ROCm 7.2) puts a
+// 16x16x16 right behind the 16x16x32 that writes its accumulator, without the
+// wait states the longer product needs, and with the edge features' product as
+// a 16x16x16 the sums lacked the products of hp * hq.
 __global__ __launch_bounds__(256, kHeadWaves) void k_head_mfma(int64_t ne, uint32_t nvb, const int32_t *__restrict__ cand,
                                                    const int32_t *__restrict__ u, const int32_t *__restrict__ v,
                                                    const __hip_bfloat16 *__restrict__ h,
