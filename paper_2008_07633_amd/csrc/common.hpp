@@ -123,6 +123,16 @@ __device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb, u
     return ((i / chunk) * kNumXcd + x) * chunk + i % chunk;
 }
 
+// Between a wavefront's writes to LDS and its other lanes' reads of them (and
+// before the next writes there).  Its LDS accesses run in program order; the
+// fences keep the compiler from moving them, which wave_barrier alone, no
+// access to memory, does not.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Quotients with one denominator, bit for bit as the operator gives them: the
 // compiler's own steps for a division (a reciprocal refined by Newton's method,
 // the product, the remainder's correction) with the reciprocal taken once.  Its

@@ -578,12 +578,11 @@ __global__ __launch_bounds__(256) void k_degree_long(const int32_t *__restrict__
         double d = 0.0;
         for (uint32_t c = j0; c < j1; c += kChunk) {
             const int32_t len = (j1 - c) < kChunk ? (j1 - c) : kChunk;
-            // one wavefront runs in program order: the first lane reads what
-            // all lanes wrote, and the next chunk is written after it is done
+            // the first lane reads what all lanes wrote, and the next chunk is written after it is done
             for (int32_t i = lane; i < len; i += 64) b[i] = (double)val[c + i];
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             if (lane == 0) d = seq_sum(d, b, len);
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
         }
         if (lane == 0) deg[row] = (TW)d;
     }

@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
             turn[wv][lane][t] = pack2(self[2 * t], self[2 * t + 1]);
             turn[wv][lane][4 + t] = pack2(a[2 * t], a[2 * t + 1]);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         const int64_t base = first(vb);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
             }
             if (node < n) store_relu(out, q, h + node * kH);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         cur = nxt;
         nxt = after;
         p = pn;
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(256) void k_head_f32(int64_t ne, const int32_t *__r
         float *sd = s_d[wv];
 #pragma unroll
         for (int r = 0; r < 16; ++r) sd[tile_row(r, half) * 33 + col] = fmaxf(acc[r], 0.f) * w4c;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         float o = 0.f;
 #pragma unroll
         for (int j = 0; j < 16; ++j) o += sd[col * 33 + 16 * half + j];
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(256) void k_head_f32(int64_t ne, const int32_t *__r
                     sp[col * 33 + 8 * t + 4 * half + q] = a[t][q];
                     sq[col * 33 + 8 * t + 4 * half + q] = b[t][q];
                 }
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             // dG in the D layout (d is 0 on edges past the end), the w4 gradient, and W3's: z^T dG
             float dg[16];
 #pragma unroll
@@ -840,7 +840,7 @@ __global__ __launch_bounds__(256) void k_head_f32(int64_t ne, const int32_t *__r
             // dz = dG W3^T needs dG with a row per lane
 #pragma unroll
             for (int r = 0; r < 16; ++r) sd[tile_row(r, half) * 33 + col] = dg[r];
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             f32x16 dz0 = {}, dz1 = {};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(256) void k_head_f32(int64_t ne, const int32_t *__r
                     dhq[(base + row) * kH + col] = -dz0[r] * sg + dz1[r] * pa;
                 }
             }
-            __builtin_amdgcn_wave_barrier();      // the next tile writes over this one's LDS
+            wave_lds_sync();      // the next tile writes over this one's LDS
         }
     }
     if constexpr (TRAIN) {
