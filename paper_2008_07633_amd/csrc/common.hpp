@@ -111,16 +111,40 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb) {
 }
 
 // The same in chunks dealt round-robin: XCD x takes chunks x, x + 8, ... of
-// `chunk` consecutive logical blocks (0: one contiguous range per XCD).  Every
-// XCD then gets a sample of the whole index range, where contiguous ranges
-// would give one XCD most of the work (nodes numbered by degree).  Blocks past
-// the last whole round of chunks keep their own index.
-__device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb, uint32_t chunk) {
-    if (chunk == 0) return xcd_remap(b, nb);
-    const uint32_t round = kNumXcd * chunk;
+// kXcdChunk consecutive logical blocks.  Every XCD then gets a sample of the
+// whole index range.  Blocks past the last whole round of chunks keep their
+// own index.
+constexpr uint32_t kXcdChunk = 64;
+
+__device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb) {
+    constexpr uint32_t round = kNumXcd * kXcdChunk;
     if (b >= nb / round * round) return b;
     const uint32_t x = b % kNumXcd, i = b / kNumXcd;
-    return ((i / chunk) * kNumXcd + x) * chunk + i % chunk;
+    return ((i / kXcdChunk) * kNumXcd + x) * kXcdChunk + i % kXcdChunk;
+}
+
+// How a kernel over the rows of a graph deals its workgroups to the XCDs: one
+// contiguous range of rows each keeps neighbouring rows in one L2 (meshes,
+// trees, preorders), but where one range would hold over 1.5 times its share of
+// the entries (a power-law graph numbered by degree: 3.8 to 5 times) its XCD
+// would be the last by far, and chunks are dealt.  Graphs averaging under 8
+// entries per row have no such rows to speak of and are not asked.  (A sweep
+// reads one word that the kernel of the column means left: nine loads in front
+// of every workgroup cost 2 to 5% where the block stays in the caches.)
+// Measured, FP32, 16 vectors: the 4M-node Chung-Lu graph, contiguous 3,486 us a
+// sweep, chunks 1,417; relabelled in a tree's preorder (1.01 times the share)
+// 1,739 and 1,744; 27-point meshes in their own order of 64,000 nodes 15.5 and
+// 16.9 (FP64 20.6 and 23.2), of 2.1M nodes 351 and 329.  A row of a million
+// entries among 25 million makes 1.28 of its range, and hub rows have
+// workgroups of their own, hence no less than 1.5.
+__device__ __forceinline__ bool xcd_uneven(const int32_t *__restrict__ rowptr, int64_t n) {
+    uint32_t most = 0;
+#pragma unroll
+    for (int x = 0; x < kNumXcd; ++x) {
+        const uint32_t part = (uint32_t)(rowptr[n * (x + 1) / kNumXcd] - rowptr[n * x / kNumXcd]);
+        most = part > most ? part : most;
+    }
+    return 2ull * kNumXcd * most > 3ull * (uint32_t)(rowptr[n] - rowptr[0]);
 }
 
 // Between a wavefront's writes to LDS and its other lanes' reads of them (and
@@ -369,6 +393,9 @@ struct TreePrecond {
     double *rz = nullptr;              // [lanes][k] lane sums of r . z (one lane: their sum, from partials in dot)
     double *dot = nullptr;
 };
+
+// Graphs averaging 8 or more entries per row (see xcd_uneven).
+inline bool dense_rows(const sfg_csr *H) { return H->nnz >= 8 * H->n; }
 
 inline uint32_t grid_for(int64_t items, int block) {
     int64_t g = (items + block - 1) / block;

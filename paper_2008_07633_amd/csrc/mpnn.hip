@@ -380,7 +380,7 @@ __device__ __forceinline__ void row_mean(const float (&acc)[8], const float (&se
 // (a row of x is 32 bytes), and turns their [x | a] rows through LDS into the
 // operands of four tiles.
 template <int U>
-__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, uint32_t nvb, uint32_t chunk,
+__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, uint32_t nvb, bool dense,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ col, const float *__restrict__ val,
                                                      const float *__restrict__ deg, const float *__restrict__ x,
@@ -401,7 +401,10 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
 #pragma unroll
         for (int i = 0; i < 8; ++i) o[i] = x[row * kF + i];
     };
-    auto first = [&](uint32_t vb) { return ((int64_t)xcd_remap_chunked(vb, nvb, chunk) * 4 + wv) * 64; };
+    const bool uneven = dense && xcd_uneven(rowptr, n);
+    auto first = [&](uint32_t vb) {
+        return ((int64_t)(uneven ? xcd_remap_chunked(vb, nvb) : xcd_remap(vb, nvb)) * 4 + wv) * 64;
+    };
     auto row_of = [&](uint32_t vb) {
         const int64_t p = (vb < nvb ? first(vb) : 0) + lane;
         return p < n ? p : n - 1;
@@ -469,7 +472,7 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
 // h2 = relu([h1 | D^-1 A h1 | 1] W2): lane quarter q holds columns 4q .. 4q + 3
 // and 16 + 4q .. 16 + 4q + 3.
 template <int U>
-__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, uint32_t nvb, uint32_t chunk,
+__global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, uint32_t nvb, bool dense,
                                                      const int32_t *__restrict__ rowptr,
                                                      const int32_t *__restrict__ col, const float *__restrict__ val,
                                                      const float *__restrict__ deg,
@@ -491,7 +494,10 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
     }
     auto raw = [&](int64_t row) { return *reinterpret_cast<const uint4 *>(h1 + row * kH + 8 * q); };
     auto load = [&](int64_t row, float (&o)[8]) { unpack8(raw(row), o); };
-    auto first = [&](uint32_t vb) { return ((int64_t)xcd_remap_chunked(vb, nvb, chunk) * 4 + wv) * 16; };
+    const bool uneven = dense && xcd_uneven(rowptr, n);
+    auto first = [&](uint32_t vb) {
+        return ((int64_t)(uneven ? xcd_remap_chunked(vb, nvb) : xcd_remap(vb, nvb)) * 4 + wv) * 16;
+    };
     auto row_of = [&](uint32_t vb) {
         const int64_t p = (vb < nvb ? first(vb) : 0) + c;
         return p < n ? p : n - 1;
@@ -1205,17 +1211,18 @@ extern "C" sfg_status sfg_mpnn_forward(const sfg_csr *G, const float *params, co
             SFG_LAUNCH_CHECK();
         } else {
             __hip_bfloat16 *h1 = (__hip_bfloat16 *)p.h1, *h2 = (__hip_bfloat16 *)p.h2;
-            // the first U entries of a row are in flight together: the average row of a lattice (6), 4 below, 8 above;
-            // the XCDs' shares are the sweep's
-            const uint32_t chunk = G->nnz >= 8 * n ? 64u : 0u;
+            // the first U entries of a row are in flight together: the average row of a lattice (6), 4 below, 8 above
+            const bool dense = dense_rows(G);
             auto layers = [&](auto ut) {
                 constexpr int U = decltype(ut)::value;
                 const uint32_t nb1 = grid_for(n, 256), nb2 = grid_for(n, 64);
-                hipLaunchKernelGGL(k_layer1_mfma<U>, dim3(tile_grid(nb1, kLayerWaves(U))), b, 0, s, n, nb1, chunk, G->rowptr, G->col,
-                                   (const float *)G->val, (const float *)G->deg, node_feat, params + kOffW1, h1);
+                hipLaunchKernelGGL(k_layer1_mfma<U>, dim3(tile_grid(nb1, kLayerWaves(U))), b, 0, s, n, nb1, dense,
+                                   G->rowptr, G->col, (const float *)G->val, (const float *)G->deg, node_feat,
+                                   params + kOffW1, h1);
                 SFG_LAUNCH_CHECK();
-                hipLaunchKernelGGL(k_layer2_mfma<U>, dim3(tile_grid(nb2, kLayerWaves(U))), b, 0, s, n, nb2, chunk, G->rowptr, G->col,
-                                   (const float *)G->val, (const float *)G->deg, h1, params + kOffW2, h2);
+                hipLaunchKernelGGL(k_layer2_mfma<U>, dim3(tile_grid(nb2, kLayerWaves(U))), b, 0, s, n, nb2, dense,
+                                   G->rowptr, G->col, (const float *)G->val, (const float *)G->deg, h1,
+                                   params + kOffW2, h2);
                 SFG_LAUNCH_CHECK();
             };
             if (G->nnz <= 4 * n)

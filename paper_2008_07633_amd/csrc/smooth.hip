@@ -103,10 +103,14 @@ __global__ __launch_bounds__(kSumThreads) void k_colsum_partial(int64_t n, int32
 }
 
 // One workgroup per column: strided partial sums, then a fixed-shape tree.
+// The first also leaves how the sweeps on the graph (rowptr) deal their
+// workgroups, where uneven is given.
 __global__ __launch_bounds__(256) void k_colsum_final(int32_t nb, int32_t k, const DD *__restrict__ partial,
-                                                      int64_t n, double *mean) {
+                                                      int64_t n, double *mean, const int32_t *__restrict__ rowptr,
+                                                      uint32_t *__restrict__ uneven) {
     __shared__ double shi[256], slo[256];
     const int c = blockIdx.x, t = threadIdx.x;
+    if (uneven && c == 0 && t == 255) *uneven = xcd_uneven(rowptr, n);
     DD s{0.0, 0.0};
     for (int b = t; b < nb; b += 256) s = dd_add(s, partial[(int64_t)b * k + c]);
     shi[t] = s.hi;
@@ -329,7 +333,8 @@ __device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *par
 
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER, bool LONG>
 __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, int32_t lpr_log2, int32_t ldx,
-                                               int32_t ldy, int32_t max_len, uint32_t chunk, uint32_t nlong,
+                                               int32_t ldy, int32_t max_len, int64_t n, bool dense,
+                                               const uint32_t *__restrict__ uneven, uint32_t nlong,
                                                const int32_t *__restrict__ long_rows,
                                                const int32_t *__restrict__ long_cnt,
                                                const int32_t *__restrict__ rows,
@@ -349,7 +354,9 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
             return;
         }
     }
-    const uint32_t b = xcd_remap_chunked(blockIdx.x - nlong, gridDim.x - nlong, chunk);
+    const uint32_t lb = blockIdx.x - nlong, nb = gridDim.x - nlong;
+    const bool chunks = dense && (uneven ? *uneven != 0 : xcd_uneven(rowptr, n));
+    const uint32_t b = chunks ? xcd_remap_chunked(lb, nb) : xcd_remap(lb, nb);
     const int64_t t = (int64_t)b * 256 + threadIdx.x;
     if (t >= nthreads) return;
     const int64_t ri = lpr_log2 >= 0 ? (t >> lpr_log2) : t / lpr;
@@ -545,6 +552,7 @@ __global__ __launch_bounds__(256) void k_sweep_hub64(int32_t kw, int32_t ldx, in
 }
 
 struct LongRows {
+    const uint32_t *uneven = nullptr;      // device word: xcd_uneven of the graph (nullptr: the kernel finds out)
     const int32_t *rows = nullptr;
     const int32_t *count = nullptr;
     int32_t max_len = 0x7fffffff;
@@ -594,16 +602,7 @@ struct SweepShape {
 // in flight at once: 355 against 377 ms for the 4M-node Chung-Lu hierarchy.
 // Others get 1,024, since every launch dispatches its workgroups even when
 // the list is empty: 16,384 there cost 1.4 us per sweep.  A multiple of 8.
-inline unsigned long_row_blocks(const sfg_csr *H) { return H->nnz >= 8 * H->n ? 16384u : 1024u; }
-
-// How k_sweep deals its workgroups to the XCDs (see xcd_remap_chunked): one
-// contiguous range of rows each keeps neighbouring rows in one L2 (meshes,
-// trees), but on a power-law graph numbered by degree it hands XCD 0 most of
-// the entries.  Graphs averaging 8 or more entries per row are dealt in
-// chunks of 64 workgroups instead: one FP32 sweep of 16 vectors on the
-// 4M-node Chung-Lu graph takes 1.44 ms against 3.57, on its 1M-node coarse
-// level 1.19 against 1.82 (chunks of 1 to 64 alike, 256: 1.57).
-inline uint32_t xcd_chunk(const sfg_csr *H) { return H->nnz >= 8 * H->n ? 64u : 0u; }
+inline unsigned long_row_blocks(const sfg_csr *H) { return dense_rows(H) ? 16384u : 1024u; }
 
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER, bool LONG>
 void launch_sweep_u(const sfg_csr *H, const SweepShape &sh, const TIN *x, const double *mean, TO *y, double omega,
@@ -617,9 +616,9 @@ void launch_sweep_u(const sfg_csr *H, const SweepShape &sh, const TIN *x, const 
     if (lr.side) SFG_HIP(hipStreamWaitEvent(s, lr.ez, 0));
     const unsigned nlong = LONG ? long_row_blocks(H) : 0u;
     hipLaunchKernelGGL((k_sweep<TIN, TX, TO, TW, TA, VPL, U, CENTER, LONG>), dim3(nlong + grid_for(nthreads, 256)),
-                       dim3(256), 0, s, nthreads, lpr, ilog2_exact(lpr), sh.ldx, sh.ldy, lr.max_len, xcd_chunk(H),
-                       nlong, lr.rows, lr.count, rows, H->rowptr, H->col, (const TW *)H->val, (const TW *)H->deg, x,
-                       mean, y, (TA)(1.0 - omega), (TA)omega);
+                       dim3(256), 0, s, nthreads, lpr, ilog2_exact(lpr), sh.ldx, sh.ldy, lr.max_len, H->n,
+                       dense_rows(H), lr.uneven, nlong, lr.rows, lr.count, rows, H->rowptr, H->col, (const TW *)H->val,
+                       (const TW *)H->deg, x, mean, y, (TA)(1.0 - omega), (TA)omega);
     SFG_LAUNCH_CHECK();
     // FP64 hub rows: on the side stream after the previous main sweep, beside this one
     if constexpr (sizeof(TA) == 8) {
@@ -745,6 +744,7 @@ SweepShape part_shape(const sfg_csr *H, int32_t k) {
 struct SmoothPlan {
     DD *partial;
     double *mean;
+    uint32_t *uneven;
     void *buf0, *buf1;
     int32_t *lflag, *lpos, *lrows, *lscan;
 };
@@ -771,7 +771,8 @@ int colsum_blocks(int64_t n) {
 SmoothPlan plan_smooth(Carver &c, int64_t n, int32_t k, sfg_dtype storage) {
     SmoothPlan p;
     p.partial = c.take<DD>((size_t)colsum_blocks(n) * k);
-    p.mean = c.take<double>(k);
+    p.mean = c.take<double>(k + 1);
+    p.uneven = reinterpret_cast<uint32_t *>(p.mean + k);
     p.buf0 = c.take<char>((size_t)n * k * dtype_size(storage));
     p.buf1 = c.take<char>((size_t)n * k * dtype_size(storage));
     p.lflag = c.take<int32_t>(n + 1);
@@ -782,12 +783,13 @@ SmoothPlan plan_smooth(Carver &c, int64_t n, int32_t k, sfg_dtype storage) {
 }
 
 template <typename TIN>
-void launch_column_means(const TIN *x, int64_t n, int32_t k, DD *partial, double *mean, hipStream_t s) {
+void launch_column_means(const TIN *x, int64_t n, int32_t k, DD *partial, double *mean, hipStream_t s,
+                         const int32_t *rowptr = nullptr, uint32_t *uneven = nullptr) {
     const int nb = colsum_blocks(n);
     const int64_t rpb = (n + nb - 1) / nb;
     hipLaunchKernelGGL(k_colsum_partial<TIN>, dim3(nb), dim3(kSumThreads), 0, s, n, k, x, rpb, partial);
     SFG_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_colsum_final, dim3(k), dim3(256), 0, s, nb, k, partial, n, mean);
+    hipLaunchKernelGGL(k_colsum_final, dim3(k), dim3(256), 0, s, nb, k, partial, n, mean, rowptr, uneven);
     SFG_LAUNCH_CHECK();
 }
 
@@ -797,7 +799,7 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
     const int64_t n = H->n;
     const int64_t total = n * (int64_t)k;
     // a2: column means (the block becomes orthogonal to the all-one vector)
-    launch_column_means<double>(x0, n, k, p.partial, p.mean, s);
+    launch_column_means<double>(x0, n, k, p.partial, p.mean, s, H->rowptr, dense_rows(H) ? p.uneven : nullptr);
     if (sweeps == 0) {
         if (final_f32)
             hipLaunchKernelGGL(k_center_convert<float>, dim3(grid_for(total, 256)), dim3(256), 0, s, total, k, x0,
@@ -812,6 +814,7 @@ void run_smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const
     // reduced precision, and FP64 when the caller knows there are hub rows: list
     // the rows over kLongRow entries once for all sweeps (device-side count)
     LongRows lr;
+    lr.uneven = p.uneven;
     if (sizeof(TA) == 4 || hub_rows) {
         hipLaunchKernelGGL(k_long_flag, dim3(grid_for(n, 256)), dim3(256), 0, s, n, H->rowptr, kLongRow, p.lflag);
         SFG_LAUNCH_CHECK();
