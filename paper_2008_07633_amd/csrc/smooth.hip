@@ -166,92 +166,20 @@ __device__ __forceinline__ void load_row(const TIN *p, const double *mo, TA (&ou
 // Entries are counted from their row's first: a graph may have 2^31 - 2 of
 // them, and an index that steps over the end of its last rows would wrap.
 
-// The epilogue of a row whose sum the lanes hold: y = (1 - omega) x + omega s / d.
-template <typename TIN, typename TX, typename TO, typename TA, int VPL, bool CENTER>
-__device__ __forceinline__ void store_row(const TIN *__restrict__ xrow, const double (&mo)[VPL], const TA (&sum)[VPL],
-                                          TA d, TO *__restrict__ yrow, TA keep, TA omega) {
-    TA self[VPL];
-    load_row<TIN, TX, TA, VPL, CENTER>(xrow, mo, self);
-    Vec<TO, VPL> out;
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-        const TA a = keep * self[i];
-        const TA q = sum[i] / d;
-        const TA bo = omega * q;
-        out.v[i] = cvt<TO>(a + bo);
-    }
-    *reinterpret_cast<Vec<TO, VPL> *>(yrow) = out;
-}
-
 // Rows longer than max_len (hubs of power-law graphs), reduced precision
-// only, taken by workgroup `wg` of `nwg` (`part`: 256 VPL values of LDS).  The
-// sum of such a row is defined by 256/lpr lane groups that take interleaved
-// entries and are then combined by a fixed-shape tree, so it is deterministic
-// (the order differs from the sequential one, which FP64 keeps).  Up to
-// kWaveRow entries, where lpr is a power of two, one wavefront forms it: it
-// plays the four wavefronts' groups in turn (four sums per lane, 4 or 8
-// gathers in flight) and combines them with lane shuffles, no barrier; the
-// workgroup's four wavefronts take four rows.  Longer rows, and other lpr,
-// take the whole workgroup.  Both make the same additions.  One FP32 sweep of
-// 16 vectors on the 1M-node coarse level of the 4M-node Chung-Lu graph (36,099
-// such rows) takes 1.12 ms against 1.19 with a workgroup per row, its whole
-// hierarchy 184 ms against 191; with kWaveRow = 1024 the sweeps of the two
-// coarsest levels were 2 to 4% slower.
-constexpr int32_t kWaveRow = 4096;
-
+// only, one at a time by workgroup `wg` of `nwg` (`part`: 256 VPL values of
+// LDS): its 256/lpr lane groups take interleaved entries, then their sums are
+// combined by a fixed-shape tree, so the result is deterministic (the order
+// differs from the sequential one, which FP64 keeps).  The code keeps to the
+// registers of the sweep's other rows (48 in FP32 with 4 columns a lane, 8
+// wavefronts a SIMD): it is part of their kernel.  A form that gave hub rows of
+// up to 4,096 entries a wavefront each, eight gathers in flight, took 86, which
+// left 5 wavefronts to all rows: one FP32 sweep of 32 vectors on a 100^3 mesh
+// 125 us against 108, of 16 on the 4M-node Chung-Lu graph with shuffled ids
+// 1,876 against 1,532 (in its own order 1,432 and 1,458).
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
-__device__ __forceinline__ void sweep_long_wave(int32_t lpr, int32_t ldx, int32_t ldy, int64_t row, int32_t len,
-                                                const int32_t *__restrict__ col, const TW *__restrict__ val,
-                                                const TW *__restrict__ deg,
-                                                const TIN *__restrict__ x, const double *__restrict__ mean,
-                                                TO *__restrict__ y, TA keep, TA omega) {
-    constexpr int kSteps = VPL <= 4 ? 2 : 1;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int gw = kWave / lpr, g = lane / lpr, off = (lane - g * lpr) * VPL;
-    double mo[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) mo[i] = CENTER ? mean[off + i] : 0.0;
-    TA acc[4][VPL];
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) acc[w][i] = TA(0);
-    for (int32_t j = g; j < len; j += kSteps * 4 * gw) {
-        int32_t cj[kSteps * 4];
-        TA wj[kSteps * 4], xv[kSteps * 4][VPL];
-#pragma unroll
-        for (int q = 0; q < kSteps * 4; ++q) {
-            const int32_t jj = j + q * gw < len ? j + q * gw : len - 1;
-            cj[q] = col[jj];
-            wj[q] = cvt<TA>(val[jj]);
-        }
-#pragma unroll
-        for (int q = 0; q < kSteps * 4; ++q)
-            load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[q] * ldx + off, mo, xv[q]);
-#pragma unroll
-        for (int q = 0; q < kSteps * 4; ++q)
-            if (j + q * gw < len) {
-#pragma unroll
-                for (int i = 0; i < VPL; ++i) acc[q % 4][i] = madd(acc[q % 4][i], wj[q], xv[q][i]);
-            }
-    }
-    for (int st = 1; st < gw; st <<= 1)
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) acc[w][i] += __shfl_down(acc[w][i], st * lpr, kWave);
-    if (g == 0) {
-        TA sum[VPL];
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) sum[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
-        store_row<TIN, TX, TO, TA, VPL, CENTER>(x + row * ldx + off, mo, sum, cvt<TA>(deg[row]), y + row * ldy + off,
-                                                keep, omega);
-    }
-}
-
-template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, bool CENTER>
-__device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *part, int32_t lpr, int32_t lpr_log2,
-                                                int32_t ldx, int32_t ldy, const int32_t *__restrict__ long_rows,
+__device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *part, int32_t lpr, int32_t ldx,
+                                                int32_t ldy, const int32_t *__restrict__ long_rows,
                                                 const int32_t *__restrict__ long_cnt,
                                                 const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                 const TW *__restrict__ val, const TW *__restrict__ deg,
@@ -266,68 +194,61 @@ __device__ __forceinline__ void sweep_long_rows(int32_t wg, int32_t nwg, TA *par
 #pragma unroll
     for (int i = 0; i < VPL; ++i) mo[i] = (CENTER && active) ? mean[off + i] : 0.0;
     const int32_t cnt = *long_cnt;
-    const bool waves = lpr_log2 >= 0 && lpr <= kWave;
-    for (int64_t r0 = wg; r0 < cnt; r0 += 4 * (int64_t)nwg) {
-        if (waves) {
-            const int64_t r = r0 + (int64_t)(t / kWave) * nwg;
-            if (r < cnt) {
-                const int64_t row = long_rows[r];
-                const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
-                if (len <= kWaveRow)
-                    sweep_long_wave<TIN, TX, TO, TW, TA, VPL, CENTER>(lpr, ldx, ldy, row, len, col + j0, val + j0, deg,
-                                                                      x, mean, y, keep, omega);
-            }
-        }
-        for (int64_t r = r0; r < cnt && r < r0 + 4 * (int64_t)nwg; r += nwg) {
-            const int64_t row = long_rows[r];
-            const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
-            if (waves && len <= kWaveRow) continue;
-            const int32_t *cr = col + j0;
-            const TW *vr = val + j0;
-            TA acc[VPL];
+    for (int32_t r = wg; r < cnt; r += nwg) {
+        const int64_t row = long_rows[r];
+        const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
+        const int32_t *cr = col + j0;
+        const TW *vr = val + j0;
+        TA acc[VPL];
 #pragma unroll
-            for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
-            if (active) {
-                // four of the group's entries in flight, added in their order
-                for (int32_t j = g; j < len; j += 4 * ngroups) {
-                    int32_t cj[4];
-                    TA wj[4], xv[4][VPL];
+        for (int i = 0; i < VPL; ++i) acc[i] = TA(0);
+        if (active) {
+            // four of the group's entries in flight, added in their order
+            for (int32_t j = g; j < len; j += 4 * ngroups) {
+                int32_t cj[4];
+                TA wj[4], xv[4][VPL];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int32_t jj = j + i * ngroups < len ? j + i * ngroups : len - 1;
-                        cj[i] = cr[jj];
-                        wj[i] = cvt<TA>(vr[jj]);
+                for (int i = 0; i < 4; ++i) {
+                    const int32_t jj = j + i * ngroups < len ? j + i * ngroups : len - 1;
+                    cj[i] = cr[jj];
+                    wj[i] = cvt<TA>(vr[jj]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (j + i * ngroups < len) {
+#pragma unroll
+                        for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
                     }
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        load_row<TIN, TX, TA, VPL, CENTER>(x + (int64_t)cj[i] * ldx + off, mo, xv[i]);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (j + i * ngroups < len) {
-#pragma unroll
-                            for (int q = 0; q < VPL; ++q) acc[q] = madd(acc[q], wj[i], xv[i][q]);
-                        }
-                }
             }
+        }
 #pragma unroll
-            for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
-            __syncthreads();
-            for (int st = 1; st < ngroups; st <<= 1) {
-                if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
+        for (int i = 0; i < VPL; ++i) part[t * VPL + i] = acc[i];
+        __syncthreads();
+        for (int st = 1; st < ngroups; st <<= 1) {
+            if (active && (g % (2 * st)) == 0 && g + st < ngroups) {
 #pragma unroll
-                    for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
-                }
-                __syncthreads();
-            }
-            if (g == 0) {
-                TA sum[VPL];
-#pragma unroll
-                for (int i = 0; i < VPL; ++i) sum[i] = part[l * VPL + i];
-                store_row<TIN, TX, TO, TA, VPL, CENTER>(x + row * ldx + off, mo, sum, cvt<TA>(deg[row]),
-                                                        y + row * ldy + off, keep, omega);
+                for (int i = 0; i < VPL; ++i) part[t * VPL + i] += part[(t + st * lpr) * VPL + i];
             }
             __syncthreads();
         }
+        if (g == 0) {
+            TA self[VPL];
+            load_row<TIN, TX, TA, VPL, CENTER>(x + row * ldx + off, mo, self);
+            const TA d = cvt<TA>(deg[row]);
+            Vec<TO, VPL> out;
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                const TA a = keep * self[i];
+                const TA q = part[l * VPL + i] / d;
+                const TA bo = omega * q;
+                out.v[i] = cvt<TO>(a + bo);
+            }
+            *reinterpret_cast<Vec<TO, VPL> *>(y + row * ldy + off) = out;
+        }
+        __syncthreads();
     }
 }
 
@@ -343,20 +264,20 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
                                                const TW *__restrict__ deg, const TIN *__restrict__ x,
                                                const double *__restrict__ mean, TO *__restrict__ y, TA keep,
                                                TA omega) {
-    // LONG (reduced precision): the first nlong workgroups (a multiple of 8,
-    // so that the others keep their XCD) take the rows over max_len
+    // LONG (reduced precision): the last nlong workgroups take the rows over
+    // max_len
+    const uint32_t nb = gridDim.x - nlong;
     if constexpr (LONG) {
         __shared__ TA part[256 * VPL];
-        if (blockIdx.x < nlong) {
-            sweep_long_rows<TIN, TX, TO, TW, TA, VPL, CENTER>((int32_t)blockIdx.x, (int32_t)nlong, part, lpr,
-                                                             lpr_log2, ldx, ldy, long_rows, long_cnt, rowptr, col,
-                                                             val, deg, x, mean, y, keep, omega);
+        if (blockIdx.x >= nb) {
+            sweep_long_rows<TIN, TX, TO, TW, TA, VPL, CENTER>((int32_t)(blockIdx.x - nb), (int32_t)nlong, part, lpr,
+                                                             ldx, ldy, long_rows, long_cnt, rowptr, col, val, deg, x,
+                                                             mean, y, keep, omega);
             return;
         }
     }
-    const uint32_t lb = blockIdx.x - nlong, nb = gridDim.x - nlong;
     const bool chunks = dense && (uneven ? *uneven != 0 : xcd_uneven(rowptr, n));
-    const uint32_t b = chunks ? xcd_remap_chunked(lb, nb) : xcd_remap(lb, nb);
+    const uint32_t b = chunks ? xcd_remap_chunked(blockIdx.x, nb) : xcd_remap(blockIdx.x, nb);
     const int64_t t = (int64_t)b * 256 + threadIdx.x;
     if (t >= nthreads) return;
     const int64_t ri = lpr_log2 >= 0 ? (t >> lpr_log2) : t / lpr;
@@ -367,7 +288,7 @@ __global__ __launch_bounds__(256) void k_sweep(int64_t nthreads, int32_t lpr, in
 #pragma unroll
     for (int i = 0; i < VPL; ++i) mo[i] = CENTER ? mean[off + i] : 0.0;
     const int32_t j0 = rowptr[row], len = rowptr[row + 1] - j0;
-    if (len > max_len) return;      // a long row: taken by the workgroups above (FP64: k_sweep_hub64)
+    if (len > max_len) return;      // a long row: taken by other workgroups (FP64: k_sweep_hub64)
     col += j0;
     val += j0;
     TA self[VPL];
@@ -596,12 +517,14 @@ struct SweepShape {
 };
 
 // Workgroups for the hub rows (a grid-stride loop over the device-side list
-// of rows over 256 entries; in reduced precision the first workgroups of the
-// sweep's own launch).  Graphs averaging 8 or more entries per row (power-law
-// graphs and their dense coarse levels) get 16,384, so that many hub rows are
-// in flight at once: 355 against 377 ms for the 4M-node Chung-Lu hierarchy.
-// Others get 1,024, since every launch dispatches its workgroups even when
-// the list is empty: 16,384 there cost 1.4 us per sweep.  A multiple of 8.
+// of rows over 256 entries; in reduced precision the last workgroups of the
+// sweep's own launch, where an empty list delays nothing: in front of the other
+// rows the 20 sweeps of 32 FP16 vectors on the 400,000-point k-NN graph took
+// 2.03 ms, behind them 1.96).  Graphs averaging 8 or more entries per row
+// (power-law graphs and their dense coarse levels) get 16,384, so that many hub
+// rows are in flight at once: 165.7 ms for the 4M-node Chung-Lu hierarchy,
+// 167.5 with 4,096 (k-NN 1.95).  Others get 1,024, since every launch
+// dispatches its workgroups even when the list is empty.
 inline unsigned long_row_blocks(const sfg_csr *H) { return dense_rows(H) ? 16384u : 1024u; }
 
 template <typename TIN, typename TX, typename TO, typename TW, typename TA, int VPL, int U, bool CENTER, bool LONG>

@@ -46,7 +46,7 @@ def at_the_end(G):
     return End(G.n, G.nnz, G.rowptr, G.col, G.val, G.eid, G.deg)
 
 
-# the last row: taken by a lane group, by a wavefront (257 to 4096 entries) and by a workgroup
+# the last row: taken by a lane group and, in reduced precision from 257 entries on, by a workgroup
 @pytest.mark.parametrize("length", [3, 21, 257, 4096, 5000])
 @pytest.mark.parametrize("dt,k", [(torch.float32, 16), (torch.float32, 12), (torch.float32, 5), (torch.float64, 16),
                                   (torch.bfloat16, 16), (torch.float16, 24)])

@@ -1,5 +1,6 @@
 """Calls on shapes that a kernel's usual case does not cover take times of the usual order: hub rows that share one
-workgroup's nodes in a tree's layout, chains of hooks as long as the graph in the spanning forest."""
+workgroup's nodes in a tree's layout, chains of hooks as long as the graph in the spanning forest; and the sweeps of
+graphs without hub rows do not pay for the code that takes them."""
 import numpy as np
 import pytest
 import torch
@@ -63,3 +64,18 @@ def test_forest_of_one_chain(n):
         assert comps == 1 and int(tree.sum()) == n - 1
         t[name] = micros(lambda: S.sfg_spanning_tree(*a))
     assert t["chain"] <= 3.0 * t["random"], t
+
+
+def test_sweeps_without_hub_rows():
+    # 32 FP32 vectors and 16 FP64 ones are as many bytes; with the hub rows' registers in every row's way the FP32
+    # sweeps, which move less for the graph, took 1.18 times as long
+    import workloads as W
+    from paper_2008_07633_amd import sfg as S
+
+    g, t = W.mesh3d(80, 80, 80, seed=912), {}
+    for dt, k in ((torch.float32, 32), (torch.float64, 16)):
+        G = S.sfg_laplacian_csr(g.n, dev(g.u), dev(g.v), dev(g.w).to(dt))
+        x0 = dev(np.random.default_rng(913).standard_normal((g.n, k)))
+        out = torch.empty((g.n, k), dtype=dt, device="cuda")
+        t[dt] = micros(lambda: S.sfg_smooth(G, x0, 20, storage=dt, out=out))
+    assert t[torch.float32] <= 1.1 * t[torch.float64], t
