@@ -564,8 +564,9 @@ typedef struct {
                              Hierarchy (levels > 1): per level, the preorder of a spanning tree of G_l, for the
                              sweeps on G_l and on the level's sparsifier, when n_l >= 65536, the level's block
                              of k vectors exceeds 96 MiB (256 MiB on the coarse levels, whose spanning tree is
-                             computed for it), G_l's longest row is at most 32 times its average one and more
-                             than half of G_l's entries lie over 4096 rows from their own row.  The environment variable SFG_NODE_ORDER=0 / 1 forces
+                             computed for it), at most an eighth of G_l's entries lie in rows over 32 times its
+                             average one and more than half of its entries, in the other rows, lie over 4096
+                             rows from their own row.  The environment variable SFG_NODE_ORDER=0 / 1 forces
                              either.  Results are bit-identical either way: rows keep their entry order */
     int64_t n_scored;      /* candidates scored exactly (n_cand, or the surrogate's share) */
     int32_t surrogate_fallback;   /* a surrogate was given but was not usable: the plain path ran */

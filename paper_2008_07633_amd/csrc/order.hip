@@ -23,19 +23,9 @@ namespace {
 
 constexpr int kB = 256;
 
-// Entries of H whose column is more than `window` rows from their row;
-// one atomic add per workgroup onto *count (zeroed by the caller).
-__global__ void k_far_count(int64_t n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                            int64_t window, unsigned long long *count) {
+// Adds every thread's c onto *count, one atomic per workgroup.
+__device__ __forceinline__ void add_count(unsigned long long c, unsigned long long *count) {
     __shared__ unsigned long long part[kB / 64];
-    unsigned long long c = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
-        const int32_t a = rowptr[i], e = rowptr[i + 1];
-        for (int32_t j = a; j < e; ++j) {
-            const int64_t d = (int64_t)col[j] - i;
-            c += (d > window || d < -window) ? 1u : 0u;
-        }
-    }
     for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -44,6 +34,32 @@ __global__ void k_far_count(int64_t n, const int32_t *__restrict__ rowptr, const
         for (int w = 0; w < kB / 64; ++w) t += part[w];
         if (t) atomicAdd(count, t);
     }
+}
+
+// Entries of H whose column is more than `window` rows from their row, in rows
+// of at most max_len entries (*count zeroed by the caller).
+__global__ void k_far_count(int64_t n, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                            int64_t window, int32_t max_len, unsigned long long *count) {
+    unsigned long long c = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
+        const int32_t a = rowptr[i], e = rowptr[i + 1];
+        if (e - a > max_len) continue;
+        for (int32_t j = a; j < e; ++j) {
+            const int64_t d = (int64_t)col[j] - i;
+            c += (d > window || d < -window) ? 1u : 0u;
+        }
+    }
+    add_count(c, count);
+}
+
+// Entries of H in rows of more than len entries.
+__global__ void k_long_count(int64_t n, const int32_t *__restrict__ rowptr, int32_t len, unsigned long long *count) {
+    unsigned long long c = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < n; i += (int64_t)gridDim.x * kB) {
+        const int32_t l = rowptr[i + 1] - rowptr[i];
+        c += l > len ? (unsigned)l : 0u;
+    }
+    add_count(c, count);
 }
 
 __global__ void k_inverse_perm(int64_t n, const int32_t *__restrict__ order, int32_t *__restrict__ inv) {
@@ -111,10 +127,17 @@ __global__ void k_gather_block(int64_t n, int32_t k, const int32_t *__restrict__
 
 }  // namespace
 
-void far_entries(const sfg_csr *H, int64_t window, unsigned long long *count, hipStream_t s) {
+void far_entries(const sfg_csr *H, int64_t window, int32_t max_len, unsigned long long *count, hipStream_t s) {
     if (H->n <= 0) return;
     const uint32_t g = std::min<uint32_t>(grid_for(H->n, kB), 1024u);
-    hipLaunchKernelGGL(k_far_count, dim3(g), dim3(kB), 0, s, H->n, H->rowptr, H->col, window, count);
+    hipLaunchKernelGGL(k_far_count, dim3(g), dim3(kB), 0, s, H->n, H->rowptr, H->col, window, max_len, count);
+    SFG_LAUNCH_CHECK();
+}
+
+void long_row_entries(const sfg_csr *H, int32_t len, unsigned long long *count, hipStream_t s) {
+    if (H->n <= 0) return;
+    const uint32_t g = std::min<uint32_t>(grid_for(H->n, kB), 1024u);
+    hipLaunchKernelGGL(k_long_count, dim3(g), dim3(kB), 0, s, H->n, H->rowptr, len, count);
     SFG_LAUNCH_CHECK();
 }
 

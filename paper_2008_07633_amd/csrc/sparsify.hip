@@ -51,7 +51,8 @@ int smooth_ordered(const sfg_csr *H, const int32_t *order, int32_t k, int32_t sw
 double predicted_cone_share(const sfg_csr *H, int32_t sweeps, int64_t n_cand, const int32_t *cand,
                             const int32_t *u, const int32_t *v, double band, double limit, DevArena &A,
                             hipStream_t s);
-void far_entries(const sfg_csr *H, int64_t window, unsigned long long *count, hipStream_t s);
+void far_entries(const sfg_csr *H, int64_t window, int32_t max_len, unsigned long long *count, hipStream_t s);
+void long_row_entries(const sfg_csr *H, int32_t len, unsigned long long *count, hipStream_t s);
 void inverse_permutation(int64_t n, const int32_t *order, int32_t *inv, hipStream_t s);
 sfg_csr relabel_csr(const sfg_csr *H, const int32_t *order, const int32_t *inv, DevArena &A, hipStream_t s);
 void map_endpoints(int64_t m, const int32_t *inv, const int32_t *u, const int32_t *v, int32_t *nu, int32_t *nv,
@@ -366,12 +367,13 @@ struct StageClock {
 // The preorder is taken when the call plans at least kOrderMinLaunches
 // column-part sweep launches (sweeps x ceil(k / 8) x batches), the graph has
 // at least kOrderMinRows nodes and more than a quarter of the scoring graph's
-// entries reach beyond kNearRows rows of their own row.  The launch bound
-// comes from the 2M-point k-NN graph (20 sweeps of 32 vectors: 80 launches a
-// batch): the layout costs about 1.9 ns per node once and 0.4 ns per batch
-// (relabelled scoring graph, gathered start block) and saves about 10 ps per
-// node and launch; one batch ran 14.6 ms in the input numbering against
-// 16.6 ms in preorder, four batches 44.8 against 44.3 ms.
+// entries reach beyond kNearRows rows of their own row.  Measured with 20
+// sweeps, in the input numbering and in preorder (which includes the layout, the
+// relabelled graph and the gathered blocks): the 2M-point k-NN graph, FP64, 32
+// vectors (80 launches a batch), 11.0 and 11.6 ms in one batch, 38.3 and 35.7 in
+// four, 74.6 and 67.4 in eight; the 1000 x 1000 power grid with 16 vectors (40 a
+// batch), four batches, 7.3 and 6.8 ms, but 4.4 and 5.1 in FP32; a 160^3 mesh
+// 34.0 and 34.0, in FP32 20.7 and 23.7.  512 is on the safe side of all of them.
 // SFG_NODE_ORDER=0 keeps the input numbering, =1 always takes the preorder
 // (read at every call; tests use it).  Results do not depend on the choice.
 
@@ -415,21 +417,21 @@ void make_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, c
 // (`tree`: its edges marked 1; nullptr = compute the maximum one) is taken
 // when the level has at least kOrderMinRows nodes, its block of k vectors
 // exceeds kOrderMinBlock bytes (kOrderMinBlockNoTree when the tree would have
-// to be computed first), its longest row is at most kOrderMaxRow times the
-// average one and more than half of G_l's entries reach beyond kNearRows
-// rows.  On the 2M-point k-NN graph (ids random in space) the FP32 hierarchy
-// with 16 vectors and 20 sweeps takes 32.1 ms in preorder against 34.5 (FP64
-// 39.0 against 38.8).  Power-law graphs have no small-scale locality to gain:
-// the 4M-node Chung-Lu level 0 sweeps in 1.38 ms in preorder against 1.43 in
-// its own numbering (FP32), and the tree layout, relabelled rows and gathered
-// blocks cost its hierarchy 265 ms against 248 (FP64 513 against 460).  Their
-// hubs give them away: longest row 437 times the average, against 3 on the
-// k-NN graph.
+// to be computed first), at most an eighth of its entries lie in rows over
+// kOrderLongRow times the average one and more than half of G_l's entries reach
+// beyond kNearRows rows.  On the 2M-point k-NN graph (ids random in space) the
+// FP32 hierarchy of four levels with 16 vectors and 20 sweeps takes 23.9 ms in
+// preorder against 28.0 (FP64 30.8 against 31.5), with a hub of 10,000 more
+// neighbours 28.8 against 31.6 (FP64 52.0 against 51.2).  Power-law graphs have
+// no small-scale locality to gain: the 4M-node Chung-Lu hierarchy takes 202 ms
+// in preorder against 176 (FP64 375 against 286).  Their hubs give them away:
+// 19% of its entries lie in such rows (14% at 500,000 nodes), none of the k-NN
+// graph's, and 4% where one node of it has a million neighbours.
 // SFG_NODE_ORDER as above; results do not depend on the choice.  max_row: the
 // longest row, or -1 when the caller does not know it.
 constexpr double kOrderMinBlock = 96.0 * (1 << 20);
 constexpr double kOrderMinBlockNoTree = 256.0 * (1 << 20);
-constexpr int64_t kOrderMaxRow = 32;
+constexpr int64_t kOrderLongRow = 32, kOrderLongShare = 8;
 
 void level_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const double *w64, const sfg_csr *G,
                       const uint8_t *tree, int32_t k, sfg_dtype storage, int32_t max_row, NodeOrder *no, DevArena &A,
@@ -441,20 +443,21 @@ void level_node_order(int64_t n, int64_t m, const int32_t *u, const int32_t *v, 
     if (mode == 2) {
         const double block = (double)n * k * dtype_size(storage);
         if (n < kOrderMinRows || block <= (tree ? kOrderMinBlock : kOrderMinBlockNoTree)) return;
-        if (max_row < 0) {
-            int32_t *mr = A.alloc<int32_t>(1);
-            max_row_length(G, mr, s);
-            SFG_HIP(hipMemcpyAsync(&max_row, mr, 4, hipMemcpyDeviceToHost, s));
+        const int32_t long_row = (int32_t)std::min<int64_t>(kOrderLongRow * G->nnz / n, 0x7fffffff);
+        unsigned long long *cnt = A.alloc<unsigned long long>(2);
+        fill_i32((int32_t *)cnt, 4, 0, s);
+        const auto read = [&](const unsigned long long *p) {
+            unsigned long long h = 0;
+            SFG_HIP(hipMemcpyAsync(&h, p, 8, hipMemcpyDeviceToHost, s));
             SFG_HIP(hipStreamSynchronize(s));
+            return (int64_t)h;
+        };
+        if (max_row < 0 || max_row > long_row) {
+            long_row_entries(G, long_row, cnt, s);
+            if (kOrderLongShare * read(cnt) > G->nnz) return;
         }
-        if (max_row * n > kOrderMaxRow * G->nnz) return;
-        unsigned long long *far = A.alloc<unsigned long long>(1);
-        fill_i32((int32_t *)far, 2, 0, s);
-        far_entries(G, kNearRows, far, s);
-        unsigned long long far_h = 0;
-        SFG_HIP(hipMemcpyAsync(&far_h, far, 8, hipMemcpyDeviceToHost, s));
-        SFG_HIP(hipStreamSynchronize(s));
-        if (2 * far_h <= (unsigned long long)G->nnz) return;
+        far_entries(G, kNearRows, long_row, cnt + 1, s);
+        if (2 * read(cnt + 1) <= G->nnz) return;
     }
     if (!tree) {
         uint8_t *t = A.alloc<uint8_t>(m + 1);
@@ -497,7 +500,7 @@ ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t
     if (decide && mode == 2 && n >= kOrderMinRows && no->launches >= kOrderMinLaunches) {
         far = A.alloc<unsigned long long>(1);
         fill_i32((int32_t *)far, 2, 0, s);
-        far_entries(&G.H, kNearRows, far, s);
+        far_entries(&G.H, kNearRows, 0x7fffffff, far, s);
     }
     // FP64 sums hub rows through LDS only where they are known to exist: the
     // longest row comes back with the entry count

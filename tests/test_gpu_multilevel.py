@@ -115,3 +115,24 @@ def test_power_law_hierarchy_is_deterministic(S, storage):
         taus.append([r["tau"] for r in rep])
     assert all(np.array_equal(keeps[0], k) for k in keeps[1:])
     assert all(t == taus[0] for t in taus[1:])
+
+
+def test_one_hub_keeps_the_preorder(monkeypatch):
+    # ids of a mesh shuffled, one node beside 5,000 others: the rows that the tree's preorder serves are still nearly
+    # all of them (a power-law graph, an eighth of whose entries lie in such rows, keeps its own numbering)
+    from paper_2008_07633_amd import sfg as S
+
+    monkeypatch.delenv("SFG_NODE_ORDER", raising=False)
+    g, rng = W.mesh3d(74, 74, 74, seed=970), np.random.default_rng(971)
+    ids, far = rng.permutation(g.n), rng.choice(g.n - 1, 5000, replace=False) + 1
+    a, b = np.r_[ids[g.u], np.zeros(5000, int)], np.r_[ids[g.v], far]
+    key = np.unique(np.minimum(a, b).astype(np.int64) * g.n + np.maximum(a, b))
+    u, v = (key // g.n).astype(np.int32), (key % g.n).astype(np.int32)
+    w = rng.uniform(0.5, 2.0, key.size)
+    p = S.make_params(levels=2, k=32, sweeps=2, frac=0.05)
+    t = [torch.from_numpy(x).cuda() for x in (u, v, w)]
+    keep, rep = S.sfg_sparsify(g.n, *t, None, p)
+    assert rep[0]["node_order"] == 1
+    monkeypatch.setenv("SFG_NODE_ORDER", "0")
+    same, rep = S.sfg_sparsify(g.n, *t, None, p)
+    assert rep[0]["node_order"] == 0 and torch.equal(same, keep)
