@@ -1079,7 +1079,7 @@ struct FwdPlan {
 FwdPlan plan_fwd(Carver &c, int64_t n, sfg_dtype act) {
     FwdPlan p;
     const size_t s = dtype_size(act);
-    p.a = c.take<char>((size_t)n * kH * s);
+    p.a = act == SFG_F32 ? c.take<char>((size_t)n * kH * s) : nullptr;   // the BF16 layers aggregate in registers
     p.h1 = c.take<char>((size_t)n * kH * s);
     p.h2 = c.take<char>((size_t)n * kH * s);
     return p;

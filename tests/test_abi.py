@@ -195,3 +195,12 @@ def test_a_workspace_serves_smaller_graphs(L, op, m):
         assert need(small, m) <= need(large, m), (small, large)
     for n in sizes:
         assert need(n, m - 1) <= need(n, m) <= need(n, m + 1)
+
+
+def test_bf16_inference_holds_two_blocks(L):
+    """The BF16 layers keep the aggregate in registers: two blocks of 32 values a node, where FP32 has a third."""
+    from paper_2008_07633_amd import sfg
+
+    n = 1000000
+    assert sfg.sfg_workspace_bytes(sfg.OP_MPNN_FORWARD, n, 0, 0, sfg.BF16) < 2 * n * 32 * 2 + 4096
+    assert sfg.sfg_workspace_bytes(sfg.OP_MPNN_FORWARD, n, 0, 0, sfg.F32) >= 3 * n * 32 * 4
