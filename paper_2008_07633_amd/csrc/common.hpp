@@ -112,13 +112,14 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb) {
 
 // The same in chunks dealt round-robin: XCD x takes chunks x, x + 8, ... of
 // kXcdChunk consecutive logical blocks.  Every XCD then gets a sample of the
-// whole index range.  Blocks past the last whole round of chunks keep their
-// own index.
+// whole index range.  What is left of the last whole round of chunks, all of a
+// small graph among it, is one contiguous range per XCD.
 constexpr uint32_t kXcdChunk = 64;
 
 __device__ __forceinline__ uint32_t xcd_remap_chunked(uint32_t b, uint32_t nb) {
     constexpr uint32_t round = kNumXcd * kXcdChunk;
-    if (b >= nb / round * round) return b;
+    const uint32_t whole = nb / round * round;      // a multiple of 8: b and b - whole are on one XCD
+    if (b >= whole) return whole + xcd_remap(b - whole, nb - whole);
     const uint32_t x = b % kNumXcd, i = b / kNumXcd;
     return ((i / kXcdChunk) * kNumXcd + x) * kXcdChunk + i % kXcdChunk;
 }
