@@ -28,7 +28,7 @@ void radix_sort_pairs(uint64_t *keys, int32_t *vals, int64_t n, const int *shift
 size_t csr_workspace_bytes(int64_t n, int64_t m);
 void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
                const uint8_t *mask, int32_t *rowptr, int32_t *col, void *val, int32_t *eid, void *deg, void *ws,
-               size_t ws_bytes, hipStream_t s);
+               size_t ws_bytes, hipStream_t s, int64_t included = 0);
 size_t smooth_workspace_bytes(int64_t n, int32_t k, sfg_dtype storage);
 void smooth(const sfg_csr *H, int32_t k, int32_t sweeps, double omega, const double *x0, sfg_dtype storage,
             int32_t final_f32, void *x, void *ws, size_t ws_bytes, hipStream_t s, int32_t max_row);

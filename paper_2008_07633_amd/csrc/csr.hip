@@ -62,13 +62,20 @@ struct CsrPlan {
 // the 39.9M edges of the 4M-node Chung-Lu graph 9.65 ms edge-parallel, 3.55
 // sorted; its coarse graphs of 36.9M, 35.5M and 28.7M edges 10.6, 7.9 and 5.4
 // ms against 2.8, 2.6 and 1.9.  Below kSortMinEdges the sort's launches (five
-// per digit, about 4 us each) weigh more than the atomics; k-NN graphs (5.7
-// edges per node, no lower part over 32) build in 0.1 ms edge-parallel.
+// per digit, about 4 us each) weigh more than the atomics, and so they do where
+// a mask leaves under an eighth of the edges: of the 5.0M edges of the
+// 500,000-node Chung-Lu graph, the spanning tree takes 312 us sorted and 222
+// edge-parallel, 20% of the edges 367 and 473, all of them 548 and 1,211.  k-NN
+// graphs (5.7 edges per node, no lower part over 32) build in 0.1 ms
+// edge-parallel.
 constexpr int64_t kWalkDensity = 4;
 constexpr int64_t kSortDensity = 8;
+constexpr int64_t kSortShare = 8;
 constexpr int64_t kSortMinEdges = int64_t(1) << 18;
 
-bool csr_sorts(int64_t n, int64_t m) { return m > kSortDensity * n && m >= kSortMinEdges; }
+bool csr_sorts(int64_t n, int64_t m, int64_t included) {
+    return m > kSortDensity * n && m >= kSortMinEdges && kSortShare * included >= m;
+}
 
 CsrPlan plan_csr(Carver &c, int64_t n, int64_t m, bool sorts) {
     CsrPlan p;
@@ -778,9 +785,11 @@ size_t csr_workspace_bytes(int64_t n, int64_t m) {
     return std::max(walks.used, sorted.used) + 256;
 }
 
+// included: the edges that the mask leaves, as far as the caller knows (0: few,
+// or not known).
 void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
                const uint8_t *mask, int32_t *rowptr, int32_t *col, void *val, int32_t *eid, void *deg, void *ws,
-               size_t ws_bytes, hipStream_t s) {
+               size_t ws_bytes, hipStream_t s, int64_t included) {
     SFG_REQUIRE(n >= 1 && m >= 0, SFG_EINVAL, "laplacian_csr: need n >= 1 and m >= 0");
     SFG_REQUIRE(2 * m < (int64_t(1) << 31), SFG_EUNSUPPORTED, "laplacian_csr: 2*m must be < 2^31");
     SFG_REQUIRE(n < (int64_t(1) << 31) - 1, SFG_EUNSUPPORTED, "laplacian_csr: n must be < 2^31-1");
@@ -789,7 +798,7 @@ void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const v
     SFG_REQUIRE(rowptr && deg && (m == 0 || (u && v && w && col && val && eid)), SFG_EINVAL,
                 "laplacian_csr: null pointer");
     Carver c(ws);
-    const bool walk = m <= kWalkDensity * n, sorts = csr_sorts(n, m);
+    const bool walk = m <= kWalkDensity * n, sorts = csr_sorts(n, m, mask ? included : m);
     CsrPlan p = plan_csr(c, n, m, sorts);
     const dim3 gn(grid_for(n, 256)), b(256);
     fill_i32(p.zeroed, p.zeroed_len, 0, s);
@@ -864,7 +873,7 @@ extern "C" sfg_status sfg_laplacian_csr(int64_t n, int64_t m, const int32_t *u, 
                                         void *ws, size_t ws_bytes, void *stream) {
     return sfg::guard([&] {
         hipStream_t s = sfg::as_stream(stream);
-        sfg::build_csr(n, m, u, v, w, wt, mask, rowptr, col, val, eid, deg, ws, ws_bytes, s);
+        sfg::build_csr(n, m, u, v, w, wt, mask, rowptr, col, val, eid, deg, ws, ws_bytes, s, 0);
         if (nnz_out) {
             int32_t nnz = 0;
             SFG_HIP(hipMemcpyAsync(&nnz, rowptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s));

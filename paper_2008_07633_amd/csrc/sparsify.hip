@@ -17,7 +17,7 @@ size_t csr_workspace_bytes(int64_t n, int64_t m);
 size_t csr_select_workspace_bytes(int64_t n, int64_t m);
 void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const void *w, sfg_dtype wt,
                const uint8_t *mask, int32_t *rowptr, int32_t *col, void *val, int32_t *eid, void *deg, void *ws,
-               size_t ws_bytes, hipStream_t s);
+               size_t ws_bytes, hipStream_t s, int64_t included = 0);
 size_t smooth_workspace_bytes(int64_t n, int32_t k, sfg_dtype storage);
 size_t smooth_ordered_workspace_bytes(int64_t n, int32_t k, sfg_dtype storage);
 size_t color_workspace_bytes(int64_t n);
@@ -491,7 +491,8 @@ ScoringGraph scoring_graph(int64_t n, int64_t m, const int32_t *u, const int32_t
     void *val = A.raw((2 * m + 1) * dtype_size(vt));
     void *deg = A.raw(n * dtype_size(vt));
     const size_t wsb = csr_workspace_bytes(n, m);
-    build_csr(n, m, u, v, wv, vt, hmask, rowptr, col, val, eid, deg, A.raw(wsb), wsb, s);
+    build_csr(n, m, u, v, wv, vt, hmask, rowptr, col, val, eid, deg, A.raw(wsb), wsb, s,
+              known_nnz >= 0 ? known_nnz / 2 : m);
     ScoringGraph G;
     G.H = sfg_csr{n, 0, rowptr, col, val, eid, deg, vt};
     const int mode = node_order_mode();

@@ -47,3 +47,19 @@ def test_sorted_build_matches_host(n, m, hub, share, dtype):
     got = [x.cpu().numpy() for x in (H.rowptr, H.col[:H.nnz], H.val[:H.nnz], H.eid[:H.nnz], H.deg)]
     for a, b in zip(got, (ptr, col, val, eid, deg.astype(got[4].dtype))):
         assert np.array_equal(a, b)
+
+
+def test_masked_scoring_graphs_match_oracle(orc):
+    # inside a call that cannot tell how many edges its mask leaves (several rounds), the masked CSR of such a list is
+    # sorted too; a caller's mask, a spanning tree as a rule, takes the edge-parallel build
+    import workloads as W
+    from paper_2008_07633_amd import sfg as S
+
+    n, rounds, k, sweeps, frac = 2000, 3, 4, 4, 0.2
+    u, v, w = edge_list(n, (1 << 18) + 3000, 640, "first")
+    assert u.size > 8 * n and u.size >= 1 << 18
+    X0s = np.stack([W.random_block(n, k, 641 + r) for r in range(rounds)])
+    ref = orc.sparsify_rounds(n, u, v, w, list(X0s), rounds, sweeps, frac)
+    t = [torch.from_numpy(a).cuda() for a in (u, v, w, X0s)]
+    keep, _ = S.sfg_sparsify(n, *t, S.make_params(k=k, sweeps=sweeps, frac=frac, rounds=rounds))
+    assert np.array_equal(keep.cpu().numpy(), ref.keep)

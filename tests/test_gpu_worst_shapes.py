@@ -79,3 +79,20 @@ def test_sweeps_without_hub_rows():
         out = torch.empty((g.n, k), dtype=dt, device="cuda")
         t[dt] = micros(lambda: S.sfg_smooth(G, x0, 20, storage=dt, out=out))
     assert t[torch.float32] <= 1.1 * t[torch.float64], t
+
+
+def test_tree_csr_of_a_dense_list():
+    # the few edges that a spanning tree's mask leaves of a long list: sorting the list by digits took 0.83 of the whole
+    # list's time
+    import workloads as W
+    from paper_2008_07633_amd import sfg as S
+
+    g, t = W.chung_lu(50000, 500000, 2.2, seed=914), {}
+    assert g.m > 8 * g.n and g.m >= 1 << 18
+    u, v, w = dev(g.u), dev(g.v), dev(g.w)
+    tree, _ = S.sfg_spanning_tree(g.n, u, v, w)
+    ws = torch.empty(S.sfg_workspace_bytes(S.OP_LAPLACIAN_CSR, g.n, g.m, 0, w.dtype), dtype=torch.uint8, device="cuda")
+    for name, mask, nnz in (("all", None, 2 * g.m), ("tree", tree, 2 * (g.n - 1))):
+        out = S.sfg_laplacian_csr(g.n, u, v, w, mask=mask)
+        t[name] = micros(lambda: S.sfg_laplacian_csr(g.n, u, v, w, mask=mask, ws=ws, out=out, nnz=nnz))
+    assert t["tree"] <= 0.7 * t["all"], t
