@@ -52,3 +52,15 @@ def test_marks_with_a_ring(n, ring):
     with pytest.raises(S.SfgError) as e:
         S.sfg_tree_order(n, dev(u), dev(v), dev(np.ones(n - 1)), torch.ones(n - 1, dtype=torch.uint8, device="cuda"))
     assert e.value.name == "SFG_ENOTCONN"
+
+
+# 196608 nodes: 393214 arcs, the longest walk that is ranked by pointer jumping; splitters from 393216 on
+@pytest.mark.parametrize("n", [196608, 196609, 200003])
+@pytest.mark.parametrize("kind", ["path", "star", "random", "caterpillar"])
+def test_walk_order_at_the_bound(orc, kind, n):
+    test_walk_order(orc, kind, n)
+
+
+@pytest.mark.parametrize("ring", [3, 64, 100000])
+def test_marks_with_a_ring_by_splitters(ring):
+    test_marks_with_a_ring(250000, ring)
