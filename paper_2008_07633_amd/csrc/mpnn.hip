@@ -328,31 +328,49 @@ struct RowAhead {
 };
 
 // acc[i] += w x[i] over entries U, U + 1, ... of a row of len entries (counted
-// from its first: at 2^31 - 2 entries the last rows' indices step over 2^31), U
-// in flight
-template <int V, int U, typename LOAD>
+// from its first: at 2^31 - 2 entries the last rows' indices step over 2^31), B
+// in flight.  AHEAD: the next B columns and weights are loaded before the
+// gathered rows are added; a hub row is one chain, and its loads would be two
+// waits a step.  (Layer 2 where it has the registers: inference on the
+// 50,000-node Chung-Lu graph takes 500 us, 558 without.  In layer 1, where a
+// wavefront holds 64 rows of two loads an entry, it took 310 us for 290 on
+// 20,000 nodes, and so did more entries in flight.)  RAW: what load() returns
+// of a row, taken apart by add().
+template <int U, int B, bool AHEAD, typename RAW, typename LOAD, typename ADD>
 __device__ __forceinline__ void gather_rest(int32_t len, const int32_t *__restrict__ col,
-                                            const float *__restrict__ val, LOAD load, float (&acc)[V]) {
+                                            const float *__restrict__ val, LOAD load, ADD add) {
     if (len <= U) return;
-    for (int32_t j = U; j < len; j += U) {
-        int32_t cj[U];
-        float wj[U], xv[U][V];
+    int32_t cj[B];
+    float wj[B];
+    auto entries = [&](int32_t j) {
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
+        for (int i = 0; i < B; ++i) {
             const int32_t jj = j + i < len ? j + i : len - 1;
             cj[i] = col[jj];
             wj[i] = val[jj];
         }
+    };
+    if constexpr (AHEAD) entries(U);
+    for (int32_t j = U; j < len; j += B) {
+        RAW x[B];
+        float w[B];
+        if constexpr (!AHEAD) entries(j);
 #pragma unroll
-        for (int i = 0; i < U; ++i) load(cj[i], xv[i]);
+        for (int i = 0; i < B; ++i) {
+            load(cj[i], x[i]);
+            w[i] = wj[i];
+        }
+        if constexpr (AHEAD)
+            if (j + B < len) entries(j + B);
 #pragma unroll
-        for (int i = 0; i < U; ++i)
-            if (j + i < len) {
-#pragma unroll
-                for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(wj[i], xv[i][c], acc[c]);
-            }
+        for (int i = 0; i < B; ++i)
+            if (j + i < len) add(w[i], x[i]);
     }
 }
+
+struct Row8 {
+    float v[8];
+};
 
 // a[i] = acc[i] / d + 0 self[i]: the sweep's form with omega = 1, bit for bit,
 // with one reciprocal for all eight columns in divide_row's range.  After a
@@ -438,7 +456,12 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer1_mfma(int64_t n, 
             for (int i = 0; i < U; ++i)
                 if (i < cur.j1 - cur.j0) add(i);
         }
-        gather_rest<8, U>(cur.j1 - cur.j0, col + cur.j0, val + cur.j0, load, acc);
+        gather_rest<U, U, false, Row8>(
+            cur.j1 - cur.j0, col + cur.j0, val + cur.j0, [&](int64_t row, Row8 &o) { load(row, o.v); },
+            [&](float w, const Row8 &row) {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) acc[t] = __builtin_fmaf(w, row.v[t], acc[t]);
+            });
         float a[8];
         row_mean(acc, self, cur.d, a);
 #pragma unroll
@@ -493,7 +516,6 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
         wb[b] = bias_row(W[2 * kH * kH + 16 * b + c], q);
     }
     auto raw = [&](int64_t row) { return *reinterpret_cast<const uint4 *>(h1 + row * kH + 8 * q); };
-    auto load = [&](int64_t row, float (&o)[8]) { unpack8(raw(row), o); };
     const bool uneven = dense && xcd_uneven(rowptr, n);
     auto first = [&](uint32_t vb) {
         return ((int64_t)(uneven ? xcd_remap_chunked(vb, nvb) : xcd_remap(vb, nvb)) * 4 + wv) * 16;
@@ -534,7 +556,14 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
             for (int i = 0; i < U; ++i)
                 if (i < cur.j1 - cur.j0) add(i);
         }
-        gather_rest<8, U>(cur.j1 - cur.j0, col + cur.j0, val + cur.j0, load, acc);
+        gather_rest<U, U, (U > 4), uint4>(
+            cur.j1 - cur.j0, col + cur.j0, val + cur.j0, [&](int64_t row, uint4 &o) { o = raw(row); },
+            [&](float w, const uint4 &row) {
+                float xv[8];
+                unpack8(row, xv);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) acc[t] = __builtin_fmaf(w, xv[t], acc[t]);
+            });
         unpack8(own, self);
         row_mean(acc, self, cur.d, a);
         const bf16x4 item[4] = {operand4(own.x, own.y), operand4(own.z, own.w),
