@@ -842,11 +842,12 @@ void build_csr(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const v
         SFG_LAUNCH_CHECK();
     }
     exclusive_scan_i32(p.tot, rowptr, n, p.scan, s);
+    const EdgeSort *sorted = sorts ? &es : nullptr;
     if (wt == SFG_F64)
-        fill_entries<double>(walk, sorts ? &es : nullptr, n, m, u, v, (const double *)w, mask, p, rowptr, col, (double *)val, eid,
+        fill_entries<double>(walk, sorted, n, m, u, v, (const double *)w, mask, p, rowptr, col, (double *)val, eid,
                              (double *)deg, s);
     else
-        fill_entries<float>(walk, sorts ? &es : nullptr, n, m, u, v, (const float *)w, mask, p, rowptr, col, (float *)val, eid,
+        fill_entries<float>(walk, sorted, n, m, u, v, (const float *)w, mask, p, rowptr, col, (float *)val, eid,
                             (float *)deg, s);
 }
 

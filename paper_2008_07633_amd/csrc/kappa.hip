@@ -16,9 +16,9 @@
 // solve after the first started from the Ritz pairs (X = Y diag(theta)).
 // Every block lives in the tree's preorder: G and P are relabelled once, so
 // the tree solve needs no gathers and tree neighbours sit in nearby rows.
-// Seven launches per iteration: the direction, the Laplacian product on P
-// (with p . Ap), the CG update (with r . r and r's tile sums), the tree
-// solve's three and r . z.
+// Seven launches per iteration (tree.hip says where it is more): the direction,
+// the Laplacian product on P (with p . Ap), the CG update (with r . r and r's
+// tile sums), the tree solve's three and r . z.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -255,8 +255,12 @@ __global__ __launch_bounds__(kB) void k_cg_dir(int64_t n, int32_t k, int32_t fir
         p[t] = first ? z[t] : z[t] + beta * p[t];
 }
 
-// The update's workgroups add up to this many partial sums of p . Ap each
-// (8 columns: 128 KB); more are added by a launch of their own.
+// The update's workgroups add up to this many rows of partial sums of p . Ap each
+// (128 KB with 8 columns, 512 KB with 32); more are added by a launch of their
+// own.  Of 0 to 4,096 rows, 2,048 is within 2% of the best on 3,600 to 230,400
+// nodes with 4 to 32 columns (a launch saved is 2 us of an iteration of 60 to 80;
+// on 14,400 nodes with 32 columns, where 512 workgroups read them, 81 us for
+// 79); 4,096 takes 234 us for 176 on 90,000 nodes with 32.
 constexpr int32_t kPapRows = 2048;
 
 // r = z - L_H x
@@ -545,11 +549,11 @@ struct KappaEstimator {
                                active, dmask, M.rz, M.lanes, rz0, rz1, Zp, Pd);
             SFG_LAUNCH_CHECK();
             if (k % 2 == 0)
-                hipLaunchKernelGGL(k_cg_lap<2>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
-                                   part);
+                hipLaunchKernelGGL(k_cg_lap<2>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd,
+                                   AP, part);
             else
-                hipLaunchKernelGGL(k_cg_lap<1>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd, AP,
-                                   part);
+                hipLaunchKernelGGL(k_cg_lap<1>, dim3((uint32_t)lb), b, 0, s, n, k, P.rowptr, P.col, P.val, P.deg, Pd,
+                                   AP, part);
             SFG_LAUNCH_CHECK();
             std::swap(rz0, rz1);      // rz0: this iteration's r . z
             if (lb > kPapRows) finish_partials(lb, k, part, pap, s);

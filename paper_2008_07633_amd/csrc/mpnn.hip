@@ -573,7 +573,8 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[t][b], item[t], out[b], 0, 0, 0);
+            for (int b = 0; b < 2; ++b)
+                out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[t][b], item[t], out[b], 0, 0, 0);
 #pragma unroll
         for (int b = 0; b < 2; ++b) out[b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb[b], one, out[b], 0, 0, 0);
         const int64_t node = first(vb) + c;
@@ -592,7 +593,8 @@ __global__ __launch_bounds__(256, kLayerWaves(U)) void k_layer2_mfma(int64_t n, 
 // 16x16x16 right behind the 16x16x32 that writes its accumulator, without the
 // wait states the longer product needs, and with the edge features' product as
 // a 16x16x16 the sums lacked the products of hp * hq.
-__global__ __launch_bounds__(256, kHeadWaves) void k_head_mfma(int64_t ne, uint32_t nvb, const int32_t *__restrict__ cand,
+__global__ __launch_bounds__(256, kHeadWaves) void k_head_mfma(int64_t ne, uint32_t nvb,
+                                                   const int32_t *__restrict__ cand,
                                                    const int32_t *__restrict__ u, const int32_t *__restrict__ v,
                                                    const __hip_bfloat16 *__restrict__ h,
                                                    const float *__restrict__ ef, const float *__restrict__ W3,
@@ -1065,7 +1067,8 @@ __global__ __launch_bounds__(256) void k_grad_finish(int nb1, int nb2, int nb3, 
     __syncthreads();
     if (g == 0 && e < kParams + 1) {
         const int l = threadIdx.x;
-        const float t = ((sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l])) + ((sh[4][l] + sh[5][l]) + (sh[6][l] + sh[7][l]));
+        const float t =
+            ((sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l])) + ((sh[4][l] + sh[5][l]) + (sh[6][l] + sh[7][l]));
         if (e < kParams) grad[e] = t;
         else *loss = t * inv_ne;
     }

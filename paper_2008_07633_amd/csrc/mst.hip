@@ -410,10 +410,19 @@ __global__ __launch_bounds__(256) void k_mst_count(int64_t n, const int32_t *__r
     if (threadIdx.x == 0 && part) atomicAdd(cnt, part);
 }
 
-// Edge lists with fewer edges per node than this are taken in one part.
+// Edge lists with fewer edges per node than this are taken in one part.  In two
+// parts and in one, FP64: a power grid of 1M nodes thinned to 1.43 edges a node
+// 695 and 652 us, to 1.63 624 and 720; a 150^3 mesh thinned to 1.04 1,193 and
+// 1,153, whole (2.98) 1,629 and 3,125.
 constexpr double kSplitDensity = 1.6;
-constexpr int kRoundsFirst = 6;      // rounds on the first part (whatever is left joins the second)
-constexpr int kRoundsBlind = 4;      // rounds before the host first reads the list's length
+// Rounds on the first part (whatever is left joins the second).  With 3, 6 and
+// 10: the 150^3 mesh 1,972, 1,623 and 1,603 us, the 4M-node Chung-Lu graph
+// 5,303, 3,404 and 3,468; the 1M-node power grid 684, 734 and 789, the
+// 400,000-point k-NN graph 774, 811 and 859.
+constexpr int kRoundsFirst = 6;
+// Rounds before the host first reads the list's length, and between its reads
+// (1 to 8 and 1 to 6 differ by under 5% on these four graphs).
+constexpr int kRoundsBlind = 4;
 constexpr int kRoundsCheck = 3;
 
 template <typename TW>

@@ -629,7 +629,8 @@ void score_level(int64_t n, int64_t m, const int32_t *u, const int32_t *v, const
     void *x = A.raw((size_t)n * q->k * dtype_size(xt));
     // in the tree's preorder the Jacobi sweeps can take several per pass (smooth_ordered decides, same bits)
     const bool passes = no && no->use && q->smoother == SFG_SMOOTH_JACOBI;
-    size_t wss = passes ? smooth_ordered_workspace_bytes(n, q->k, q->storage) : smooth_workspace_bytes(n, q->k, q->storage);
+    size_t wss = passes ? smooth_ordered_workspace_bytes(n, q->k, q->storage)
+                        : smooth_workspace_bytes(n, q->k, q->storage);
     void *wsm = A.raw(wss);
     if (rep) clock.mark();
     if (q->smoother == SFG_SMOOTH_GAUSS_SEIDEL) {

@@ -712,10 +712,15 @@ void finish_partials(int32_t nb, int32_t k, const double *partial, double *out, 
 // All of them read a few MB, and an iteration is bound by the launches' own
 // latency, so a launch's small sums are added up by the workgroups of the
 // next one.  Conjugate gradients stopped at a loose tolerance carry the
-// rounding of every sum into their result, so each sum keeps the order that
-// block_scan and k_partials_finish give it, whatever launch it is in.
+// rounding of every sum into their result, so each sum that enters an iterate
+// keeps the order that block_scan and k_partials_finish give it, whatever launch
+// it is in; r . r, which only says when a column has converged, is added up
+// tile by tile.
 // On the 300 x 300 power grid (90,000 nodes, 8 columns) an iteration takes
-// 73 us in seven launches; it took 98 us in sixteen.
+// 73 us in seven launches; it took 98 us in sixteen.  (More launches: two for the
+// offsets of each prefix sum over kDirectGroups groups of tiles, one for r . z
+// beyond kDotPerLane, one for p . Ap beyond kPapRows, and the convergence test's
+// where there is one.)
 
 namespace {
 
@@ -800,8 +805,8 @@ __device__ __forceinline__ void tile_totals(const double *tile, const ByK &by, d
 // the order of k_scan_mid and k_scan_top; tot[c] then gets the sum of all
 // tiles up to this workgroup's group.  Else from those kernels' offsets.
 __device__ __forceinline__ void tile_offset(int64_t tiles, const double *__restrict__ tile_sum,
-                                            const double *__restrict__ group_off, const ByK &by, double *sh, double *off,
-                                            double *tot) {
+                                            const double *__restrict__ group_off, const ByK &by, double *sh,
+                                            double *off, double *tot) {
     const int k = by.k, G = by.div(kB);
     const int64_t b = blockIdx.x, tpg = (int64_t)G * kTpl;
     if (group_off) {

@@ -14,8 +14,8 @@ def dev(a):
 
 # selections by one workgroup (up to 16,384 candidates) and by passes
 @pytest.mark.parametrize("side", [40, 200])
-@pytest.mark.parametrize("kw", [dict(), dict(storage=torch.float32), dict(storage=torch.float16, final_f32=True, band=0.01),
-                                dict(levels=2)])
+@pytest.mark.parametrize("kw", [dict(), dict(storage=torch.float32), dict(levels=2),
+                                dict(storage=torch.float16, final_f32=True, band=0.01)])
 def test_keep_after_nan(side, kw):
     from paper_2008_07633_amd import sfg as S
 

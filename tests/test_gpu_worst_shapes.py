@@ -41,7 +41,8 @@ def test_layout_of_hub_rows():
     i = np.arange(1, n)
     random, ids = rng.integers(0, i), rng.permutation(n)
     leaf = np.arange(n - 256)
-    hubs = (np.r_[leaf, np.arange(n - 256, n - 1)], np.r_[n - 256 + rng.integers(0, 256, n - 256), np.arange(n - 255, n)])
+    hubs = (np.r_[leaf, np.arange(n - 256, n - 1)],
+            np.r_[n - 256 + rng.integers(0, 256, n - 256), np.arange(n - 255, n)])
     w, keep, t = dev(np.ones(n - 1)), torch.ones(n - 1, dtype=torch.uint8, device="cuda"), {}
     for name, (a, b) in {"random": (ids[i], ids[random]), "hubs": hubs}.items():
         u, v, _ = canonical(n, a, b)
