@@ -373,7 +373,9 @@ struct StageClock {
 // vectors (80 launches a batch), 11.0 and 11.6 ms in one batch, 38.3 and 35.7 in
 // four, 74.6 and 67.4 in eight; the 1000 x 1000 power grid with 16 vectors (40 a
 // batch), four batches, 7.3 and 6.8 ms, but 4.4 and 5.1 in FP32; a 160^3 mesh
-// 34.0 and 34.0, in FP32 20.7 and 23.7.  512 is on the safe side of all of them.
+// 34.0 and 34.0, in FP32 20.7 and 23.7.  In one batch the grid takes 2.5 ms both
+// ways (FP32 1.7 and 2.1), a 200^3 mesh 19.0 and 15.4 (FP32 12.9 and 13.0): 512
+// is on the safe side, and leaves such a mesh's gain.
 // SFG_NODE_ORDER=0 keeps the input numbering, =1 always takes the preorder
 // (read at every call; tests use it).  Results do not depend on the choice.
 
